@@ -9,7 +9,9 @@ namespace grouter {
 typedef uint16_t bf16_t;  // raw bfloat16 bit pattern
 
 constexpr int kMaxExperts = 1024;
-constexpr int kPlanChunk = 512;   // routed slots handled by one wave in the plan kernels
+constexpr int kPlanWaves = 16;       // waves of a plan workgroup; each takes a contiguous run of the workgroup's slots
+constexpr int kPlanOne = 4096;       // up to this many routed slots one workgroup builds the whole plan
+constexpr int kPlanMaxChunks = 256;  // beyond that the slots are cut into at most this many chunks, one per workgroup
 constexpr int kTileRowsSmall = 128;  // row-tile heights for which the plan keeps a tile list
 
 static inline __host__ __device__ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -19,7 +21,7 @@ struct PlanLayout {
     int64_t T;
     int k, E;
     int64_t N;
-    int n_chunks;
+    int n_chunks, chunk;    // chunks of `chunk` slots
     int max_tiles_small;    // upper bound on row tiles: N/rows + E
     size_t off_header;      // int32[64]: [0]=status flags, [1]=#row tiles, [2]=N, [3]=k, [4]=E the plan was built for
     size_t off_chunk_bad;   // int32[n_chunks]: chunk holds an id outside [0,E)
@@ -31,7 +33,7 @@ struct PlanLayout {
     size_t off_row_token;   // int32[N + 128] = row_to_src / k: the token whose row sits at each expert-sorted position
                             // (the last 128 are padding: a row tile's ids are fetched without a bounds check)
     size_t off_row_gate;    // fp32[N]: gate weight of the slot behind each row, once grouter_plan_set_gates has run
-    size_t off_chunk_hist;  // int32[E][n_chunks]; after the scan: exclusive base of each chunk inside its expert
+    size_t off_chunk_hist;  // int32[n_chunks][E]
     size_t off_tiles_small; // int32[max_tiles_small][8]: expert, the expert's first row, row count, first tile, tile count, 3 unused
     size_t total;
 };
@@ -39,7 +41,10 @@ struct PlanLayout {
 static inline __host__ PlanLayout make_plan_layout(int64_t T, int k, int E) {
     PlanLayout L{};
     L.T = T; L.k = k; L.E = E; L.N = T * (int64_t)k;
-    L.n_chunks = (int)((L.N + kPlanChunk - 1) / kPlanChunk);
+    const int64_t unit = kPlanWaves * 128;   // two 64-slot rounds per wave
+    const int64_t chunk = (L.N + unit * kPlanMaxChunks - 1) / (unit * kPlanMaxChunks) * unit;   // < 2^31 / 256 + 2048
+    L.chunk = (int)chunk;
+    L.n_chunks = (int)((L.N + chunk - 1) / chunk);
     L.max_tiles_small = (int)(L.N / kTileRowsSmall) + E;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };

@@ -2,13 +2,18 @@
 // slots (the cached top-k expert ids of Sec. 3.3.1), plus the row-tile list the grouped GEMMs walk.
 //
 // The scatter must reproduce the stable counting sort exactly (ties in ascending slot order), so ranks
-// come from prefix counts, never from the arrival order of atomics.  Three launches:
-//   1. hist     one wave per chunk of 512 consecutive slots -> chunk_hist[e][chunk], chunk_bad[chunk]
-//   2. finish   one workgroup: per expert an exclusive scan over its chunks (chunk_hist becomes the chunk's
-//               base inside the expert) and its count; then offsets, experts by descending load, the
-//               row-tile list and the header (status flag, tile count)
-//   3. scatter  one wave per chunk walks its slots 64 at a time in order; a lane's rank among the lanes
-//               of the same expert comes from wave ballots, the running per-expert cursor from LDS
+// come from prefix counts, never from the arrival order of atomics.
+//
+// What bounds a plan is latency: launches, dependent memory round trips, and the serial walk over a wave's slots.
+//   N <= kPlanOne   one launch of one workgroup: its 16 waves count their runs of slots in LDS, scan, and place
+//   larger N        two launches: k_plan_hist counts the chunks; then every chunk's workgroup adds up the counts of the
+//                   chunks before it (at most 256 x E numbers out of L2, cheaper than a launch of its own for a scan)
+//                   and places its slots, while one further workgroup writes counts, offsets, order and tile list
+// In the placing pass a wave walks its slots 64 at a time in order; a lane's rank among the lanes of the same expert
+// comes from wave ballots, the running per-expert cursor from the wave's own LDS column.
+// Back-to-back builds, three launches (histogram, finish, scatter) before and now: N = 6, E = 64 13.8 -> 7.8 us; N = 4995,
+// E = 60 16.9 -> 10.0; N = 49152, E = 64 19.1 -> 10.2; N = 131072, E = 128 37.4 -> 13.7.  One launch against two at N = 4995:
+// 10.7 against 10.0 us, at 8192: 16.7 against 10.3.
 // Nothing is accumulated into memory that an earlier launch must have cleared, so a plan can be rebuilt in
 // place and the build can be captured into a HIP graph as it is.
 #include "common.hpp"
@@ -26,31 +31,9 @@ __device__ __forceinline__ int load_expert(const IdxT* idx, int64_t i, int E, bo
     return e;
 }
 
-// chunk_hist is laid out [E][n_chunks] so that the scan over chunks of one expert reads contiguously.
-template <typename IdxT>
-__global__ __launch_bounds__(64) void k_plan_hist(const IdxT* __restrict__ idx, int64_t N, int E, int n_chunks,
-                                                  int32_t* __restrict__ chunk_hist, int32_t* __restrict__ chunk_bad) {
-    __shared__ int32_t cnt[kMaxExperts];
-    const int lane = threadIdx.x;
-    const int chunk = blockIdx.x;
-    for (int e = lane; e < E; e += 64) cnt[e] = 0;
-    __syncthreads();
-    const int64_t base = (int64_t)chunk * kPlanChunk;
-    bool bad = false;
-    for (int it = 0; it < kPlanChunk / 64; ++it) {
-        const int64_t i = base + it * 64 + lane;
-        if (i < N) atomicAdd(&cnt[load_expert(idx, i, E, &bad)], 1);
-    }
-    __syncthreads();
-    for (int e = lane; e < E; e += 64) chunk_hist[(size_t)e * n_chunks + chunk] = cnt[e];
-    const bool any_bad = __any(bad);
-    if (lane == 0) chunk_bad[chunk] = any_bad ? 1 : 0;
-}
+constexpr int kPlanThreads = kPlanWaves * 64;  // thread e <-> expert e (E <= 1024)
 
-constexpr int kFinishThreads = 1024;  // thread e <-> expert e (E <= 1024)
-constexpr int kFinishWaves = kFinishThreads / 64;
-
-// Exclusive prefix sum over the workgroup's threads; *total receives the sum.  s_w: kFinishWaves + 1 words.
+// Exclusive prefix sum over the workgroup's threads; *total receives the sum.  s_w: kPlanWaves + 1 words.
 __device__ __forceinline__ int block_exclusive_scan(int v, int32_t* s_w, int tid, int* total) {
     const int lane = tid & 63, wave = tid >> 6;
     int incl = v;
@@ -61,118 +44,178 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int32_t* s_w, int tid
     if (lane == 63) s_w[wave] = incl;
     __syncthreads();
     if (wave == 0) {
-        const int w = lane < kFinishWaves ? s_w[lane] : 0;
+        const int w = lane < kPlanWaves ? s_w[lane] : 0;
         int wi = w;
-        for (int o = 1; o < kFinishWaves; o <<= 1) {
+        for (int o = 1; o < kPlanWaves; o <<= 1) {
             const int up = __shfl_up(wi, o, 64);
             if (lane >= o) wi += up;
         }
-        if (lane < kFinishWaves) s_w[lane] = wi - w;
-        if (lane == kFinishWaves - 1) s_w[kFinishWaves] = wi;
+        if (lane < kPlanWaves) s_w[lane] = wi - w;
+        if (lane == kPlanWaves - 1) s_w[kPlanWaves] = wi;
     }
     __syncthreads();
     const int res = s_w[wave] + incl - v;
-    *total = s_w[kFinishWaves];
+    *total = s_w[kPlanWaves];
     __syncthreads();  // s_w may be reused right away
     return res;
 }
 
-// One workgroup finishes the counting: chunk scans, counts, offsets, load ranking, tile list, header.
-__global__ __launch_bounds__(kFinishThreads) void k_plan_finish(int E, int k, int N, int n_chunks, int32_t* __restrict__ chunk_hist,
-                                                                const int32_t* __restrict__ chunk_bad,
-                                                                int32_t* __restrict__ counts, int32_t* __restrict__ header,
-                                                                int32_t* __restrict__ offsets, int32_t* __restrict__ by_load,
-                                                                int32_t* __restrict__ tiles, int max_tiles) {
-    __shared__ int32_t s_cnt[kMaxExperts];
+// chunk_hist[chunk][e], chunk_bad[chunk]
+template <typename IdxT>
+__global__ __launch_bounds__(kPlanThreads) void k_plan_hist(const IdxT* __restrict__ idx, int64_t N, int E, int chunk,
+                                                            int32_t* __restrict__ chunk_hist, int32_t* __restrict__ chunk_bad) {
+    __shared__ int32_t cnt[kMaxExperts];
+    __shared__ int32_t s_bad;
+    const int tid = threadIdx.x;
+    if (tid < E) cnt[tid] = 0;
+    if (tid == 0) s_bad = 0;
+    __syncthreads();
+    const int64_t begin = (int64_t)blockIdx.x * chunk, end = min(N, begin + chunk);
+    bool bad = false;
+    for (int64_t i = begin + tid; i < end; i += kPlanThreads) atomicAdd(&cnt[load_expert(idx, i, E, &bad)], 1);
+    if (bad) atomicOr(&s_bad, 1);
+    __syncthreads();
+    if (tid < E) chunk_hist[(size_t)blockIdx.x * E + tid] = cnt[tid];
+    if (tid == 0) chunk_bad[blockIdx.x] = s_bad;
+}
+
+struct PlanOut {
+    int32_t* header; int32_t* counts; int32_t* offsets; int32_t* by_load;
+    int32_t* row_to_src; int32_t* src_to_row; int32_t* row_token;
+    int32_t* tiles; int max_tiles;
+};
+
+// ONE: the only workgroup, which does everything.  Otherwise workgroup c < n_chunks places chunk c and workgroup
+// n_chunks writes what concerns the plan as a whole.
+template <typename IdxT, bool ONE>
+__global__ __launch_bounds__(kPlanThreads) void k_plan_place(const IdxT* __restrict__ idx, int N, int E, int k, int bits, int chunk,
+                                                             int n_chunks, const int32_t* __restrict__ chunk_hist,
+                                                             const int32_t* __restrict__ chunk_bad, const PlanOut out) {
+    __shared__ int32_t s_hist[kPlanWaves * kMaxExperts];   // [wave][expert]: counts, then cursors
+    __shared__ __attribute__((aligned(16))) int32_t s_cnt[kMaxExperts];
     __shared__ int32_t s_off[kMaxExperts];
-    __shared__ int32_t s_order[kMaxExperts];  // expert id at each load rank
+    __shared__ int32_t s_before[kMaxExperts];     // slots of the expert in earlier chunks; later the load order
     __shared__ int32_t s_first[kMaxExperts + 1];  // first tile of each load rank
-    __shared__ int32_t s_w[kFinishWaves + 1];
+    __shared__ int32_t s_w[kPlanWaves + 1];
     __shared__ int32_t s_bad;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool place = ONE || (int)blockIdx.x < n_chunks;
+    const bool finish = ONE || (int)blockIdx.x == n_chunks;
+    const int64_t begin = ONE ? 0 : (int64_t)blockIdx.x * chunk;
+    const int64_t end = min((int64_t)N, ONE ? (int64_t)N : begin + chunk);
+    const int per_wave = (ONE ? (N + kPlanThreads - 1) / kPlanThreads : chunk / kPlanThreads) * 64;
+    const int64_t w_begin = begin + (int64_t)wave * per_wave, w_end = min(end, w_begin + per_wave);
+    int32_t* const my_hist = s_hist + wave * E;
+
     if (tid == 0) s_bad = 0;
-    // per expert: exclusive scan of its per-chunk counts (in place) and its total.  A wave takes four experts at
-    // a time and requests the first two 64-chunk blocks of all four before it scans any of them, so the global
-    // loads overlap instead of forming a chain of dependent round trips.
-    for (int e0 = wave; e0 < E; e0 += 4 * kFinishWaves) {
-        int v[4][2];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = e0 + i * kFinishWaves;
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int c = b * 64 + lane;
-                v[i][b] = (e < E && c < n_chunks) ? chunk_hist[(size_t)e * n_chunks + c] : 0;
+    s_cnt[tid] = tid < E ? 0 : -1;   // (no expert: ranks behind every expert)
+    if (!ONE && tid < E) s_before[tid] = 0;
+    if (place)
+        for (int e = lane; e < E; e += 64) my_hist[e] = 0;
+    __syncthreads();
+    bool bad = false;
+    if (place)
+        for (int64_t i = w_begin + lane; i < w_end; i += 64) atomicAdd(&my_hist[load_expert(idx, i, E, &bad)], 1);
+    if constexpr (!ONE) {
+        const int n = n_chunks * E, mine = (int)blockIdx.x * E;
+        for (int i = tid; i < n; i += kPlanThreads) {
+            const int v = chunk_hist[i], e = (int)((uint32_t)i % (uint32_t)E);
+            if (v) {
+                atomicAdd(&s_cnt[e], v);
+                if (i < mine) atomicAdd(&s_before[e], v);
             }
         }
+        if (finish)
+            for (int c = tid; c < n_chunks; c += kPlanThreads) bad |= chunk_bad[c] != 0;
+    }
+    if (bad) atomicOr(&s_bad, 1);
+    __syncthreads();
+    int cnt = 0;
+    if (tid < E) {
+        if constexpr (ONE) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = e0 + i * kFinishWaves;
-            if (e >= E) break;
-            int32_t* row = chunk_hist + (size_t)e * n_chunks;
-            int carry = 0;
-            for (int c0 = 0; c0 < n_chunks; c0 += 64) {
-                const int c = c0 + lane;
-                int val;
-                if (c0 == 0) val = v[i][0];
-                else if (c0 == 64) val = v[i][1];
-                else val = c < n_chunks ? row[c] : 0;
-                int incl = val;
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int up = __shfl_up(incl, o, 64);
-                    if (lane >= o) incl += up;
-                }
-                if (c < n_chunks) row[c] = carry + incl - val;
-                carry += __shfl(incl, 63, 64);
-            }
-            if (lane == 0) {
-                s_cnt[e] = carry;
-                counts[e] = carry;
-            }
+            for (int w = 0; w < kPlanWaves; ++w) cnt += s_hist[w * E + tid];
+            s_cnt[tid] = cnt;
+        } else {
+            cnt = s_cnt[tid];
         }
     }
-    __syncthreads();
-    int bad = 0;
-    for (int c = tid; c < n_chunks; c += kFinishThreads) bad |= chunk_bad[c];
-    if (bad) atomicOr(&s_bad, 1);
-    // offsets
-    const int cnt = tid < E ? s_cnt[tid] : 0;
     int total;
     const int off = block_exclusive_scan(cnt, s_w, tid, &total);
     if (tid < E) {
         s_off[tid] = off;
-        offsets[tid] = off;
-    }
-    if (tid == 0) offsets[E] = total;
-    // rank experts by load, heaviest first, ties by lower id
-    if (tid < E) {
-        int rank = 0;
-        for (int o = 0; o < E; ++o) {
-            const int co = s_cnt[o];
-            rank += (co > cnt) || (co == cnt && o < tid);
+        if (place) {
+            int run = off + (ONE ? 0 : s_before[tid]);
+#pragma unroll
+            for (int w = 0; w < kPlanWaves; ++w) {
+                const int t = s_hist[w * E + tid];
+                s_hist[w * E + tid] = run;
+                run += t;
+            }
         }
-        s_order[rank] = tid;
-        by_load[rank] = tid;
     }
     __syncthreads();
+    if (place) {
+        // the cursors of a wave are its own: no barrier between its rounds, LDS accesses of one wave stay in order
+        volatile int32_t* const cursor = my_hist;
+        const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+        for (int64_t i0 = w_begin; i0 < w_end; i0 += 64) {
+            const int64_t i = i0 + lane;
+            const bool valid = i < w_end;
+            bool bad_unused = false;  // already reported by the counting pass
+            const int e = valid ? load_expert(idx, i, E, &bad_unused) : 0;
+            uint64_t peers = __ballot(valid);
+            for (int b = 0; b < bits; ++b) {
+                const bool bit = (e >> b) & 1;
+                const uint64_t m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+            if (valid) {
+                const int p = cursor[e] + __popcll(peers & below);
+                out.row_to_src[p] = (int32_t)i;
+                out.src_to_row[i] = p;
+                out.row_token[p] = (int32_t)((uint32_t)i / (uint32_t)k);
+                if ((peers >> lane) == 1ull) cursor[e] = p + 1;  // highest lane of the group advances the cursor
+            }
+        }
+    }
+    if (!finish) return;
+
+    // offsets, load order, tile list, header
+    int32_t* const s_order = s_before;  // expert id at each load rank
+    if (tid < E) {
+        out.counts[tid] = cnt;
+        out.offsets[tid] = off;
+        // heaviest first, ties by lower id
+        int rank = 0;
+#pragma unroll 4
+        for (int o = 0; o < E; o += 4) {
+            const int4 co = *(const int4*)(s_cnt + o);
+            rank += ((co.x > cnt) | ((co.x == cnt) & (o < tid))) + ((co.y > cnt) | ((co.y == cnt) & (o + 1 < tid))) +
+                    ((co.z > cnt) | ((co.z == cnt) & (o + 2 < tid))) + ((co.w > cnt) | ((co.w == cnt) & (o + 3 < tid)));
+        }
+        s_order[rank] = tid;
+        out.by_load[rank] = tid;
+    }
+    if (tid == 0) out.offsets[E] = total;
+    __syncthreads();
     // row tiles in load-rank order: thread r owns the expert of rank r
-    const int e = tid < E ? s_order[tid] : 0;
-    const int rows = tid < E ? s_cnt[e] : 0;
+    const int rows = tid < E ? s_cnt[s_order[tid]] : 0;
     const int n_tiles = (rows + kTileRowsSmall - 1) / kTileRowsSmall;
     int total_tiles;
     const int t = block_exclusive_scan(n_tiles, s_w, tid, &total_tiles);
     if (tid == 0) {
-        header[0] = s_bad;  // every atomicOr above happened before the barriers inside the scans
-        header[1] = total_tiles;
-        header[2] = N;
-        header[3] = k;
-        header[4] = E;
+        out.header[0] = s_bad;
+        out.header[1] = total_tiles;
+        out.header[2] = N;
+        out.header[3] = k;
+        out.header[4] = E;
     }
     if (tid < E) s_first[tid] = t;
     if (tid == 0) s_first[E] = total_tiles;
     __syncthreads();
     // every tile is written by its own thread: find the load rank whose tile range holds tile ti
-    for (int ti = tid; ti < min(total_tiles, max_tiles); ti += kFinishThreads) {
+    for (int ti = tid; ti < min(total_tiles, out.max_tiles); ti += kPlanThreads) {
         int lo = 0, hi = E - 1;  // largest rank r with s_first[r] <= ti (ranks without tiles share their successor's start)
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -182,78 +225,33 @@ __global__ __launch_bounds__(kFinishThreads) void k_plan_finish(int E, int k, in
         // one 32-byte record per tile, the same for every tile of an expert: a kernel that is handed tile ti learns
         // from it where any other tile of that expert lies, with one load
         const int ex = s_order[lo];
-        int32_t* const rec = tiles + 8 * (size_t)ti;
-        rec[0] = ex;
-        rec[1] = s_off[ex];
-        rec[2] = s_cnt[ex];
-        rec[3] = s_first[lo];
-        rec[4] = s_first[lo + 1] - s_first[lo];
-        rec[5] = rec[6] = rec[7] = 0;
+        int4* const rec = (int4*)(out.tiles + 8 * (size_t)ti);
+        rec[0] = int4{ex, s_off[ex], s_cnt[ex], s_first[lo]};
+        rec[1] = int4{s_first[lo + 1] - s_first[lo], 0, 0, 0};
     }
 }
 
 template <typename IdxT>
-__global__ __launch_bounds__(64) void k_plan_scatter(const IdxT* __restrict__ idx, int64_t N, int E, int k, int bits,
-                                                     int n_chunks, const int32_t* __restrict__ chunk_base,
-                                                     const int32_t* __restrict__ offsets,
-                                                     int32_t* __restrict__ row_to_src, int32_t* __restrict__ src_to_row,
-                                                     int32_t* __restrict__ row_token) {
-    __shared__ int32_t cursor[kMaxExperts];
-    const int lane = threadIdx.x;
-    const int chunk = blockIdx.x;
-    for (int e = lane; e < E; e += 64) cursor[e] = offsets[e] + chunk_base[(size_t)e * n_chunks + chunk];
-    __syncthreads();
-    const int64_t base = (int64_t)chunk * kPlanChunk;
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int it = 0; it < kPlanChunk / 64; ++it) {
-        const int64_t i = base + it * 64 + lane;
-        const bool valid = i < N;
-        bool bad_unused = false;  // already reported by the histogram pass
-        const int e = valid ? load_expert(idx, i, E, &bad_unused) : 0;
-        uint64_t peers = __ballot(valid);
-        for (int b = 0; b < bits; ++b) {
-            const bool bit = (e >> b) & 1;
-            const uint64_t m = __ballot(bit);
-            peers &= bit ? m : ~m;
-        }
-        int p = 0;
-        if (valid) {
-            const int rank = __popcll(peers & below);
-            p = cursor[e] + rank;
-            row_to_src[p] = (int32_t)i;
-            src_to_row[i] = p;
-            row_token[p] = (int32_t)(i / k);
-        }
-        __syncthreads();
-        if (valid && (peers >> lane) == 1ull) cursor[e] = p + 1;  // highest lane of the group advances the cursor
-        __syncthreads();
+static void launch_plan_t(const IdxT* idx, const PlanLayout& L, char* b, hipStream_t s) {
+    int32_t* const hist = (int32_t*)(b + L.off_chunk_hist);
+    int32_t* const bad = (int32_t*)(b + L.off_chunk_bad);
+    const PlanOut out{(int32_t*)(b + L.off_header), (int32_t*)(b + L.off_counts), (int32_t*)(b + L.off_offsets),
+                      (int32_t*)(b + L.off_by_load), (int32_t*)(b + L.off_row_to_src), (int32_t*)(b + L.off_src_to_row),
+                      (int32_t*)(b + L.off_row_token), (int32_t*)(b + L.off_tiles_small), L.max_tiles_small};
+    int bits = 0;
+    while ((1 << bits) < L.E) ++bits;
+    if (L.N <= kPlanOne) {
+        hipLaunchKernelGGL((k_plan_place<IdxT, true>), dim3(1), dim3(kPlanThreads), 0, s, idx, (int)L.N, L.E, L.k, bits, L.chunk, 1, hist, bad, out);
+        return;
     }
+    hipLaunchKernelGGL(k_plan_hist<IdxT>, dim3((unsigned)L.n_chunks), dim3(kPlanThreads), 0, s, idx, L.N, L.E, L.chunk, hist, bad);
+    hipLaunchKernelGGL((k_plan_place<IdxT, false>), dim3((unsigned)L.n_chunks + 1), dim3(kPlanThreads), 0, s, idx, (int)L.N, L.E, L.k, bits,
+                       L.chunk, L.n_chunks, (const int32_t*)hist, (const int32_t*)bad, out);
 }
 
 hipError_t launch_plan_build(const void* idx, int idx_dtype, const PlanLayout& L, void* plan_ws, hipStream_t s) {
-    char* b = (char*)plan_ws;
-    int32_t* header = (int32_t*)(b + L.off_header);
-    int32_t* hist = (int32_t*)(b + L.off_chunk_hist);
-    int32_t* bad = (int32_t*)(b + L.off_chunk_bad);
-    int32_t* counts = (int32_t*)(b + L.off_counts);
-    int32_t* offsets = (int32_t*)(b + L.off_offsets);
-    int bits = 0;
-    while ((1 << bits) < L.E) ++bits;
-    const dim3 grid((unsigned)L.n_chunks), wave(64);
-    if (idx_dtype == 0)
-        hipLaunchKernelGGL(k_plan_hist<int32_t>, grid, wave, 0, s, (const int32_t*)idx, L.N, L.E, L.n_chunks, hist, bad);
-    else
-        hipLaunchKernelGGL(k_plan_hist<uint8_t>, grid, wave, 0, s, (const uint8_t*)idx, L.N, L.E, L.n_chunks, hist, bad);
-    hipLaunchKernelGGL(k_plan_finish, dim3(1), dim3(kFinishThreads), 0, s, L.E, L.k, (int)L.N, L.n_chunks, hist, (const int32_t*)bad, counts,
-                       header, offsets, (int32_t*)(b + L.off_by_load), (int32_t*)(b + L.off_tiles_small), L.max_tiles_small);
-    if (idx_dtype == 0)
-        hipLaunchKernelGGL(k_plan_scatter<int32_t>, grid, wave, 0, s, (const int32_t*)idx, L.N, L.E, L.k, bits,
-                           L.n_chunks, (const int32_t*)hist, (const int32_t*)offsets, (int32_t*)(b + L.off_row_to_src),
-                           (int32_t*)(b + L.off_src_to_row), (int32_t*)(b + L.off_row_token));
-    else
-        hipLaunchKernelGGL(k_plan_scatter<uint8_t>, grid, wave, 0, s, (const uint8_t*)idx, L.N, L.E, L.k, bits,
-                           L.n_chunks, (const int32_t*)hist, (const int32_t*)offsets, (int32_t*)(b + L.off_row_to_src),
-                           (int32_t*)(b + L.off_src_to_row), (int32_t*)(b + L.off_row_token));
+    if (idx_dtype == 0) launch_plan_t((const int32_t*)idx, L, (char*)plan_ws, s);
+    else launch_plan_t((const uint8_t*)idx, L, (char*)plan_ws, s);
     return hipGetLastError();
 }
 
