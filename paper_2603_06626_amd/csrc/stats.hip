@@ -104,22 +104,41 @@ __device__ __forceinline__ void load_token8(const IdxT* __restrict__ base, int64
     decode_token8(base, fetch_token8(base, t, k), k, E, e);
 }
 
+// Entropy of a sample's counts in bits: H = -sum p log2 p with p = c / n, i.e. log2(n) - (sum c log2 c) / n, from every
+// thread's part of n and of the sum; in thread 0.  The order of the additions is fixed.
+__device__ __forceinline__ double block_entropy(long long tot, double clogc, double* s_red, long long* s_tot, int tid) {
+    for (int o = 32; o > 0; o >>= 1) {
+        clogc += __shfl_xor(clogc, o);
+        tot += __shfl_xor(tot, o);
+    }
+    if ((tid & 63) == 0) {
+        s_red[tid >> 6] = clogc;
+        s_tot[tid >> 6] = tot;
+    }
+    __syncthreads();
+    double sum = 0.0;
+    long long n = 0;
+    for (int w = 0; w < kStatThreads / 64; ++w) {
+        sum += s_red[w];
+        n += s_tot[w];
+    }
+    return n > 0 ? log2((double)n) - sum / (double)n : 0.0;
+}
+
 // One workgroup per sample, one pass over its ids for both statistics:
-//   AFF    histogram of token membership, entropy of the normalised histogram (fp64, fixed summation order) and the
-//          sample's contribution to the global loads
+//   AFF    histogram of token membership, entropy of the normalised histogram (fp64, fixed summation order)
 //   PLACE  expert_nodes[e] has bit n set when expert e lives on node n, so the nodes a token reaches are the OR
 //          over its experts; per node the wave counts its lanes with one ballot
 template <class IdxT, bool AFF, bool PLACE>
 __global__ __launch_bounds__(kStatThreads) void k_sample_stats(const IdxT* __restrict__ idx, int L, int k, int E,
                                                                int32_t* __restrict__ counts, double* __restrict__ entropy,
-                                                               unsigned long long* __restrict__ loads,
                                                                const uint64_t* __restrict__ expert_nodes, int n_nodes,
                                                                int32_t* __restrict__ comm, int32_t* __restrict__ best_node) {
     __shared__ int32_t s_hist[AFF ? kMaxExperts : 1];
     __shared__ uint64_t s_nodes[PLACE ? kMaxExperts : 1];
     __shared__ int32_t s_comm[64];
-    __shared__ double s_red[kStatThreads];
-    __shared__ long long s_tot[kStatThreads];
+    __shared__ double s_red[kStatThreads / 64];
+    __shared__ long long s_tot[kStatThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int64_t s = blockIdx.x;
     if (AFF)
@@ -182,25 +201,203 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats(const IdxT* __res
         const int c = s_hist[e];
         counts[s * E + e] = c;
         if (c > 0) {
-            atomicAdd(&loads[e], (unsigned long long)c);
             tot += c;
             clogc += (double)c * log2((double)c);
         }
     }
-    s_red[tid] = clogc;
-    s_tot[tid] = tot;
+    const double h = block_entropy(tot, clogc, s_red, s_tot, tid);
+    if (tid == 0) entropy[s] = h;
+}
+
+// The same for k <= 8, E <= 247, at most 16 nodes and samples of at most 255 * 256 tokens, i.e. for everything the cached
+// format holds in practice.  The general kernel above is bound by LDS bank conflicts (64 lanes add to and look up random
+// experts: about five rounds per access) and by 28 compares per token.  Here
+//   * a word of the table is (node set << 16 | count) and every lane of a wave has a column of its own in it (R columns), so
+//     one conflict-free atomic per id counts the expert and returns its nodes;
+//   * ids that do not count (out of range, repeated, tokens past the end) go to a spare row;
+//   * repeats are detected four bytes at a time on the packed ids; only a wave that has one compares slot by slot;
+//   * a lane keeps its votes per node as bytes and adds them up at the end.
+// Measured on 2048 x 4096 tokens, k = 8, E = 128, uint8, 4 nodes: 82 -> 42 us (a lane-atomic costs about 20 cycles per wave even without conflicts).
+constexpr int kFastStatE = 247, kFastStatNodes = 16, kFastStatL = 255 * kStatThreads;
+
+// nonzero if two of the eight bytes of (x, y) are equal
+__device__ __forceinline__ uint32_t equal_bytes8(uint32_t x, uint32_t y) {
+    auto rot = [](uint32_t v, int n) { return __builtin_amdgcn_alignbyte(v, v, n); };
+    auto zero_bytes = [](uint32_t v) { return (v - 0x01010101u) & ~v; };   // bit 7 of the lowest zero byte is set
+    const uint32_t y1 = rot(y, 1), y2 = rot(y, 2);
+    const uint32_t z = zero_bytes(x ^ y) | zero_bytes(x ^ y1) | zero_bytes(x ^ y2) | zero_bytes(x ^ rot(y, 3)) |
+                       zero_bytes(x ^ rot(x, 1)) | zero_bytes(x ^ rot(x, 2)) | zero_bytes(y ^ y1) | zero_bytes(y ^ y2);
+    return z & 0x80808080u;
+}
+
+template <class IdxT, bool AFF, bool PLACE, int R>
+__global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __restrict__ idx, int L, int k, int E,
+                                                                int32_t* __restrict__ counts, double* __restrict__ entropy,
+                                                                const uint64_t* __restrict__ expert_nodes, int n_nodes,
+                                                                int32_t* __restrict__ comm, int32_t* __restrict__ best_node) {
+    constexpr int kRows = (R == 64 ? 128 : kFastStatE) + 1;
+    __shared__ __attribute__((aligned(16))) uint32_t s_tab[kRows * R];
+    __shared__ int32_t s_cnt[kRows];
+    __shared__ int32_t s_comm[kFastStatNodes];
+    __shared__ double s_red[kStatThreads / 64];
+    __shared__ long long s_tot[kStatThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t s = blockIdx.x;
+    const IdxT* base = idx + (size_t)s * L * k;
+    RawIds8 ahead{};
+    if (tid < L) ahead = fetch_token8(base, tid, k);
+    for (int i = tid; i < (E + 1) * (R / 4); i += kStatThreads) {
+        const int e = i / (R / 4);
+        const uint32_t w = PLACE && e < E ? (uint32_t)expert_nodes[e] << 16 : 0u;
+        reinterpret_cast<uint4*>(s_tab)[i] = uint4{w, w, w, w};
+    }
+    if (tid <= E) s_cnt[tid] = 0;
+    if (tid < kFastStatNodes) s_comm[tid] = 0;
     __syncthreads();
-    for (int w = kStatThreads / 2; w > 0; w >>= 1) {
+    uint32_t* const column = s_tab + (lane & (R - 1));
+    uint32_t votes[4] = {0u, 0u, 0u, 0u};
+    for (int t0 = 0; t0 < L; t0 += kStatThreads) {
+        const RawIds8 raw = ahead;
+        if (t0 + kStatThreads + tid < L) ahead = fetch_token8(base, t0 + kStatThreads + tid, k);
+        int e[8];
+        unpack_token8(base, raw, k, e);
+        const bool live = t0 + tid < L;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) e[j] = live ? (int)min((uint32_t)e[j], (uint32_t)E) : E;
+        uint32_t x, y;
+        if (sizeof(IdxT) == 1 && k == 8 && (reinterpret_cast<uintptr_t>(base) & 7u) == 0) {
+            x = (uint32_t)raw.e[0];
+            y = (uint32_t)raw.e[1];
+        } else {   // slots past k: values that no expert has
+            uint32_t p[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) p[j] = j < k ? (uint32_t)e[j] : 0xf8u + j;
+            x = p[0] | (p[1] << 8) | (p[2] << 16) | (p[3] << 24);
+            y = p[4] | (p[5] << 8) | (p[6] << 16) | (p[7] << 24);
+        }
+        if (__any(live && equal_bytes8(x, y))) {
+#pragma unroll
+            for (int j = 1; j < 8; ++j) {
+                bool dup = false;
+#pragma unroll
+                for (int i = 0; i < j; ++i) dup = dup || (e[i] == e[j]);
+                if (dup) e[j] = E;
+            }
+        }
+        uint32_t seen = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (j < k) {
+                if (AFF && PLACE) seen |= atomicAdd(&column[e[j] * R], 1u);
+                else if (AFF) atomicAdd(&column[e[j] * R], 1u);
+                else seen |= column[e[j] * R];
+            }
+        if (PLACE) {
+            const uint32_t reach = seen >> 16;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)   // four bits to four bytes
+                if (4 * q < n_nodes) votes[q] += (((reach >> (4 * q)) & 15u) * 0x00204081u) & 0x01010101u;
+        }
+    }
+    if (PLACE) {
+        for (int n = 0; n < n_nodes; ++n) {
+            const uint32_t w = (n >> 2) == 0 ? votes[0] : (n >> 2) == 1 ? votes[1] : (n >> 2) == 2 ? votes[2] : votes[3];
+            int v = (int)((w >> (8 * (n & 3))) & 255u);
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+            if (lane == 0) atomicAdd(&s_comm[n], v);
+        }
+    }
+    __syncthreads();
+    if (PLACE) {
+        if (tid < n_nodes) comm[s * n_nodes + tid] = s_comm[tid];
+        if (tid == 64) {
+            int best = 0, mx = -1;
+            for (int n = 0; n < n_nodes; ++n)
+                if (s_comm[n] > mx) {
+                    mx = s_comm[n];
+                    best = n;
+                }
+            best_node[s] = best;
+        }
+    }
+    if (!AFF) return;
+    // columns -> counts: a thread adds 16 words of a row (starting points rotated, so that the lanes use all banks)
+    constexpr int kParts = R / 16;
+    for (int i = tid; i < E * kParts; i += kStatThreads) {
+        uint32_t v = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint4 w = reinterpret_cast<const uint4*>(s_tab)[i * 4 + ((q + (i >> 2)) & 3)];
+            v += w.x + w.y + w.z + w.w;
+        }
+        const int e = i / kParts;
+        if (PLACE) v -= ((uint32_t)expert_nodes[e] << 16) * 16u;   // modulo 2^32; the count itself is below 2^16
+        atomicAdd(&s_cnt[e], (int)v);
+    }
+    __syncthreads();
+    long long tot = 0;
+    double clogc = 0.0;
+    if (tid < E) {
+        const int c = s_cnt[tid];
+        counts[s * E + tid] = c;
+        if (c > 0) {
+            tot = c;
+            clogc = (double)c * log2((double)c);
+        }
+    }
+    const double h = block_entropy(tot, clogc, s_red, s_tot, tid);
+    if (tid == 0) entropy[s] = h;
+}
+
+// loads[e] = sum over the samples of counts[s][e].  A workgroup owns 16 experts (one 64-byte segment of every row).
+constexpr int kLoadsCols = 16, kLoadsThreads = 1024;
+__global__ __launch_bounds__(kLoadsThreads) void k_loads(const int32_t* __restrict__ counts, int64_t S, int E,
+                                                         unsigned long long* __restrict__ loads) {
+    __shared__ unsigned long long s_sum[kLoadsThreads];
+    const int tid = threadIdx.x, e = (int)blockIdx.x * kLoadsCols + tid % kLoadsCols;
+    unsigned long long v = 0;
+    if (e < E)
+#pragma unroll 8
+        for (int64_t s = tid / kLoadsCols; s < S; s += kLoadsThreads / kLoadsCols) v += (unsigned long long)counts[s * E + e];
+    s_sum[tid] = v;
+    __syncthreads();
+    for (int w = kLoadsThreads / 2; w >= kLoadsCols; w >>= 1) {
+        if (tid < w) s_sum[tid] += s_sum[tid + w];
+        __syncthreads();
+    }
+    if (tid < kLoadsCols && e < E) loads[e] = s_sum[tid];
+}
+
+// loads and maxvio of few samples in one workgroup (one launch instead of two, 4 us): thread t adds up column t % E.
+__global__ __launch_bounds__(kLoadsThreads) void k_loads_maxvio(const int32_t* __restrict__ counts, int S, int E,
+                                                                unsigned long long* __restrict__ loads, double* __restrict__ out) {
+    __shared__ unsigned long long s_sum[kLoadsThreads], s_max[kLoadsThreads];
+    const int tid = threadIdx.x, per = kLoadsThreads / E;   // rows side by side
+    unsigned long long v = 0;
+    if (tid < per * E)
+#pragma unroll 8
+        for (int i = tid; i < S * E; i += per * E) v += (unsigned long long)counts[i];
+    s_sum[tid] = v;
+    __syncthreads();
+    v = 0;
+    if (tid < E) {
+        for (int r = 0; r < per; ++r) v += s_sum[r * E + tid];
+        loads[tid] = v;
+    }
+    __syncthreads();
+    s_sum[tid] = v;
+    s_max[tid] = v;
+    __syncthreads();
+    for (int w = kLoadsThreads / 2; w > 0; w >>= 1) {
         if (tid < w) {
-            s_red[tid] += s_red[tid + w];
-            s_tot[tid] += s_tot[tid + w];
+            s_max[tid] = s_max[tid + w] > s_max[tid] ? s_max[tid + w] : s_max[tid];
+            s_sum[tid] += s_sum[tid + w];
         }
         __syncthreads();
     }
     if (tid == 0) {
-        // H = -sum p log2 p with p = c / tot  =  log2(tot) - (sum c log2 c) / tot
-        const double n = (double)s_tot[0];
-        entropy[s] = s_tot[0] > 0 ? log2(n) - s_red[0] / n : 0.0;
+        const double mean = (double)s_sum[0] / (double)E;
+        out[0] = s_sum[0] > 0 ? ((double)s_max[0] - mean) / mean : 0.0;
     }
 }
 
@@ -392,27 +589,131 @@ __global__ __launch_bounds__(256) void k_coact_mirror(int E, unsigned long long*
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Greedy affinity grouping, one workgroup, thread j <-> source expert j.  Groups are filled one after the
-// other; a group starts with the lowest unassigned expert, then takes the unassigned expert with the
-// largest summed co-activation with its members (lowest number on ties).
+// Greedy affinity grouping.  Groups are filled one after the other; a group starts with the lowest unassigned expert, then
+// takes the unassigned expert with the largest summed co-activation with its members (lowest number on ties): a serial
+// chain of E_S rounds, so what counts is the length of one round.
+//
+// Up to 256 experts one wave runs it, lane l holding the experts l, l + 64, ...: a round is a maximum over the wave in six
+// DPP steps, ballots that find who holds it, and one row of the matrix from LDS (E_S <= 128, staged by the whole
+// workgroup first) or L2.  No barrier is involved.  Scores are exact in double below 2^53; a matrix with larger entries is
+// grouped in 64-bit integers by the same loop.  Measured, 128 -> 32 groups: 131 -> 31 us (a workgroup of 128 threads with
+// three barriers per round before).
+template <int ctrl, class V>
+__device__ __forceinline__ V dpp_max(V v) {
+    union { V v; int w[2]; } a, b;
+    a.v = v;
+    b.w[0] = __builtin_amdgcn_update_dpp(a.w[0], a.w[0], ctrl, 0xf, 0xf, false);
+    b.w[1] = __builtin_amdgcn_update_dpp(a.w[1], a.w[1], ctrl, 0xf, 0xf, false);
+    if constexpr (sizeof(V) == 8 && V(0.5) != V(0)) return __builtin_fmax(a.v, b.v);
+    else return b.v > a.v ? b.v : a.v;
+}
+// the maximum over the wave, in every lane
+template <class V>
+__device__ __forceinline__ V wave_max(V v) {
+    v = dpp_max<0x111>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row of 16
+    v = dpp_max<0x112>(v);
+    v = dpp_max<0x114>(v);
+    v = dpp_max<0x118>(v);
+    v = dpp_max<0x142>(v);   // row_bcast:15, row_bcast:31: lane 63 of the wave
+    v = dpp_max<0x143>(v);
+    union { V v; int w[2]; } a;
+    a.v = v;
+    a.w[0] = __builtin_amdgcn_readlane(a.w[0], 63);
+    a.w[1] = __builtin_amdgcn_readlane(a.w[1], 63);
+    return a.v;
+}
+
+// row(e, i): entry (e, lane + 64 i) of the matrix
+template <class V, int PER, class Row>
+__device__ __forceinline__ void fold_loop(int E_S, int E_T, int lane, int32_t* __restrict__ group_of, V lowest, Row row) {
+    uint64_t open[PER];   // unassigned experts, by lane
+#pragma unroll
+    for (int i = 0; i < PER; ++i) open[i] = __ballot(lane + 64 * i < E_S);
+    const int g_avg = E_S / E_T, n_extra = E_S % E_T;
+    int group[PER] = {};
+    for (int g = 0; g < E_T; ++g) {
+        const int size = g_avg + (g < n_extra ? 1 : 0);
+        V score[PER];
+        for (int m = 0; m < size; ++m) {
+            uint64_t best[PER];
+            if (m == 0) {   // every unassigned expert ties
+#pragma unroll
+                for (int i = 0; i < PER; ++i) best[i] = open[i];
+            } else {
+                V cand[PER], mx = lowest;
+#pragma unroll
+                for (int i = 0; i < PER; ++i) {
+                    cand[i] = ((open[i] >> lane) & 1) ? score[i] : lowest;
+                    mx = cand[i] > mx ? cand[i] : mx;
+                }
+                mx = wave_max(mx);
+#pragma unroll
+                for (int i = 0; i < PER; ++i) best[i] = __ballot(cand[i] == mx) & open[i];
+            }
+            int pick = -1;
+#pragma unroll
+            for (int i = PER - 1; i >= 0; --i)
+                if (best[i]) pick = 64 * i + (int)__builtin_ctzll(best[i]);
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                if (pick >> 6 == i) open[i] &= ~(1ull << (pick & 63));
+                if (pick == lane + 64 * i) group[i] = g;
+            }
+            if (m + 1 < size) {
+#pragma unroll
+                for (int i = 0; i < PER; ++i) {
+                    const V p = row(pick, i);
+                    score[i] = m == 0 ? p : score[i] + p;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        if (lane + 64 * i < E_S) group_of[lane + 64 * i] = group[i];
+}
+
+template <int PER>   // E_S <= 64 PER
+__global__ __launch_bounds__(1024) void k_fold_groups_wave(const long long* __restrict__ P, int E_S, int E_T, int32_t* __restrict__ group_of) {
+    constexpr bool STAGED = PER <= 2;
+    constexpr long long kExact = 1ll << 43;   // entries below this: sums of up to 1024 of them are exact in double
+    __shared__ double s_P[STAGED ? 64 * PER * 64 * PER : 1];
+    __shared__ int s_large;
+    const int tid = threadIdx.x;
+    if (tid == 0) s_large = 0;
+    __syncthreads();
+    bool large = false;
+    for (int i = tid; i < E_S * E_S; i += 1024) {
+        const long long v = P[i];
+        large |= v >= kExact || v <= -kExact;
+        if (STAGED) s_P[i] = (double)v;
+    }
+    if (large) s_large = 1;
+    __syncthreads();
+    if (tid >= 64) return;
+    auto entry = [&](int e, int i) { return (int64_t)e * E_S + min(tid + 64 * i, E_S - 1); };
+    if (s_large) {
+        fold_loop<long long, PER>(E_S, E_T, tid, group_of, -0x7fffffffffffffffLL - 1, [&](int e, int i) { return P[entry(e, i)]; });
+    } else {
+        fold_loop<double, PER>(E_S, E_T, tid, group_of, -1e300, [&](int e, int i) -> double {
+            if constexpr (STAGED) return s_P[entry(e, i)];
+            else return (double)P[entry(e, i)];
+        });
+    }
+}
+
+// More than 256 experts: one workgroup, thread j <-> source expert j.
 constexpr long long kNoCandidate = -0x7fffffffffffffffLL - 1;  // below every real score
 
-// THREADS >= E_S.  STAGED (E_S <= 128): the whole matrix is first copied into LDS, so a round's row read is an
-// LDS access instead of a global round trip on the critical path of E_S dependent rounds.
-template <int THREADS, bool STAGED>
+template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_fold_groups(const long long* __restrict__ P, int E_S, int E_T,
                                                          int32_t* __restrict__ group_of) {
     constexpr int kWaves = THREADS / 64;
     __shared__ long long s_key[kWaves];
     __shared__ int s_idx[kWaves];
     __shared__ int s_pick;
-    __shared__ long long s_P[STAGED ? 128 * 128 : 1];
     const int j = threadIdx.x;
     const int lane = j & 63, wave = j >> 6;
-    if (STAGED) {
-        for (int i = j; i < E_S * E_S; i += THREADS) s_P[i] = P[i];
-        __syncthreads();
-    }
     const bool real = j < E_S;
     bool assigned = !real;
     long long score = 0;
@@ -452,28 +753,49 @@ __global__ __launch_bounds__(THREADS) void k_fold_groups(const long long* __rest
                 assigned = true;
                 group_of[j] = g;
             }
-            if (real) score = (m == 0 ? 0 : score) + (STAGED ? s_P[pick * E_S + j] : P[(size_t)pick * E_S + j]);
+            if (real) score = (m == 0 ? 0 : score) + P[(size_t)pick * E_S + j];
             __syncthreads();  // s_pick, s_key are rewritten by the next round
         }
     }
 }
 
 // out[r][g] = sum over source experts e with group_of[e] == g of W[r][e], e ascending, fp32.
+// A workgroup takes 8 rows.  It first lists the members of every group in ascending order (the stable rank of an expert
+// among those of its group), so an output adds its own members only instead of looking at all E_S (2048 rows, 128 -> 32:
+// 12.1 -> 7.5 us).
+constexpr int kFoldRows = 8;
 __global__ __launch_bounds__(kStatThreads) void k_fold_weights(const float* __restrict__ W, const int32_t* __restrict__ group_of,
-                                                               int E_S, int E_T, float* __restrict__ out) {
-    __shared__ float s_w[kMaxExperts];
-    __shared__ int32_t s_g[kMaxExperts];
-    const int r = blockIdx.x;
-    for (int e = threadIdx.x; e < E_S; e += kStatThreads) {
-        s_w[e] = W[(size_t)r * E_S + e];
-        s_g[e] = group_of[e];
+                                                               int d, int E_S, int E_T, float* __restrict__ out) {
+    __shared__ float s_w[kFoldRows * kMaxExperts];
+    __shared__ __attribute__((aligned(16))) int32_t s_g[kMaxExperts];
+    __shared__ int32_t s_member[kMaxExperts], s_start[kMaxExperts];
+    const int tid = threadIdx.x;
+    const int r0 = (int)blockIdx.x * kFoldRows, rows = min(kFoldRows, d - r0);
+    for (int i = tid; i < rows * E_S; i += kStatThreads) s_w[i] = W[(size_t)r0 * E_S + i];
+    for (int e = tid; e < kMaxExperts; e += kStatThreads) {
+        s_g[e] = e < E_S ? group_of[e] : 0x7fffffff;
+        s_start[e] = E_S;   // a group without members
     }
     __syncthreads();
-    for (int g = threadIdx.x; g < E_T; g += kStatThreads) {
+    // place of expert e: the experts of lower groups, and those of its own group that come before it
+    for (int e = tid; e < E_S; e += kStatThreads) {
+        const int g = s_g[e];
+        int at = 0, before = 0;
+#pragma unroll 4
+        for (int o = 0; o < E_S; o += 4) {
+            const int4 v = *(const int4*)(s_g + o);
+            at += (v.x < g) + (v.y < g) + (v.z < g) + (v.w < g);
+            before += ((v.x == g) & (o < e)) + ((v.y == g) & (o + 1 < e)) + ((v.z == g) & (o + 2 < e)) + ((v.w == g) & (o + 3 < e));
+        }
+        s_member[at + before] = e;
+        if (before == 0 && (uint32_t)g < (uint32_t)E_T) s_start[g] = at;
+    }
+    __syncthreads();
+    for (int i = tid; i < rows * E_T; i += kStatThreads) {
+        const int r = i / E_T, g = i - r * E_T;
         float acc = 0.f;
-        for (int e = 0; e < E_S; ++e)
-            if (s_g[e] == g) acc += s_w[e];
-        out[(size_t)r * E_T + g] = acc;
+        for (int m = s_start[g]; m < E_S && s_g[s_member[m]] == g; ++m) acc += s_w[r * E_S + s_member[m]];
+        out[(size_t)r0 * E_T + i] = acc;
     }
 }
 
@@ -485,21 +807,39 @@ hipError_t launch_sample_stats(const void* idx, int idx_dtype, int64_t S, int L,
                                int32_t* comm, int32_t* best_node, hipStream_t s) {
     auto* l = reinterpret_cast<unsigned long long*>(loads);
     const dim3 grid((unsigned)S), block(kStatThreads);
-    if (counts) hipLaunchKernelGGL(k_fill_u64, dim3((E + 255) / 256), dim3(256), 0, s, l, (int64_t)E);
 #define GROUTER_STATS(T_, A_, P_)                                                                                  \
-    hipLaunchKernelGGL((k_sample_stats<T_, A_, P_>), grid, block, 0, s, (const T_*)idx, L, k, E, counts, entropy, l, \
+    hipLaunchKernelGGL((k_sample_stats<T_, A_, P_>), grid, block, 0, s, (const T_*)idx, L, k, E, counts, entropy,  \
                        expert_nodes, n_nodes, comm, best_node)
-    if (idx_dtype == 1) {
-        if (counts && comm) GROUTER_STATS(uint8_t, true, true);
-        else if (counts) GROUTER_STATS(uint8_t, true, false);
-        else GROUTER_STATS(uint8_t, false, true);
-    } else {
-        if (counts && comm) GROUTER_STATS(int32_t, true, true);
-        else if (counts) GROUTER_STATS(int32_t, true, false);
-        else GROUTER_STATS(int32_t, false, true);
-    }
+#define GROUTER_STATS8(T_, A_, P_, R_)                                                                             \
+    hipLaunchKernelGGL((k_sample_stats8<T_, A_, P_, R_>), grid, block, 0, s, (const T_*)idx, L, k, E, counts, entropy, \
+                       expert_nodes, n_nodes, comm, best_node)
+    const bool fast = k <= 8 && E <= kFastStatE && n_nodes <= kFastStatNodes && L <= kFastStatL;
+    // a column per lane where the table then fits 33 KB
+#define GROUTER_STATS_T(A_, P_)                                                      \
+    do {                                                                             \
+        if (idx_dtype == 1) {                                                        \
+            if (fast && E <= 128) GROUTER_STATS8(uint8_t, A_, P_, 64);               \
+            else if (fast) GROUTER_STATS8(uint8_t, A_, P_, 32);                      \
+            else GROUTER_STATS(uint8_t, A_, P_);                                     \
+        } else {                                                                     \
+            if (fast && E <= 128) GROUTER_STATS8(int32_t, A_, P_, 64);               \
+            else if (fast) GROUTER_STATS8(int32_t, A_, P_, 32);                      \
+            else GROUTER_STATS(int32_t, A_, P_);                                     \
+        }                                                                            \
+    } while (0)
+    if (counts && comm) GROUTER_STATS_T(true, true);
+    else if (counts) GROUTER_STATS_T(true, false);
+    else GROUTER_STATS_T(false, true);
+#undef GROUTER_STATS_T
+#undef GROUTER_STATS8
 #undef GROUTER_STATS
-    if (counts) hipLaunchKernelGGL(k_maxvio, dim3(1), dim3(kStatThreads), 0, s, l, E, maxvio);
+    // one workgroup reads 32 numbers per thread in 3 us; at 2048 x 128 it would take 17 against the 9 us of two launches
+    if (counts && S * E <= 32 * kLoadsThreads) {
+        hipLaunchKernelGGL(k_loads_maxvio, dim3(1), dim3(kLoadsThreads), 0, s, counts, (int)S, E, l, maxvio);
+    } else if (counts) {
+        hipLaunchKernelGGL(k_loads, dim3((unsigned)((E + kLoadsCols - 1) / kLoadsCols)), dim3(kLoadsThreads), 0, s, counts, S, E, l);
+        hipLaunchKernelGGL(k_maxvio, dim3(1), dim3(kStatThreads), 0, s, l, E, maxvio);
+    }
     return hipGetLastError();
 }
 
@@ -544,14 +884,15 @@ hipError_t launch_coactivation(const void* idx, int idx_dtype, int64_t T, int k,
 
 hipError_t launch_fold_groups(const int64_t* P, int E_S, int E_T, int32_t* group_of, hipStream_t s) {
     const long long* p = (const long long*)P;
-    if (E_S <= 128) hipLaunchKernelGGL((k_fold_groups<128, true>), dim3(1), dim3(128), 0, s, p, E_S, E_T, group_of);
-    else if (E_S <= 256) hipLaunchKernelGGL((k_fold_groups<256, false>), dim3(1), dim3(256), 0, s, p, E_S, E_T, group_of);
-    else hipLaunchKernelGGL((k_fold_groups<1024, false>), dim3(1), dim3(1024), 0, s, p, E_S, E_T, group_of);
+    if (E_S <= 64) hipLaunchKernelGGL(k_fold_groups_wave<1>, dim3(1), dim3(1024), 0, s, p, E_S, E_T, group_of);
+    else if (E_S <= 128) hipLaunchKernelGGL(k_fold_groups_wave<2>, dim3(1), dim3(1024), 0, s, p, E_S, E_T, group_of);
+    else if (E_S <= 256) hipLaunchKernelGGL(k_fold_groups_wave<4>, dim3(1), dim3(1024), 0, s, p, E_S, E_T, group_of);
+    else hipLaunchKernelGGL(k_fold_groups<1024>, dim3(1), dim3(1024), 0, s, p, E_S, E_T, group_of);
     return hipGetLastError();
 }
 
 hipError_t launch_fold_weights(const float* W, const int32_t* group_of, int d, int E_S, int E_T, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_fold_weights, dim3((unsigned)d), dim3(kStatThreads), 0, s, W, group_of, E_S, E_T, out);
+    hipLaunchKernelGGL(k_fold_weights, dim3((unsigned)((d + kFoldRows - 1) / kFoldRows)), dim3(kStatThreads), 0, s, W, group_of, d, E_S, E_T, out);
     return hipGetLastError();
 }
 

@@ -1,0 +1,57 @@
+"""Routing statistics at the sizes where their kernels change, against oracle/routing_stats.py (same bars as there)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from oracle import routing_stats as rs                      # noqa: E402
+from paper_2603_06626_amd import binding as b               # noqa: E402
+from tests.test_gpu_routing_stats import DEV, check_all     # noqa: E402
+
+
+@pytest.mark.parametrize("S,L,k,E,n_nodes,dtype", [
+    (3, 255, 8, 128, 16, np.uint8),     # widest table with a column per lane, one token short of a workgroup
+    (3, 257, 8, 129, 4, np.uint8),      # narrower table
+    (2, 300, 8, 247, 16, np.int32),     # last E of the packed form
+    (2, 300, 8, 248, 4, np.uint8),      # general kernel by E
+    (2, 100, 9, 64, 4, np.uint8),       # by k
+    (2, 100, 8, 64, 17, np.int32),      # by the number of nodes
+    (1, 65280, 2, 5, 3, np.uint8),      # longest sample whose votes fit a byte per lane
+    (1, 65281, 2, 5, 3, np.uint8),
+    (4, 1, 1, 1, 1, np.int32),
+    (512, 3, 2, 64, 4, np.uint8),       # loads in one workgroup
+    (513, 3, 2, 64, 4, np.uint8),       # and in two launches
+])
+def test_statistics_at_the_edges_of_their_kernels(S, L, k, E, n_nodes, dtype):
+    rng = np.random.default_rng(E + k)
+    idx = rng.integers(0, E, size=(S, L, k)).astype(dtype)      # repeated ids inside tokens occur
+    idx[:, L // 2:] = np.sort(idx[:, L // 2:], axis=2)[:, :, ::-1]
+    perm = rng.permutation(E)
+    check_all(idx, E, [perm[n::n_nodes] for n in range(n_nodes)], E_T_list=(max(1, E // 5),), label=f"{S}x{L}x{k} E={E}")
+
+
+@pytest.mark.parametrize("E_S,E_T,scale", [(1, 1, 1), (63, 5, 1), (64, 64, 1), (65, 7, 1), (128, 1, 1), (129, 40, 1), (256, 100, 1),
+                                           (257, 60, 1), (128, 31, 1 << 44), (200, 9, 1 << 44)])
+def test_fold_groups_sizes_ties_and_large_entries(E_S, E_T, scale):
+    """Few distinct values make many ties; entries of 2^44 and more do not fit the fp64 form of the loop exactly."""
+    rng = np.random.default_rng(E_S)
+    P = rng.integers(0, 4, size=(E_S, E_S)).astype(np.int64) * scale + (rng.integers(0, 2, size=(E_S, E_S)) if scale > 1 else 0)
+    P = P + P.T
+    grp = torch.full((E_S,), -1, dtype=torch.int32, device=DEV)
+    b.grouter_fold_groups(torch.from_numpy(P).to(DEV), E_T, grp)
+    assert (grp.cpu().numpy() == rs.fold_groups(P, E_T)).all()
+
+
+def test_fold_weights_with_groups_that_have_no_members():
+    rng = np.random.default_rng(0)
+    d, E_S, E_T = 13, 40, 12
+    grp = rng.choice([0, 3, 11, 7], size=E_S).astype(np.int32)
+    W = rng.standard_normal((d, E_S), dtype=np.float32)
+    out = torch.full((d, E_T), float("nan"), dtype=torch.float32, device=DEV)
+    b.grouter_fold_weights(torch.from_numpy(W).to(DEV), torch.from_numpy(grp).to(DEV), E_T, out)
+    ref = np.zeros((d, E_T))
+    for e in range(E_S):
+        ref[:, grp[e]] += W[:, e]
+    # at most 40 fp32 additions of relative error 2^-24 each
+    assert np.abs(out.cpu().numpy() - ref).max() <= 40 * 2.0 ** -24 * np.abs(W).sum(axis=1).max()
