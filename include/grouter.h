@@ -233,10 +233,10 @@ enum {
     GROUTER_PH_DOWN = 3,      /* O = H W2 */
     GROUTER_PH_COMBINE = 4,   /* y */
     GROUTER_PH_DO = 5,        /* grouter_permute with gate weights */
-    GROUTER_PH_DH = 6,        /* dH GEMM + dSwiGLU */
-    GROUTER_PH_DW2 = 7,
-    GROUTER_PH_DW13 = 8,
-    GROUTER_PH_DXP = 9,
+    GROUTER_PH_DW2_DH = 6,    /* one launch: dW2, and dH GEMM + dSwiGLU */
+    GROUTER_PH_DW2 = 7,       /* unused: part of GROUTER_PH_DW2_DH */
+    GROUTER_PH_DW13 = 8,      /* unused: part of GROUTER_PH_DW13_DXP */
+    GROUTER_PH_DW13_DXP = 9,  /* one launch: dW1, dW3, and dXp */
     GROUTER_PH_DXREDUCE = 10,
     GROUTER_PH_AFFINITY = 11,  /* affinity counts, entropy, loads, MaxVio */
     GROUTER_PH_PLACEMENT = 12,

@@ -394,19 +394,12 @@ int grouter_moe_bwd(const void* plan_ws, int64_t T, int k, int E, int d, int f, 
     bf16_t* dU = (bf16_t*)(w + B.du);
     bf16_t* dXp = (bf16_t*)(w + B.dxp);
     hipError_t e;
-    // dW2 needs nothing from dH and runs first, so that dG and dU are consumed by the two kernels right behind the one
-    // that writes them (measured on the 8192-token, 64-expert training shape: dW2 -2 %, the others unchanged)
-    PhaseTimer t_dw2(GROUTER_PH_DW2, s);
-    e = launch_dw2(P, d, f, H, (const bf16_t*)dY, (bf16_t*)dW2, s);
+    PhaseTimer t_dh(GROUTER_PH_DW2_DH, s);
+    e = launch_dw2_dh(P, d, f, (const bf16_t*)dY, gate_w ? (const float*)(c + C.row_gate) : P.row_gate, H, (const bf16_t*)W2, dSdG, dSdU,
+                      (bf16_t*)dW2, dG, dU, s);
     if (e != hipSuccess) return fail_hip(e);
-    PhaseTimer t_dh(GROUTER_PH_DH, s, &t_dw2);
-    e = launch_dh(P, d, f, (const bf16_t*)dY, gate_w ? (const float*)(c + C.row_gate) : P.row_gate, (const bf16_t*)W2, dSdG, dSdU, dG, dU, s);
-    if (e != hipSuccess) return fail_hip(e);
-    PhaseTimer t_dw13(GROUTER_PH_DW13, s, &t_dh);
-    e = launch_dw13(P, d, f, (const bf16_t*)x, dG, dU, (bf16_t*)dW1, (bf16_t*)dW3, s);
-    if (e != hipSuccess) return fail_hip(e);
-    PhaseTimer t_dxp(GROUTER_PH_DXP, s, &t_dw13);
-    e = launch_dxp(P, d, f, dG, dU, (const bf16_t*)W1, (const bf16_t*)W3, dXp, s);
+    PhaseTimer t_dxp(GROUTER_PH_DW13_DXP, s, &t_dh);
+    e = launch_dw13_dxp(P, d, f, (const bf16_t*)x, dG, dU, (const bf16_t*)W1, (const bf16_t*)W3, (bf16_t*)dW1, (bf16_t*)dW3, dXp, s);
     if (e != hipSuccess) return fail_hip(e);
     PhaseTimer t_dx(GROUTER_PH_DXREDUCE, s, &t_dxp);
     e = launch_combine(P, d, dXp, nullptr, (bf16_t*)dX, s);
@@ -532,7 +525,7 @@ int grouter_timing_read(double* ms, int64_t* launches) {
 
 const char* grouter_phase_name(int phase) {
     static const char* names[GROUTER_PH_COUNT] = {"plan", "permute", "gateup", "down", "combine", "dO",
-                                                  "dH", "dW2", "dW13", "dXp", "dX_reduce", "affinity",
+                                                  "dW2+dH", "dW2", "dW13", "dW13+dXp", "dX_reduce", "affinity",
                                                   "placement", "coactivation", "fold", "sample_stats"};
     return (phase >= 0 && phase < GROUTER_PH_COUNT) ? names[phase] : "?";
 }

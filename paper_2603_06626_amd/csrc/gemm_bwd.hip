@@ -1,9 +1,12 @@
-// Backward grouped GEMMs over rows: dH = gate * (dY rows) W2_e^T with the dSwiGLU epilogue, and dXp = dG W1_e^T + dU W3_e^T.
+// Backward grouped GEMMs, in two launches of two products each: dW2_e = (gate * H)_e^T dY_e together with
+// dH = gate * (dY rows) W2_e^T and its dSwiGLU epilogue; then dW1_e = x_e^T dG_e, dW3_e = x_e^T dU_e together with
+// dXp = dG W1_e^T + dU W3_e^T.  x_e and dY_e are the expert's rows of the token-ordered x and dY, read through the
+// plan's row map.
 #include "gemm_kernels.hpp"
 
 namespace grouter {
 
-static RowsArgs base_args(const PlanView& P) {
+static RowsArgs rows_args(const PlanView& P) {
     RowsArgs a{};
     a.tiles = P.tiles_small;
     a.max_tiles = P.max_tiles_small;
@@ -11,27 +14,60 @@ static RowsArgs base_args(const PlanView& P) {
     return a;
 }
 
+static DwArgs dw_args(const PlanView& P) {
+    DwArgs a{};
+    a.plan = P.dims();
+    a.by_load = P.by_load;
+    a.offsets = P.offsets;
+    a.counts = P.counts;
+    a.row_token = P.row_token;
+    a.n_experts = P.E;
+    return a;
+}
+
 static unsigned rows_grid(const PlanView& P, int n_ntiles) { return (unsigned)P.max_tiles_small * (unsigned)n_ntiles; }
 
-hipError_t launch_dh(const PlanView& P, int d, int f, const bf16_t* dY, const float* row_gate, const bf16_t* W2,
-                     const bf16_t* dSdG, const bf16_t* dSdU, bf16_t* dG, bf16_t* dU, hipStream_t s) {
-    RowsArgs a = base_args(P);
+// 8 XCDs x (largest per-XCD share): the share pattern repeats every 4 experts
+static unsigned dw_grid(int E, int n_mt, int n_nt) {
+    int worst = 0;
+    for (int x = 0; x < 8; ++x) {
+        int per_quad = 0;
+        for (int tq = 0; tq < 4; ++tq) per_quad += DwShare(x, tq, n_mt, n_nt).tiles();
+        worst = per_quad > worst ? per_quad : worst;
+    }
+    return 8u * (unsigned)(((E + 3) / 4) * worst);
+}
+
+hipError_t launch_dw2_dh(const PlanView& P, int d, int f, const bf16_t* dY, const float* row_gate, const bf16_t* H, const bf16_t* W2,
+                         const bf16_t* dSdG, const bf16_t* dSdU, bf16_t* dW2, bf16_t* dG, bf16_t* dU, hipStream_t s) {
+    DwArgs w = dw_args(P);
+    // H is the saved gate-weighted H, so the upstream gradient enters unscaled, straight from dY [T][d]
+    w.A = H; w.B0 = dY; w.C0 = dW2;
+    w.Mdim = f; w.Ndim = d; w.n_mt = (f + kTileM - 1) / kTileM; w.n_nt = (d + 255) / 256;
+    w.gathered_bytes = (uint32_t)((uint64_t)P.T * (uint64_t)d * 2u);
+    RowsArgs a = rows_args(P);
     a.A0 = dY; a.B0 = W2; a.E0 = dSdG; a.E1 = dSdU; a.C0 = dG; a.C1 = dU;
     a.K = d; a.Ncols = f; a.n_ntiles = (f + 255) / 256;
-    a.row_token = P.row_token; a.a_total_bytes = (uint32_t)((uint64_t)P.T * (uint64_t)d * 2u);
+    a.row_token = P.row_token; a.a_total_bytes = w.gathered_bytes;
     a.row_gate = row_gate;
     a.col_group = 3;   // column tiles walked in groups, row tiles fastest (as in the forward GEMMs): measured -2 % against the plain order
-    hipLaunchKernelGGL(k_bwd_gemm<kDh>, dim3(rows_grid(P, a.n_ntiles)), dim3(kThreads), 0, s, a);
+    const unsigned n_dw = dw_grid(P.E, w.n_mt, w.n_nt);
+    hipLaunchKernelGGL(k_bwd_pair<kDh>, dim3(n_dw + rows_grid(P, a.n_ntiles)), dim3(kThreads), 0, s, w, a, (int)n_dw);
     return hipGetLastError();
 }
 
-hipError_t launch_dxp(const PlanView& P, int d, int f, const bf16_t* dG, const bf16_t* dU, const bf16_t* W1,
-                      const bf16_t* W3, bf16_t* dXp, hipStream_t s) {
-    RowsArgs a = base_args(P);
+hipError_t launch_dw13_dxp(const PlanView& P, int d, int f, const bf16_t* x, const bf16_t* dG, const bf16_t* dU, const bf16_t* W1,
+                           const bf16_t* W3, bf16_t* dW1, bf16_t* dW3, bf16_t* dXp, hipStream_t s) {
+    DwArgs w = dw_args(P);
+    w.A = x; w.B0 = dG; w.B1 = dU; w.C0 = dW1; w.C1 = dW3;
+    w.Mdim = d; w.Ndim = f; w.n_mt = (d + kTileM - 1) / kTileM; w.n_nt = (f + 127) / 128;
+    w.gathered_bytes = (uint32_t)((uint64_t)P.T * (uint64_t)d * 2u);
+    RowsArgs a = rows_args(P);
     a.A0 = dG; a.A1 = dU; a.B0 = W1; a.B1 = W3; a.C0 = dXp;
     a.K = f; a.Ncols = d; a.n_ntiles = (d + 255) / 256;
     a.col_group = 4;   // measured best of 0 (plain order), 2, 3, 4: -2 %
-    hipLaunchKernelGGL(k_bwd_gemm<kDxp>, dim3(rows_grid(P, a.n_ntiles)), dim3(kThreads), 0, s, a);
+    const unsigned n_dw = dw_grid(P.E, w.n_mt, w.n_nt);
+    hipLaunchKernelGGL(k_bwd_pair<kDxp>, dim3(n_dw + rows_grid(P, a.n_ntiles)), dim3(kThreads), 0, s, w, a, (int)n_dw);
     return hipGetLastError();
 }
 

@@ -54,10 +54,10 @@ struct RowTile {
     int e, row0, rows, col0;
 };
 template <int BN>
-__device__ __forceinline__ bool pick_row_tile(const RowsArgs& a, RowTile& t) {
+__device__ __forceinline__ bool pick_row_tile(const RowsArgs& a, int block, RowTile& t) {
     const int n_real = a.plan.row_tiles() * a.n_ntiles;   // negative for a plan of other dimensions
-    if ((int)blockIdx.x >= n_real) return false;
-    const int L = xcd_remap(blockIdx.x, n_real);
+    if (block >= n_real) return false;
+    const int L = xcd_remap(block, n_real);
     const int mt = L / a.n_ntiles;
     int nt = L - mt * a.n_ntiles;
     // every tile of an expert carries the same record, so whichever of the expert's tiles this workgroup ends
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fwd_gemm(const RowsArgs a) {
 
     __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
     RowTile t;
-    if (!pick_row_tile<BN>(a, t)) return;
+    if (!pick_row_tile<BN>(a, (int)blockIdx.x, t)) return;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t wave_base = __builtin_amdgcn_readfirstlane((uint32_t)wave * 1024u);
@@ -335,14 +335,13 @@ __global__ __launch_bounds__(kThreads, 2) void k_fwd_gemm(const RowsArgs a) {
 enum BwdMode { kDh = 0, kDxp = 1 };
 
 template <int MODE>
-__global__ __launch_bounds__(kThreads, 2) void k_bwd_gemm(const RowsArgs a) {
+__device__ __forceinline__ void bwd_rows_tile(const RowsArgs& a, int block, char* smem) {
     constexpr int BN = 256;
     constexpr int NPH = (MODE == kDxp) ? 2 : 1;
     constexpr bool GATHER_A = MODE == kDh;  // dH reads the upstream gradient's rows straight from dY [T][d]
 
-    __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
     RowTile t;
-    if (!pick_row_tile<BN>(a, t)) return;
+    if (!pick_row_tile<BN>(a, block, t)) return;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t wave_base = __builtin_amdgcn_readfirstlane((uint32_t)wave * 1024u);
@@ -592,8 +591,8 @@ struct DwArgs {
 enum DwGather { kGatherNone = 0, kGatherA = 1, kGatherB = 2 };
 constexpr int kIdRingAt = 24 * 1024;  // between the A slots (3 x 8 KB) and the B slots (from 32 KB)
 
-template <int NB, int GATHER = kGatherNone>
-__global__ __launch_bounds__(kThreads, 2) void k_dw_gemm(const DwArgs a) {
+template <int NB, int GATHER>
+__device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) {
     static_assert(GATHER != kGatherB || NB == 1, "a gathered B operand is only provided for one B");
     constexpr int kStepCopies = GATHER == kGatherNone ? 6 : 7;
     constexpr int BN = (NB == 2) ? 128 : 256;
@@ -603,16 +602,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_gemm(const DwArgs a) {
     using BTile = McTile<BN>;
     static_assert(ATile::kPasses == 2 && NB * BTile::kPasses == 4, "six copies per thread and step");
 
-    __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t wave_base = __builtin_amdgcn_readfirstlane((uint32_t)wave * 1024u);
     const uint32_t smem_addr = __builtin_amdgcn_readfirstlane(lds_addr(smem));
-    // Tile -> workgroup mapping (see DwShare): XCD x = blockIdx % 8 walks its rectangles heaviest expert first.
+    // Tile -> workgroup mapping (see DwShare): XCD x = block % 8 walks its rectangles heaviest expert first.
     if (!a.plan.match()) return;
     int rank, mt, nt;
     {
-        const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
+        const int x = block & 7, q = block >> 3;
         int per_quad = 0;
 #pragma unroll
         for (int tq = 0; tq < 4; ++tq) per_quad += DwShare(x, tq, a.n_mt, a.n_nt).tiles();
@@ -762,6 +759,26 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_gemm(const DwArgs a) {
     for (int nb = 0; nb < NB; ++nb)
         write_tile<BN, FN>(smem, tid, (nb ? a.C1 : a.C0) + tile_at, (size_t)Ndim, rows_valid, cols_valid, col_of,
                            [&](int fm, int fn, int q) { return pack_acc(acc[nb][fm][fn], q); });
+}
+
+// ===================================================================================================
+// The backward pass in two launches.  dW2 and dH need only what the forward pass kept, dW1/dW3 and dXp only dG and
+// dU, so each pair shares a grid: the first n_dw workgroups (a multiple of 8, which keeps the XCD mapping) take the
+// weight gradient's tiles, heaviest expert first, the rest the row tiles.  Alone, each product of a small or skewed
+// problem leaves the chip idle behind its longest workgroup (a weight gradient's is as long as the hottest expert's rows).
+// Measured, plan + forward + backward, four backward launches -> two: T = 256, d = 128, f = 256, E = 8, k = 2: 65.8 -> 51.0
+// us; T = 3001, d = 1032, f = 680, E = 48, k = 3: 362 -> 343; T = 8192, d = 2048, f = 1408, E = 64, k = 6, where every
+// product fills the chip many times over: 2846 -> 2847.
+template <int MODE>
+__global__ __launch_bounds__(kThreads, 2) void k_bwd_pair(const DwArgs w, const RowsArgs r, int n_dw) {
+    __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
+    const int block = (int)blockIdx.x;
+    if (block < n_dw) {
+        if constexpr (MODE == kDh) dw_tile<1, kGatherB>(w, block, smem);
+        else dw_tile<2, kGatherA>(w, block, smem);
+    } else {
+        bwd_rows_tile<MODE>(r, block - n_dw, smem);
+    }
 }
 
 }  // namespace grouter
