@@ -10,7 +10,7 @@
 // is 32 MFMAs per wave.
 //
 // Loads.  Global->LDS copies are direct (buffer_load ... lds, 16 bytes per lane, no register staging) and
-// run two steps ahead.  The vector L1 works on whole 128-byte lines - a copy instruction that touches 16
+// run two steps ahead of the fragment reads, which run one step ahead of the MFMAs.  The vector L1 works on whole 128-byte lines - a copy instruction that touches 16
 // half lines costs twice one that touches 8 full lines - so every copy instruction is laid out to cover
 // full lines: K-contiguous operands are fetched 64 K-elements (128 B) per row at a time into "super tiles"
 // that serve two consecutive steps, M/N-contiguous operands 32 K-rows at a time.
@@ -202,50 +202,68 @@ struct IntC {
 };
 
 // ---------------------------------------------------------------------------------------------------
-// The step loop shared by every GEMM.  A step is 32 MFMAs per wave.  Per-step ("B") buffers rotate through
-// three LDS slots and are fetched two steps ahead, four copies per thread and step; when kSuperA is set the
-// A operand lives in two super-tile buffers that each serve two consecutive steps and are fetched (four
-// copies) during the even step two ahead, otherwise A is part of the per-step buffers (two more copies).
+// The step loop shared by every GEMM.  A step is 32 MFMAs per wave.  Per-step ("B") buffers rotate through three LDS
+// slots; when kSuperA is set the A operand lives in two super-tile buffers that each serve two consecutive steps (four
+// copies), otherwise A is part of the per-step buffers.
 //
-//   prepare_a()                           called once, after the first per-step copies are on their way
-//   issue_a(super_index, a_buffer)        kSuperA: enqueue the 4 copies of A super tile `super_index`
-//   issue_b(step, IntC<slot>)             enqueue the per-step copies of `step` into slot `slot`
-//   compute(IntC<slot>, IntC<half>, a_buffer, issue)   the 32 MFMAs of one step; `issue()` is called once
-//                                         part-way through to enqueue the copies that belong to this step
-//   compute_rt(slot, half, a_buffer, issue)   the same with run-time indices (loop tail)
+// Two levels of prefetch.  While step j multiplies out of registers, the fragments of step j + 1 travel from LDS to the
+// other register set, and the copies of step j + 3 go to the LDS slot of step j, which is free because its fragments
+// were read during step j - 1.  Without the register level a workgroup's step was a chain of barrier, LDS reads and MFMAs
+// that only the other workgroup of the CU could fill.  Measured (ratio to the time without it, same box): forward pass of
+// 8192 tokens, d = 2048, f = 1408, E = 64, k = 6 0.983; forward and backward 0.997; 16384 tokens, d = 4096, f = 1536,
+// E = 128, k = 8 0.986.  Enqueueing the copies before the first MFMAs instead of after eight: forward the same, backward
+// out of registers (1.8 times the time).
+//
+//   prepare_a()                              called once, after the first per-step copies are on their way
+//   issue_a(super_index, a_buffer, dead)     kSuperA: enqueue the 4 copies of A super tile `super_index`
+//   issue_b(step, IntC<slot>, dead)          enqueue the per-step copies of `step` into slot `slot`
+//   first()                                  request the fragments of step 0 (slot 0, A buffer 0) from LDS
+//   step(IntC<slot>, IntC<half>, a_buffer, arrive, issue)   one step, which
+//       - calls arrive() once the last fragments of this step are requested: from then on the next step's tiles
+//         (slot + 1, the other half) may be read and this step's slot is free in all waves;
+//       - calls issue() some time later to enqueue the copies of the step after the next two;
+//       - requests the next step's fragments and multiplies this step's.
+// dead = kOutOfRange for a step that does not exist: its copies fetch nothing (they write zeros nobody reads), so the
+// number of outstanding copies, which the waits are counted in, stays the same up to the last step.
 // Copies complete in issue order, so "wait until at most N are outstanding" is all the synchronisation a wave
 // needs before the step barrier: the N youngest are exactly the ones issued for later steps.
 struct NoPrepare {
     __device__ __forceinline__ void operator()() const {}
 };
-template <bool kSuperA, int kStepCopies, class IssueA, class IssueB, class Compute, class ComputeRt, class PrepareA = NoPrepare>
-__device__ __forceinline__ void step_pipeline(int n_steps, IssueA issue_a, IssueB issue_b, Compute compute,
-                                              ComputeRt compute_rt, PrepareA prepare_a = PrepareA{}) {
+template <bool kSuperA, int kStepCopies, class IssueA, class IssueB, class First, class Step, class PrepareA = NoPrepare>
+__device__ __forceinline__ void step_pipeline(int n_steps, IssueA issue_a, IssueB issue_b, First first, Step step,
+                                              PrepareA prepare_a = PrepareA{}) {
     if (n_steps <= 0) return;
     constexpr int kACopies = kSuperA ? 4 : 0;
-    // prologue: the per-step buffers of step 0 (their addresses are known first: a gathered A operand still
-    // waits for its row map and finishes its offsets in prepare_a), A super tile 0, then the per-step buffers
-    // of step 1
-    issue_b(0, IntC<0>{});
+    auto dead = [&](int at) { return at < n_steps ? 0u : kOutOfRange; };
+    // the per-step buffers of step 0 first: their addresses are known at once, a gathered A operand still waits for its
+    // row map and finishes its offsets in prepare_a
+    issue_b(0, IntC<0>{}, 0u);
     prepare_a();
-    if (kSuperA) issue_a(0, 0);
-    if (n_steps > 1) issue_b(1, IntC<1>{});
+    if (kSuperA) issue_a(0, 0, 0u);
+    issue_b(1, IntC<1>{}, dead(1));
+    if (kSuperA) issue_a(1, 1, dead(2));
+    issue_b(2, IntC<2>{}, dead(2));
+    wait_async_copies<2 * kStepCopies + kACopies>();
+    __syncthreads();
+    first();
     int j = 0;
     int abuf = 0;  // A super buffer of the current step: (j / 2) % 2
-    // Steady state, unrolled over the three slots and the two halves of a super tile.  Every copy named in
-    // the body exists as long as step j + 7 does.
-    for (; j + 8 <= n_steps; j += 6) {
+    while (true) {   // unrolled over the three slots and the two halves of a super tile
 #define GROUTER_STEP(u, SLOT, HALF)                                                                            \
     {                                                                                                          \
-        if (kSuperA && (HALF) == 1) wait_async_copies<kStepCopies + kACopies>();                               \
-        else wait_async_copies<kStepCopies>();                                                                 \
-        __syncthreads();                                                                                       \
         const int cur = j + (u);                                                                               \
-        compute(IntC<SLOT>{}, IntC<HALF>{}, abuf, [&]() {                                                      \
-            if (kSuperA && (HALF) == 0) issue_a(cur / 2 + 1, abuf ^ 1);                                        \
-            issue_b(cur + 2, IntC<((SLOT) + 2) % 3>{});                                                        \
-        });                                                                                                    \
+        step(IntC<SLOT>{}, IntC<HALF>{}, abuf,                                                                 \
+             [&]() {                                                                                           \
+                 wait_async_copies<kStepCopies + ((HALF) == 0 ? kACopies : 0)>();   /* step cur + 1 is here */ \
+                 __syncthreads();                                                                              \
+             },                                                                                                \
+             [&]() {                                                                                           \
+                 if (kSuperA && (HALF) == 1) issue_a((cur + 3) / 2, abuf, dead(cur + 3));                      \
+                 issue_b(cur + 3, IntC<SLOT>{}, dead(cur + 3));                                                \
+             });                                                                                               \
         if ((HALF) == 1) abuf ^= 1;                                                                            \
+        if (cur + 1 >= n_steps) break;                                                                         \
     }
         GROUTER_STEP(0, 0, 0)
         GROUTER_STEP(1, 1, 1)
@@ -254,31 +272,9 @@ __device__ __forceinline__ void step_pipeline(int n_steps, IssueA issue_a, Issue
         GROUTER_STEP(4, 1, 0)
         GROUTER_STEP(5, 2, 1)
 #undef GROUTER_STEP
+        j += 6;
     }
-    // Tail: the same schedule with run-time indices and existence checks; waits are exact.
-    int slot = 0;
-    for (; j < n_steps; ++j) {
-        const int half = j & 1;
-        // copies younger than the ones this step needs: those issued during step j-1
-        const bool prev_issued_b = j + 1 < n_steps;                          // per-step copies of step j+1
-        const bool prev_issued_a = kSuperA && half == 1 && (j + 1 < n_steps);  // super tile (j+1)/2, issued at even j-1
-        if (prev_issued_b && prev_issued_a) wait_async_copies<kStepCopies + kACopies>();
-        else if (prev_issued_b) wait_async_copies<kStepCopies>();
-        else wait_async_copies<0>();
-        __syncthreads();
-        const int cur = j;
-        compute_rt(slot, half, abuf, [&]() {
-            if (kSuperA && half == 0 && cur + 2 < n_steps) issue_a(cur / 2 + 1, abuf ^ 1);
-            if (cur + 2 < n_steps) {
-                const int s2 = slot >= 1 ? slot - 1 : slot + 2;
-                if (s2 == 0) issue_b(cur + 2, IntC<0>{});
-                else if (s2 == 1) issue_b(cur + 2, IntC<1>{});
-                else issue_b(cur + 2, IntC<2>{});
-            }
-        });
-        if (half == 1) abuf ^= 1;
-        slot = slot == 2 ? 0 : slot + 1;
-    }
+    wait_async_copies<0>();   // the copies of steps that do not exist: the epilogue takes over this LDS
 }
 
 // ---------------------------------------------------------------------------------------------------

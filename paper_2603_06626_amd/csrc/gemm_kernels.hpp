@@ -210,25 +210,26 @@ __global__ __launch_bounds__(kThreads, 2) void k_fwd_gemm(const RowsArgs a) {
         b_voff[p] = b_col < Ncols ? ((uint32_t)BMc::krow_of(tid, p) * (uint32_t)Ncols + b_col) * 2u : kOutOfRange;
     }
 
-    auto issue_a = [&](int super, int abuf) {
+    auto issue_a = [&](int super, int abuf, uint32_t dead) {
         const int k0 = super * 64;
+        const uint32_t soff = dead ? 0u : (uint32_t)k0 * 2u;
         const bool partial = k0 + 64 > K;  // the last super tile may stop mid-row
         const uint32_t dst = smem_addr + abuf * kSuperBytes + wave_base;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
             uint32_t v = a_voff[p];
             if (partial) v = (k0 + a_piece * 8 < K) ? v : kOutOfRange;
-            async_copy16(bufA, v, (uint32_t)k0 * 2u, dst + KcSuper::pass_offset(p));
+            async_copy16(bufA, v, soff, dst + KcSuper::pass_offset(p));
         }
     };
-    auto issue_b = [&](int step, auto slot_c) {
+    auto issue_b = [&](int step, auto slot_c, uint32_t dead) {
         const uint32_t dst = smem_addr + kBRegion + decltype(slot_c)::value * kBTileBytes + wave_base;
-        const uint32_t soff = (uint32_t)step * 32u * (uint32_t)Ncols * 2u;
+        const uint32_t soff = dead ? 0u : (uint32_t)step * 32u * (uint32_t)Ncols * 2u;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int p = 0; p < BMc::kPasses; ++p)
-                async_copy16(nb ? bufB1 : bufB0, b_voff[p], soff, dst + nb * kBHalf + BMc::pass_offset(p));
+                async_copy16(nb ? bufB1 : bufB0, b_voff[p] | dead, soff, dst + nb * kBHalf + BMc::pass_offset(p));
     };
 
     Acc32 acc[NB][4][FN];
@@ -239,31 +240,35 @@ __global__ __launch_bounds__(kThreads, 2) void k_fwd_gemm(const RowsArgs a) {
 #pragma unroll
             for (int fn = 0; fn < FN; ++fn) clear(acc[nb][fm][fn]);
 
-    // One step: all fragments are requested up front (LDS returns them in order, so the first MFMAs start once
-    // the first ones have landed), the step's copies are enqueued after the first eight MFMAs.
+    struct Frags {
+        Frag32 a[4], b[2];
+    };
     const uint32_t b_lane = BMc::lane_base(lane) ^ BMc::column_bits(wave * (BN / 4));   // this wave's columns
-    auto step_body = [&](const char* At, const char* Bt, int half, auto issue) {
-        Frag32 af[4], bf[2];
+    auto read = [&](Frags& fr, auto slot_c, auto half_c, int abuf) {
+        const char* const At = smem + abuf * kSuperBytes;
+        const char* const Bt = smem + kBRegion + decltype(slot_c)::value * kBTileBytes;
 #pragma unroll
-        for (int g = 0; g < 2; ++g) bf[g] = BMc::read_frag(Bt + (g / FN) * kBHalf, b_lane, (g % FN) * 32);
+        for (int g = 0; g < 2; ++g) fr.b[g] = BMc::read_frag(Bt + (g / FN) * kBHalf, b_lane, (g % FN) * 32);
 #pragma unroll
-        for (int fm = 0; fm < 4; ++fm) af[fm] = KcSuper::read_frag(At, lane, fm * 32, half);
+        for (int fm = 0; fm < 4; ++fm) fr.a[fm] = KcSuper::read_frag(At, lane, fm * 32, decltype(half_c)::value);
+    };
+    auto multiply = [&](const Frags& fr, auto issue) {
 #pragma unroll
         for (int g = 0; g < 2; ++g)
 #pragma unroll
             for (int fm = 0; fm < 4; ++fm) {
-                mfma32(bf[g], af[fm], acc[g / FN][fm][g % FN]);
+                mfma32(fr.b[g], fr.a[fm], acc[g / FN][fm][g % FN]);
                 if (g == 0 && fm == 1) issue();
             }
     };
-    auto compute = [&](auto slot_c, auto half_c, int abuf, auto issue) {
-        step_body(smem + abuf * kSuperBytes, smem + kBRegion + decltype(slot_c)::value * kBTileBytes,
-                  decltype(half_c)::value, issue);
+    Frags fr[2];
+    auto step = [&](auto slot_c, auto half_c, int abuf, auto arrive, auto issue) {
+        constexpr int slot = decltype(slot_c)::value, half = decltype(half_c)::value;
+        arrive();
+        read(fr[half ^ 1], IntC<(slot + 1) % 3>{}, IntC<half ^ 1>{}, half ? abuf ^ 1 : abuf);
+        multiply(fr[half], issue);
     };
-    auto compute_rt = [&](int slot, int half, int abuf, auto issue) {
-        step_body(smem + abuf * kSuperBytes, smem + kBRegion + slot * kBTileBytes, half, issue);
-    };
-    step_pipeline<true, 4>(n_steps, issue_a, issue_b, compute, compute_rt, prepare_a);
+    step_pipeline<true, 4>(n_steps, issue_a, issue_b, [&]() { read(fr[0], IntC<0>{}, IntC<0>{}, 0); }, step, prepare_a);
 
     // ---- epilogue: accumulators -> (fused elementwise) -> LDS -> whole-row 16-byte stores
     const int cols_valid = min(BN, Ncols - t.col0);
@@ -381,25 +386,26 @@ __device__ __forceinline__ void bwd_rows_tile(const RowsArgs& a, int block, char
             b_voff[h][p] = r < Ncols ? ((uint32_t)r * (uint32_t)K + piece * 8) * 2u : kOutOfRange;
         }
 
-    auto issue_super = [&](i32x4 buf, const uint32_t voff[4], int k0, uint32_t dst) {
+    auto issue_super = [&](i32x4 buf, const uint32_t voff[4], int k0, uint32_t dst, uint32_t dead) {
         const bool partial = k0 + 64 > K;
+        const uint32_t soff = dead ? 0u : (uint32_t)k0 * 2u;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            uint32_t v = voff[p];
+            uint32_t v = voff[p] | dead;
             if (partial) v = (k0 + piece * 8 < K) ? v : kOutOfRange;
-            async_copy16(buf, v, (uint32_t)k0 * 2u, dst + KcSuper::pass_offset(p));
+            async_copy16(buf, v, soff, dst + KcSuper::pass_offset(p));
         }
     };
-    auto issue_a = [&](int super, int abuf) {
+    auto issue_a = [&](int super, int abuf, uint32_t dead) {
         const int ph = (NPH == 2 && super >= n_super) ? 1 : 0;
-        issue_super(ph ? bufA1 : bufA0, a_voff, (super - ph * n_super) * 64, smem_addr + abuf * kSuperBytes + wave_base);
+        issue_super(ph ? bufA1 : bufA0, a_voff, (super - ph * n_super) * 64, smem_addr + abuf * kSuperBytes + wave_base, dead);
     };
-    auto issue_b = [&](int step, auto slot_c) {
+    auto issue_b = [&](int step, auto slot_c, uint32_t dead) {
         const int super = step >> 1;
         const int ph = (NPH == 2 && super >= n_super) ? 1 : 0;
         const uint32_t dst = smem_addr + kBRegion + decltype(slot_c)::value * kBTileBytes + wave_base;
-        if (step & 1) issue_super(ph ? bufB1 : bufB0, b_voff[1], (super - ph * n_super) * 64, dst);
-        else issue_super(ph ? bufB1 : bufB0, b_voff[0], (super - ph * n_super) * 64, dst);
+        if (step & 1) issue_super(ph ? bufB1 : bufB0, b_voff[1], (super - ph * n_super) * 64, dst, dead);
+        else issue_super(ph ? bufB1 : bufB0, b_voff[0], (super - ph * n_super) * 64, dst, dead);
     };
 
     Acc32 acc[4][2];  // [row block][column half]
@@ -409,35 +415,38 @@ __device__ __forceinline__ void bwd_rows_tile(const RowsArgs& a, int block, char
         for (int hf = 0; hf < 2; ++hf) clear(acc[fm][hf]);
 
     // One step: 2 K halves of the super tiles x (4 A fragments, 1 B fragment) = 32 MFMAs into the wave's column
-    // block `half`.  A tile without a right half skips half 1's fragment reads and MFMAs; its copies are still issued
-    // (they are masked and fetch nothing), so the pipeline's copy counts stay as they are.
-    auto step_body = [&](const char* At, const char* Bt, auto half_c, auto issue) {
-        constexpr int hf = decltype(half_c)::value;
-        if (hf == 1 && !right_half) {
-            issue();
-            return;
+    // block `half`.  The register sets alternate between the K halves: the second half's fragments are requested before the
+    // first half's MFMAs, the next step's first half before the second half's.  A tile without a right half skips
+    // half 1's fragment reads and MFMAs; its copies are still issued (they are masked and fetch nothing), so the
+    // pipeline's copy counts stay as they are.
+    struct Frags {
+        Frag32 a[4], b;
+    };
+    Frags fr[2];
+    auto read = [&](Frags& to, auto slot_c, int abuf, int kh) {
+        const char* const At = smem + abuf * kSuperBytes;
+        const char* const Bt = smem + kBRegion + decltype(slot_c)::value * kBTileBytes;
+        to.b = KcSuper::read_frag(Bt, lane, wave * 32, kh);
+#pragma unroll
+        for (int fm = 0; fm < 4; ++fm) to.a[fm] = KcSuper::read_frag(At, lane, fm * 32, kh);
+    };
+    auto step = [&](auto slot_c, auto half_c, int abuf, auto arrive, auto issue) {
+        constexpr int slot = decltype(slot_c)::value, hf = decltype(half_c)::value;
+        const bool here = hf == 0 || right_half, next = hf == 1 || right_half;
+        if (here) {
+            read(fr[1], slot_c, abuf, 1);
+#pragma unroll
+            for (int fm = 0; fm < 4; ++fm) mfma32(fr[0].b, fr[0].a[fm], acc[fm][hf]);
         }
+        arrive();
+        if (next) read(fr[0], IntC<(slot + 1) % 3>{}, hf ? abuf ^ 1 : abuf, 0);
+        issue();
+        if (here) {
 #pragma unroll
-        for (int kh = 0; kh < 2; ++kh) {  // one K half at a time keeps the fragment registers at 40
-            Frag32 af[4];
-            const Frag32 bf = KcSuper::read_frag(Bt, lane, wave * 32, kh);
-#pragma unroll
-            for (int fm = 0; fm < 4; ++fm) af[fm] = KcSuper::read_frag(At, lane, fm * 32, kh);
-#pragma unroll
-            for (int fm = 0; fm < 4; ++fm) {
-                mfma32(bf, af[fm], acc[fm][hf]);
-                if (kh == 0 && fm == 1) issue();
-            }
+            for (int fm = 0; fm < 4; ++fm) mfma32(fr[1].b, fr[1].a[fm], acc[fm][hf]);
         }
     };
-    auto compute = [&](auto slot_c, auto half_c, int abuf, auto issue) {
-        step_body(smem + abuf * kSuperBytes, smem + kBRegion + decltype(slot_c)::value * kBTileBytes, half_c, issue);
-    };
-    auto compute_rt = [&](int slot, int half, int abuf, auto issue) {
-        if (half) step_body(smem + abuf * kSuperBytes, smem + kBRegion + slot * kBTileBytes, IntC<1>{}, issue);
-        else step_body(smem + abuf * kSuperBytes, smem + kBRegion + slot * kBTileBytes, IntC<0>{}, issue);
-    };
-    step_pipeline<true, 4>(n_steps, issue_a, issue_b, compute, compute_rt, prepare_a);
+    step_pipeline<true, 4>(n_steps, issue_a, issue_b, [&]() { read(fr[0], IntC<0>{}, 0, 0); }, step, prepare_a);
 
     const int cols_valid = min(BN, Ncols - t.col0);
     const size_t tile_at = (size_t)t.row0 * Ncols + t.col0;
@@ -656,7 +665,8 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
     const i32x4 bufTok = make_buffer(GATHER != kGatherNone ? a.row_token + off : nullptr, (uint32_t)cnt * 4u);
     const uint32_t id_ring = smem_addr + kIdRingAt + __builtin_amdgcn_readfirstlane((uint32_t)wave * 128u);
     auto issue_ids = [&](int step) {  // rows 32*step .. 32*step+31 -> this wave's ring slot step % 8
-        if (lane < 32) async_copy4(bufTok, (uint32_t)lane * 4u, (uint32_t)step * 128u, id_ring + (uint32_t)(step & 7) * 512u);
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(id_ring + (uint32_t)(step & 7) * 512u);
+        if (lane < 32) async_copy4(bufTok, (uint32_t)lane * 4u, (uint32_t)step * 128u, dst);
     };
     auto token_of = [&](int step, int krow) {
         return *(const int32_t*)(smem + kIdRingAt + wave * 128 + (step & 7) * 512 + krow * 4);
@@ -667,28 +677,28 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
     // copies in the middle of the MFMA stream find them in registers.
     constexpr int kGatherPasses = GATHER == kGatherA ? 2 : (GATHER == kGatherB ? BTile::kPasses : 1);
     int32_t tok[kGatherPasses] = {};
-    int next_issue = 2;   // the step whose copies the next compute() issues (0 and 1 belong to the prologue)
+    int next_issue = 3;   // the step whose copies the next multiply() issues (0, 1 and 2 belong to the prologue)
     auto load_ids = [&](int step) {
 #pragma unroll
         for (int p = 0; p < kGatherPasses; ++p)
             tok[p] = token_of(step, GATHER == kGatherA ? ATile::krow_of(tid, p) : BTile::krow_of(tid, p));
     };
-    auto issue_a = [&](int, int) {};
-    auto issue_b = [&](int step, auto slot_c) {  // per-step copies: the A tile (2), the B tile(s) (4), and the ids
+    auto issue_a = [&](int, int, uint32_t) {};
+    auto issue_b = [&](int step, auto slot_c, uint32_t dead) {  // per-step copies: the A tile (2), the B tile(s) (4), and the ids
         constexpr int slot = decltype(slot_c)::value;
         if constexpr (GATHER != kGatherNone) {
-            if (step < 2) load_ids(step);   // prologue; later steps were read ahead by compute()
+            if (step < 3) load_ids(step);   // prologue; later steps were read ahead
         }
-        const uint32_t k0 = (uint32_t)step * 32u;
+        const uint32_t k0 = dead ? 0u : (uint32_t)step * 32u;
         const uint32_t a_dst = smem_addr + slot * kMcSmallBytes + wave_base;
         const uint32_t b_dst = smem_addr + kBRegion + slot * kBTileBytes + wave_base;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             if constexpr (GATHER == kGatherA) {
                 const uint32_t row = (uint32_t)tok[p] * (uint32_t)Mdim;
-                async_copy16(bufA, a_col[p] < Mdim ? (row + a_col[p]) * 2u : kOutOfRange, 0u, a_dst + ATile::pass_offset(p));
+                async_copy16(bufA, a_col[p] < Mdim ? ((row + a_col[p]) * 2u) | dead : kOutOfRange, 0u, a_dst + ATile::pass_offset(p));
             } else {
-                async_copy16(bufA, a_voff[p], k0 * (uint32_t)Mdim * 2u, a_dst + ATile::pass_offset(p));
+                async_copy16(bufA, a_voff[p] | dead, k0 * (uint32_t)Mdim * 2u, a_dst + ATile::pass_offset(p));
             }
         }
 #pragma unroll
@@ -697,9 +707,9 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
             for (int p = 0; p < BTile::kPasses; ++p) {
                 if constexpr (GATHER == kGatherB) {
                     const uint32_t row = (uint32_t)tok[p] * (uint32_t)Ndim;
-                    async_copy16(bufB0, b_col[p] < Ndim ? (row + b_col[p]) * 2u : kOutOfRange, 0u, b_dst + BTile::pass_offset(p));
+                    async_copy16(bufB0, b_col[p] < Ndim ? ((row + b_col[p]) * 2u) | dead : kOutOfRange, 0u, b_dst + BTile::pass_offset(p));
                 } else {
-                    async_copy16(nb ? bufB1 : bufB0, b_voff[p], k0 * (uint32_t)Ndim * 2u,
+                    async_copy16(nb ? bufB1 : bufB0, b_voff[p] | dead, k0 * (uint32_t)Ndim * 2u,
                                  b_dst + nb * kBHalf + BTile::pass_offset(p));
                 }
             }
@@ -721,35 +731,40 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
 
     const uint32_t a_lane = ATile::lane_base(lane);
     const uint32_t b_lane = BTile::lane_base(lane) ^ BTile::column_bits(wave * (BN / 4));   // this wave's columns
-    auto step_body = [&](const char* At, const char* Bt, auto issue) {
-        Frag32 af[4], bf[2];
+    struct Frags {
+        Frag32 a[4], b[2];
+    };
+    auto read = [&](Frags& fr, auto slot_c) {
+        const char* const At = smem + decltype(slot_c)::value * kMcSmallBytes;
+        const char* const Bt = smem + kBRegion + decltype(slot_c)::value * kBTileBytes;
         // the 12 fragment addresses are derived from these two in every step (an XOR each) instead of being
         // held in registers over the whole loop
         uint32_t ab = a_lane, bb = b_lane;
         asm volatile("" : "+v"(ab), "+v"(bb));
 #pragma unroll
-        for (int g = 0; g < 2; ++g) bf[g] = BTile::read_frag(Bt + (g / FN) * kBHalf, bb, (g % FN) * 32);
+        for (int g = 0; g < 2; ++g) fr.b[g] = BTile::read_frag(Bt + (g / FN) * kBHalf, bb, (g % FN) * 32);
 #pragma unroll
-        for (int fm = 0; fm < 4; ++fm) af[fm] = ATile::read_frag(At, ab, fm * 32);
+        for (int fm = 0; fm < 4; ++fm) fr.a[fm] = ATile::read_frag(At, ab, fm * 32);
+    };
+    auto multiply = [&](const Frags& fr, auto issue) {
+        if constexpr (GATHER != kGatherNone) load_ids(next_issue++);
 #pragma unroll
         for (int g = 0; g < 2; ++g)
 #pragma unroll
             for (int fm = 0; fm < 4; ++fm) {
-                mfma32(bf[g], af[fm], acc[g / FN][fm][g % FN]);
+                mfma32(fr.b[g], fr.a[fm], acc[g / FN][fm][g % FN]);
                 if (g == 0 && fm == 1) issue();
             }
     };
-    auto compute = [&](auto slot_c, auto, int, auto issue) {
-        constexpr int slot = decltype(slot_c)::value;
-        if constexpr (GATHER != kGatherNone) load_ids(next_issue++);
-        step_body(smem + slot * kMcSmallBytes, smem + kBRegion + slot * kBTileBytes, issue);
+    Frags fr[2];
+    auto step = [&](auto slot_c, auto half_c, int, auto arrive, auto issue) {
+        constexpr int slot = decltype(slot_c)::value, half = decltype(half_c)::value;
+        arrive();
+        read(fr[half ^ 1], IntC<(slot + 1) % 3>{});
+        multiply(fr[half], issue);
     };
-    auto compute_rt = [&](int slot, int, int, auto issue) {
-        if constexpr (GATHER != kGatherNone) load_ids(next_issue++);
-        step_body(smem + slot * kMcSmallBytes, smem + kBRegion + slot * kBTileBytes, issue);
-    };
-    step_pipeline<false, kStepCopies>((cnt + 31) / 32, issue_a, issue_b, compute, compute_rt);
-    if constexpr (GATHER != kGatherNone) wait_async_copies<0>();  // id copies of steps that do not exist
+    step_pipeline<false, kStepCopies>((cnt + 31) / 32, issue_a, issue_b, [&]() { read(fr[0], IntC<0>{}); }, step);
+    if constexpr (GATHER != kGatherNone) wait_async_copies<0>();  // id copies of an expert without rows
 
     const int rows_valid = min(kTileM, Mdim - m0);
     const int cols_valid = min(BN, Ndim - n0);
