@@ -16,18 +16,30 @@ static RowsArgs base_args(const PlanView& P) {
 
 static unsigned rows_grid(const PlanView& P, int n_ntiles) { return (unsigned)P.max_tiles_small * (unsigned)n_ntiles; }
 
-// Up to 16 tokens no expert holds more than 16 rows (unless a token names it twice): the streaming kernels then read the
-// weights once at full width.  From 17 on the 128-row tiles fill the chip and are as fast (T = 16: 350 us against 375 us
-// for two layers of d = 2048, f = 1408, E = 64, k = 6; 1090 us both for d = 4096, f = 1536, E = 128, k = 8), while here an
-// expert's second 16 rows would read its weights again (T = 200: 366 us against 211 us).
+// When the streaming kernels take over.  Up to 16 tokens no expert holds more than 16 rows (unless a token names it twice)
+// and they read the weights once at full width.  From 17 to 64 tokens they still read them once, with 2 or 4 row
+// blocks, which pays where the 128-row tiles are too few to occupy the chip: d = 568, f = 1088, E = 8, k = 2 (72 and 24
+// tiles), T = 20: 31.5 -> 19.9 us a layer, T = 64: 32.1 -> 24.4; d = f = 1024, E = 16, k = 2 (128 and 64 tiles): 47.2 -> 29.0
+// and 47.6 -> 41.1.  With more tiles they lose (d = 2048, f = 1408, E = 64, k = 6, T = 64: 195 -> 219 us), and so does a
+// second pass over the weights (the first shape at T = 100: 33 -> 35 us).
+// Stages: with K of at most one block per wave a second stage would only load zeros (d = 256, f = 576, E = 128, k = 7,
+// T = 16: 28.5 -> 25.1 us); otherwise two stages are up to 1 % faster.
+// By expert: with rows of 592 bytes (d = 704, f = 296, E = 64, k = 5, T = 10), where neighbouring column blocks share lines,
+// three layers take 121 us with an expert's blocks spread over the XCDs and 87 us on one.
+constexpr int64_t kStreamTiles = 128;
 template <int MODE>
 static bool launch_stream(const PlanView& P, RowsArgs a, hipStream_t s) {
-    constexpr int kCpl = 4, kWaves = 8, kStages = 2;
-    if (P.T > kStreamRows) return false;
-    a.n_ntiles = (a.Ncols + 16 * kCpl - 1) / (16 * kCpl);
+    constexpr int kCpl = 4, kWaves = 8;
     const int64_t tiles = P.max_tiles_small < P.N ? P.max_tiles_small : P.N;   // no tile is empty
-    const dim3 grid((unsigned)(tiles * ((a.n_ntiles + 7) / 8 * 8)));
-    hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, kStages>), grid, dim3(kWaves * 64), 0, s, a);
+    const bool few_rows = P.T <= kStreamRows;
+    if (!few_rows && (P.T > 4 * kStreamRows || tiles * a.n_ntiles > kStreamTiles)) return false;
+    a.n_ntiles = (a.Ncols + 16 * kCpl - 1) / (16 * kCpl);
+    a.col_group = a.Ncols % 64 != 0 && tiles >= 32;   // 64 columns are a line; with fewer experts some XCDs would idle
+    const dim3 grid((unsigned)(a.col_group ? (tiles + 7) / 8 * 8 * a.n_ntiles : tiles * ((a.n_ntiles + 7) / 8 * 8))), block(kWaves * 64);
+    if (few_rows && a.K <= 32 * kWaves) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 1, 1>), grid, block, 0, s, a);
+    else if (few_rows) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 2, 1>), grid, block, 0, s, a);
+    else if (P.T <= 2 * kStreamRows) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 2, 2>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, MODE == kStreamDown ? 2 : 1, 4>), grid, block, 0, s, a);
     return true;
 }
 

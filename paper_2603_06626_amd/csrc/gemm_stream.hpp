@@ -1,4 +1,4 @@
-// Forward GEMMs for at most 16 tokens (decoding).
+// Forward GEMMs for few tokens (decoding).
 //
 // With so few rows per expert the layer reads every weight of the experts in use once and does next to no arithmetic per
 // byte: HBM bandwidth is the bound, and what matters is that all CUs have loads in flight from the first microsecond on.
@@ -10,24 +10,25 @@
 // loop.  A lane loads CPL columns of 8 K-rows and turns them into MFMA operands with one v_perm per two elements: the K-rows
 // 8 (l / 16) .. + 7 of column CPL (l % 16) + j are the 8 consecutive K values per lane that the 16x16x32 operand of block
 // j wants, if block j is taken to be the columns CPL c + j.  A lane of the accumulators then holds 4 CPL consecutive columns
-// of one row.  The activations' operand (16 rows, 8 consecutive K per lane) is loaded directly, too.  At the end the waves'
+// of one row.  The activations' operand (RB blocks of 16 rows, 8 consecutive K per lane) is loaded directly, too.  At the end the waves'
 // partial sums meet in LDS and are added in wave order, so results do not depend on timing.
 //
 // Measured (d = 2048, f = 1408, E = 64, k = 6, one token, kernel time): gate/up 39.7 -> 20 us, down 26.6 -> 10.5 us, that
 // is 3.4 TB/s; T = 4: a layer 86 -> 84 us; T = 16: 188 -> 175 us (5 TB/s), d = 4096 and E = 128 at T = 16 unchanged (5.7
 // TB/s, what this memory gives).  4 columns per lane (whole 128-byte lines per K-row) beat 2 (27 us) and 8 (30 us, too
-// few workgroups); 8 waves beat 4 and 16; 1 to 8 stages are alike.
+// few workgroups); 8 waves beat 4 and 16; 1 to 8 stages are within 1 % once every wave has a block for each.
 #pragma once
 #include "gemm_kernels.hpp"
 
 namespace grouter {
 
-constexpr int kStreamRows = 16;
+constexpr int kStreamRows = 16;   // rows of one MFMA
 
 enum StreamMode { kStreamGateUp = 0, kStreamGateUpOnly = 1, kStreamDown = 2 };
 
-template <int MODE, int CPL, int W, int STAGES>
-__global__ __launch_bounds__(W * 64, 2) void k_stream_gemm(const RowsArgs a) {
+// RB: row blocks of 16 that share one pass over the weights
+template <int MODE, int CPL, int W, int STAGES, int RB>
+__global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stream_gemm(const RowsArgs a) {
     constexpr bool GATEUP = MODE != kStreamDown;
     constexpr int NB = GATEUP ? 2 : 1;
     constexpr int kCols = 16 * CPL;
@@ -39,9 +40,20 @@ __global__ __launch_bounds__(W * 64, 2) void k_stream_gemm(const RowsArgs a) {
 
     // Workgroups of one expert: the 8 XCDs take one contiguous run of column blocks each, so a line that two blocks share is
     // fetched by one L2.  The tile record does not depend on the header, so the two loads overlap.
-    const int per_xcd = (a.n_ntiles + 7) >> 3;
-    const int mt = (int)blockIdx.x / (per_xcd * 8), b = (int)blockIdx.x - mt * per_xcd * 8;
-    const int cb = (b & 7) * per_xcd + (b >> 3);
+    // Where rows do not begin on a line, every block shares its first and last line with its neighbours: given enough
+    // experts, one XCD then takes all blocks of an expert (a.col_group).
+    int mt, cb;
+    if (a.col_group) {
+        const int q = (int)blockIdx.x >> 3;
+        mt = q / a.n_ntiles * 8 + ((int)blockIdx.x & 7);
+        cb = q % a.n_ntiles;
+        if (mt >= a.max_tiles) return;
+    } else {
+        const int per_xcd = (a.n_ntiles + 7) >> 3;
+        mt = (int)blockIdx.x / (per_xcd * 8);
+        const int b = (int)blockIdx.x - mt * per_xcd * 8;
+        cb = (b & 7) * per_xcd + (b >> 3);
+    }
     typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
     const i32x8 rec = *(const i32x8*)(a.tiles + 8 * (size_t)mt);
     const int n_tiles = a.plan.row_tiles();   // negative for a plan of other dimensions
@@ -66,12 +78,12 @@ __global__ __launch_bounds__(W * 64, 2) void k_stream_gemm(const RowsArgs a) {
     const int b_col = col0 + l16 * CPL;
     const uint32_t b_voff = b_col < Ncols ? (uint32_t)(8 * g16) * row_b + b_col * 2u : kOutOfRange;
 
-    // an expert of more than 16 rows (only possible when a token names it more than once) takes several turns
-    for (int r0 = 0; r0 < tile_rows; r0 += kStreamRows) {
-        const int rows = min(kStreamRows, tile_rows - r0);
+    // an expert of more than 16 RB rows (only possible when a token names it more than once) takes several turns
+    for (int r0 = 0; r0 < tile_rows; r0 += kStreamRows * RB) {
+        const int rows = min(kStreamRows * RB, tile_rows - r0);
         struct Block {
             uint32_t b[NB][8][DW];
-            u32x4 a;
+            u32x4 a[RB];
         };
         Block st[STAGES];
         auto load_b = [&](int kb, Block& s) {
@@ -93,18 +105,26 @@ __global__ __launch_bounds__(W * 64, 2) void k_stream_gemm(const RowsArgs a) {
         };
 #pragma unroll
         for (int s = 0; s < STAGES; ++s) load_b(wave + s * W, st[s]);
-        const int my_row = tile_row0 + r0 + min(l16, rows - 1);
-        const uint32_t a_voff = ((GATEUP ? (uint32_t)a.row_token[my_row] : (uint32_t)my_row) * (uint32_t)K + 8u * g16) * 2u;
+        uint32_t a_voff[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const int my_row = tile_row0 + r0 + min(rb * kStreamRows + l16, rows - 1);
+            a_voff[rb] = ((GATEUP ? (uint32_t)a.row_token[my_row] : (uint32_t)my_row) * (uint32_t)K + 8u * g16) * 2u;
+        }
         auto load_a = [&](int kb, Block& s) {
-            s.a = __builtin_amdgcn_raw_buffer_load_b128(bufA, (int)(kb * 32 + 8 * g16 < K ? a_voff : kOutOfRange), kb * 64, 0);
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+                s.a[rb] = __builtin_amdgcn_raw_buffer_load_b128(bufA, (int)(kb * 32 + 8 * g16 < K ? a_voff[rb] : kOutOfRange), kb * 64, 0);
         };
 #pragma unroll
         for (int s = 0; s < STAGES; ++s) load_a(wave + s * W, st[s]);
-        f32x4 acc[NB][CPL];
+        f32x4 acc[RB][NB][CPL];
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int j = 0; j < CPL; ++j) acc[nb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int j = 0; j < CPL; ++j) acc[rb][nb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         auto multiply = [&](const Block& s) {
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
@@ -114,7 +134,9 @@ __global__ __launch_bounds__(W * 64, 2) void k_stream_gemm(const RowsArgs a) {
 #pragma unroll
                     for (int p = 0; p < 4; ++p)
                         w[p] = __builtin_amdgcn_perm(s.b[nb][2 * p + 1][j >> 1], s.b[nb][2 * p][j >> 1], (j & 1) ? 0x07060302u : 0x05040100u);
-                    acc[nb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, s.a), acc[nb][j], 0, 0, 0);
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb)
+                        acc[rb][nb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, s.a[rb]), acc[rb][nb][j], 0, 0, 0);
                 }
         };
         int kb = wave;
@@ -130,49 +152,53 @@ __global__ __launch_bounds__(W * 64, 2) void k_stream_gemm(const RowsArgs a) {
         for (int s = 0; s < STAGES; ++s) multiply(st[s]);   // blocks past the end are all zero
 
         // ---- the waves' partial sums meet in LDS
-        if (r0) __syncthreads();
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+        for (int rb = 0; rb < RB; ++rb) {
+            if (rb * kStreamRows >= rows) break;
+            if (r0 + rb) __syncthreads();
 #pragma unroll
-            for (int h = 0; h < CPL; ++h) {   // columns 4 h .. + 3 of this lane's 4 CPL
-                f32x4 v;
+            for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) v[c] = acc[nb][(4 * h + c) % CPL][(4 * h + c) / CPL];
-                *(f32x4*)(smem + wave * kWaveLds + l16 * kPitch + (nb * kCols + g16 * 4 * CPL + h * 4) * 4) = v;
-            }
-        __syncthreads();
-        constexpr int kQuads = kStreamRows * kCols / 4;          // 4 columns of one row each
-        constexpr int kPerRow = kCols / 4;
-        static_assert(kQuads <= W * 64, "one quad per thread");
-        const int r = tid / kPerRow, col = col0 + (tid % kPerRow) * 4;
-        if (r < rows && col < Ncols) {
-            f32x4 sum[NB];
+                for (int h = 0; h < CPL; ++h) {   // columns 4 h .. + 3 of this lane's 4 CPL
+                    f32x4 v;
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                sum[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int w = 0; w < W; ++w) sum[nb] += *(const f32x4*)(smem + w * kWaveLds + r * kPitch + (nb * kCols + (tid % kPerRow) * 4) * 4);
-            }
-            const int row = tile_row0 + r0 + r;
-            const size_t at = (size_t)row * Ncols + col;
-            if constexpr (GATEUP) {
-                const float gate = a.row_gate[row];
-                float P[4], Q[4], H[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const float g = sum[0][c], u = sum[NB - 1][c];
-                    const float s = sigmoid_fast(g);
-                    Q[c] = g * s;
-                    P[c] = u * (s + Q[c] * (1.f - s));
-                    H[c] = gate * (Q[c] * u);
+                    for (int c = 0; c < 4; ++c) v[c] = acc[rb][nb][(4 * h + c) % CPL][(4 * h + c) / CPL];
+                    *(f32x4*)(smem + wave * kWaveLds + l16 * kPitch + (nb * kCols + g16 * 4 * CPL + h * 4) * 4) = v;
                 }
-                if constexpr (MODE == kStreamGateUp) {
-                    *(u32x2*)(a.C0 + at) = u32x2{pack_bf16_rne(P[0], P[1]), pack_bf16_rne(P[2], P[3])};
-                    *(u32x2*)(a.C1 + at) = u32x2{pack_bf16_rne(Q[0], Q[1]), pack_bf16_rne(Q[2], Q[3])};
+            __syncthreads();
+            constexpr int kQuads = kStreamRows * kCols / 4;          // 4 columns of one row each
+            constexpr int kPerRow = kCols / 4;
+            static_assert(kQuads <= W * 64, "one quad per thread");
+            const int r = tid / kPerRow, col = col0 + (tid % kPerRow) * 4;
+            if (rb * kStreamRows + r < rows && col < Ncols) {
+                f32x4 sum[NB];
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    sum[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int w = 0; w < W; ++w) sum[nb] += *(const f32x4*)(smem + w * kWaveLds + r * kPitch + (nb * kCols + (tid % kPerRow) * 4) * 4);
                 }
-                *(u32x2*)(a.C2 + at) = u32x2{pack_bf16_rne(H[0], H[1]), pack_bf16_rne(H[2], H[3])};
-            } else {
-                *(u32x2*)(a.C0 + at) = u32x2{pack_bf16_rne(sum[0][0], sum[0][1]), pack_bf16_rne(sum[0][2], sum[0][3])};
+                const int row = tile_row0 + r0 + rb * kStreamRows + r;
+                const size_t at = (size_t)row * Ncols + col;
+                if constexpr (GATEUP) {
+                    const float gate = a.row_gate[row];
+                    float P[4], Q[4], H[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float g = sum[0][c], u = sum[NB - 1][c];
+                        const float s = sigmoid_fast(g);
+                        Q[c] = g * s;
+                        P[c] = u * (s + Q[c] * (1.f - s));
+                        H[c] = gate * (Q[c] * u);
+                    }
+                    if constexpr (MODE == kStreamGateUp) {
+                        *(u32x2*)(a.C0 + at) = u32x2{pack_bf16_rne(P[0], P[1]), pack_bf16_rne(P[2], P[3])};
+                        *(u32x2*)(a.C1 + at) = u32x2{pack_bf16_rne(Q[0], Q[1]), pack_bf16_rne(Q[2], Q[3])};
+                    }
+                    *(u32x2*)(a.C2 + at) = u32x2{pack_bf16_rne(H[0], H[1]), pack_bf16_rne(H[2], H[3])};
+                } else {
+                    *(u32x2*)(a.C0 + at) = u32x2{pack_bf16_rne(sum[0][0], sum[0][1]), pack_bf16_rne(sum[0][2], sum[0][3])};
+                }
             }
         }
     }

@@ -1,4 +1,4 @@
-"""Forward pass at and around the sizes where the kernels for few tokens take over (at most 16 tokens), through the C ABI,
+"""Forward pass at and around the sizes where the kernels for few tokens take over (at most 16 tokens, on few experts at most 64), through the C ABI,
 against the CPU oracle.  Bar as for the other shapes: max|gpu - oracle| <= 1e-2 * max|oracle| (bf16 storage of H, O and
 y: a few 2^-9 each, fp32 accumulation)."""
 import numpy as np
@@ -22,7 +22,15 @@ TOL = 1e-2
     (15, 264, 520, 9, 2, False),    # one K-block more than the waves share evenly
     (16, 544, 192, 4, 4, False),    # 16 rows in every expert
     (16, 1056, 72, 6, 3, True),     # a token names its expert three times: 48 rows in one expert
-    (17, 544, 192, 4, 4, False),    # first size of the tiled kernels
+    (17, 544, 192, 4, 4, False),    # first size with two row blocks: 17 rows in every expert
+    (32, 72, 200, 4, 4, False),     # last size with two, full
+    (33, 264, 136, 3, 3, False),    # first with four
+    (64, 520, 264, 2, 2, False),    # last with four, full
+    (64, 264, 72, 6, 3, True),      # a token names its expert three times: 192 rows in one expert, two tiles
+    (65, 264, 136, 3, 3, False),    # first size of the tiled kernels
+    (12, 72, 136, 40, 3, False),    # rows that begin inside a line and 32 tiles or more: one XCD per expert
+    (16, 200, 264, 64, 4, False),   # the same with five column blocks
+    (20, 1032, 1032, 64, 4, False), # more than 16 tokens on many experts: tiled
 ])
 def test_few_tokens_match_the_oracle(T, d, f, E, k, repeat):
     if not torch.cuda.is_available():
