@@ -783,7 +783,8 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
 // problem leaves the chip idle behind its longest workgroup (a weight gradient's is as long as the hottest expert's rows).
 // Measured, plan + forward + backward, four backward launches -> two: T = 256, d = 128, f = 256, E = 8, k = 2: 65.8 -> 51.0
 // us; T = 3001, d = 1032, f = 680, E = 48, k = 3: 362 -> 343; T = 8192, d = 2048, f = 1408, E = 64, k = 6, where every
-// product fills the chip many times over: 2846 -> 2847.
+// product fills the chip many times over: 2846 -> 2847.  Reductions of a few steps (T = 6846, E = 128, k = 2) are 2 % slower
+// than they were with launches of their own and a step loop without masked copies.
 template <int MODE>
 __global__ __launch_bounds__(kThreads, 2) void k_bwd_pair(const DwArgs w, const RowsArgs r, int n_dw) {
     __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
