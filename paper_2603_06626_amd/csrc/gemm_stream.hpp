@@ -19,10 +19,9 @@
 // few workgroups); 8 waves beat 4 and 16; 1 to 8 stages are within 1 % once every wave has a block for each.
 #pragma once
 #include "gemm_kernels.hpp"
+#include "stream_map.hpp"
 
 namespace grouter {
-
-constexpr int kStreamRows = 16;   // rows of one MFMA
 
 enum StreamMode { kStreamGateUp = 0, kStreamGateUpOnly = 1, kStreamDown = 2 };
 
@@ -33,10 +32,9 @@ __global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stre
     constexpr int NB = GATEUP ? 2 : 1;
     constexpr int kCols = 16 * CPL;
     constexpr int DW = CPL / 2;                                // dwords a lane loads per K-row
-    constexpr int kPitch = NB * kCols * 4 + 16;                // one row of partial sums in LDS
-    constexpr int kWaveLds = kStreamRows * kPitch;
+    using Sums = StreamSums<NB, kCols>;
     static_assert(CPL == 2 || CPL == 4, "columns per lane");
-    __shared__ __attribute__((aligned(16))) char smem[W * kWaveLds];
+    __shared__ __attribute__((aligned(16))) char smem[W * Sums::kWaveBytes];
 
     // Workgroups of one expert: the 8 XCDs take one contiguous run of column blocks each, so a line that two blocks share is
     // fetched by one L2.  The tile record does not depend on the header, so the two loads overlap.
@@ -163,23 +161,21 @@ __global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stre
                     f32x4 v;
 #pragma unroll
                     for (int c = 0; c < 4; ++c) v[c] = acc[rb][nb][(4 * h + c) % CPL][(4 * h + c) / CPL];
-                    *(f32x4*)(smem + wave * kWaveLds + l16 * kPitch + (nb * kCols + g16 * 4 * CPL + h * 4) * 4) = v;
+                    *(f32x4*)(smem + wave * Sums::kWaveBytes + l16 * Sums::kPitch + (nb * kCols + g16 * 4 * CPL + h * 4) * 4) = v;
                 }
             __syncthreads();
-            constexpr int kQuads = kStreamRows * kCols / 4;          // 4 columns of one row each
-            constexpr int kPerRow = kCols / 4;
-            static_assert(kQuads <= W * 64, "one quad per thread");
-            const int r = tid / kPerRow, col = col0 + (tid % kPerRow) * 4;
-            if (rb * kStreamRows + r < rows && col < Ncols) {
+            static_assert(Sums::kThreads <= W * 64, "one quad per thread");
+            const Sums mine(tid);
+            if (mine.finishes(rows - rb * kStreamRows, Ncols - col0)) {
                 f32x4 sum[NB];
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
                     sum[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int w = 0; w < W; ++w) sum[nb] += *(const f32x4*)(smem + w * kWaveLds + r * kPitch + (nb * kCols + (tid % kPerRow) * 4) * 4);
+                    for (int w = 0; w < W; ++w) sum[nb] += *(const f32x4*)(smem + mine.at(w, nb));
                 }
-                const int row = tile_row0 + r0 + rb * kStreamRows + r;
-                const size_t at = (size_t)row * Ncols + col;
+                const int row = tile_row0 + r0 + rb * kStreamRows + mine.row;
+                const size_t at = (size_t)row * Ncols + col0 + mine.col;
                 if constexpr (GATEUP) {
                     const float gate = a.row_gate[row];
                     float P[4], Q[4], H[4];
