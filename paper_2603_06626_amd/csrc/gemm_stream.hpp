@@ -36,28 +36,14 @@ __global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stre
     static_assert(CPL == 2 || CPL == 4, "columns per lane");
     __shared__ __attribute__((aligned(16))) char smem[W * Sums::kWaveBytes];
 
-    // Workgroups of one expert: the 8 XCDs take one contiguous run of column blocks each, so a line that two blocks share is
-    // fetched by one L2.  The tile record does not depend on the header, so the two loads overlap.
-    // Where rows do not begin on a line, every block shares its first and last line with its neighbours: given enough
-    // experts, one XCD then takes all blocks of an expert (a.col_group).
-    int mt, cb;
-    if (a.col_group) {
-        const int q = (int)blockIdx.x >> 3;
-        mt = q / a.n_ntiles * 8 + ((int)blockIdx.x & 7);
-        cb = q % a.n_ntiles;
-        if (mt >= a.max_tiles) return;
-    } else {
-        const int per_xcd = (a.n_ntiles + 7) >> 3;
-        mt = (int)blockIdx.x / (per_xcd * 8);
-        const int b = (int)blockIdx.x - mt * per_xcd * 8;
-        cb = (b & 7) * per_xcd + (b >> 3);
-    }
     typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
-    const i32x8 rec = *(const i32x8*)(a.tiles + 8 * (size_t)mt);
-    const int n_tiles = a.plan.row_tiles();   // negative for a plan of other dimensions
-    if (mt >= n_tiles || cb >= a.n_ntiles) return;
-    const int col0 = cb * kCols;
-    const int e = rec[0], m_in = mt - rec[3];
+    i32x8 rec;
+    StreamTile tile;
+    if (!tile.pick((int)blockIdx.x, a.n_ntiles, a.col_group != 0, [&]() { return a.plan.row_tiles(); },
+                   [&](int mt) { rec = *(const i32x8*)(a.tiles + 8 * (size_t)mt); }))
+        return;
+    const int col0 = tile.cb * kCols;
+    const int e = rec[0], m_in = tile.mt - rec[3];
     const int tile_row0 = rec[1] + m_in * kTileM;
     const int tile_rows = min(kTileM, rec[2] - m_in * kTileM);
 

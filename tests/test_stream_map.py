@@ -53,3 +53,41 @@ def run_host(tmp_path, source):
 def test_partial_sums_stay_in_their_area_and_every_output_is_stored_once(tmp_path):
     r = run_host(tmp_path, SUMS)
     assert r.returncode == 0, r.stdout
+
+
+TILES = r"""
+#include <cstdio>
+#include <vector>
+#include "stream_map.hpp"
+using namespace grouter;
+
+int main() {
+    for (int bound = 1; bound <= 40; ++bound)              // row tiles the launch allows for
+        for (int ncb = 1; ncb <= 20; ++ncb)
+            for (int by_expert = 0; by_expert < 2; ++by_expert) {
+                const int grid = by_expert ? (bound + 7) / 8 * 8 * ncb : bound * ((ncb + 7) / 8 * 8);
+                for (int n = -1; n <= bound; ++n) {        // row tiles the plan header names; -1: a plan of other dimensions
+                    std::vector<int> taken(bound * ncb, 0);
+                    for (int block = 0; block < grid; ++block) {
+                        bool vouched = false;
+                        int read = -1;
+                        StreamTile t;
+                        const bool ok = t.pick(block, ncb, by_expert, [&]() { vouched = true; return n; },
+                                               [&](int mt) { if (!vouched || mt < 0 || mt >= n) read = -2; else if (read == -1) read = mt; });
+                        if (read == -2 || (n < 0 && ok) || (ok && read != t.mt))
+                            return std::printf("bound %d, %d column blocks, %d tiles: workgroup %d reads a record nobody vouched for\n", bound, ncb, n, block), 1;
+                        if (ok) ++taken[t.mt * ncb + t.cb];
+                    }
+                    for (int i = 0; i < bound * ncb; ++i)
+                        if (taken[i] != (i < n * ncb ? 1 : 0))
+                            return std::printf("bound %d, %d column blocks, %d tiles: pair %d taken %d times\n", bound, ncb, n, i, taken[i]), 1;
+                }
+            }
+    return 0;
+}
+"""
+
+
+def test_tile_records_are_read_after_the_header_and_every_tile_is_taken_once(tmp_path):
+    r = run_host(tmp_path, TILES)
+    assert r.returncode == 0, r.stdout
