@@ -46,8 +46,10 @@ def phase_work(T, d, f, E, k):
     return {
         "gateup": ("mfma", 4.0 * N * d * f),
         "down": ("mfma", 2.0 * N * d * f),
-        "dW2+dH": ("mfma", 4.0 * N * d * f),
-        "dW13+dXp": ("mfma", 8.0 * N * d * f),
+        "dH": ("mfma", 2.0 * N * d * f),
+        "dW2": ("mfma", 2.0 * N * d * f),
+        "dW13": ("mfma", 4.0 * N * d * f),
+        "dXp": ("mfma", 4.0 * N * d * f),
         "permute": ("hbm", 2.0 * T * d + 4.0 * N + 2.0 * N * d),
         "dO": ("hbm", 2.0 * T * d + 10.0 * N + 2.0 * N * d),
         "combine": ("hbm", 2.0 * N * d + 4.0 * N + 2.0 * T * d),

@@ -225,6 +225,8 @@ int grouter_fold_weights(const float* W_s, const int32_t* group_of, int d, int E
  * launch counts per phase; phases are indexed by the GROUTER_PH_* constants.  Host-side state shared by
  * all threads (guarded by a mutex).  Launches made while their stream is being captured into a graph are
  * not timed.  At most 4096 launches are kept between reads.
+ * Backward launches dW2 together with dH and dW1/dW3 together with dXp; a timed call launches the four one after the
+ * other, so that each has a phase of its own (same results bit for bit; together they may take longer than the two pairs).
  */
 enum {
     GROUTER_PH_PLAN = 0,      /* histogram + scan + scatter */
@@ -233,10 +235,10 @@ enum {
     GROUTER_PH_DOWN = 3,      /* O = H W2 */
     GROUTER_PH_COMBINE = 4,   /* y */
     GROUTER_PH_DO = 5,        /* grouter_permute with gate weights */
-    GROUTER_PH_DW2_DH = 6,    /* one launch: dW2, and dH GEMM + dSwiGLU */
-    GROUTER_PH_DW2 = 7,       /* unused: part of GROUTER_PH_DW2_DH */
-    GROUTER_PH_DW13 = 8,      /* unused: part of GROUTER_PH_DW13_DXP */
-    GROUTER_PH_DW13_DXP = 9,  /* one launch: dW1, dW3, and dXp */
+    GROUTER_PH_DH = 6,        /* dH GEMM + dSwiGLU */
+    GROUTER_PH_DW2 = 7,
+    GROUTER_PH_DW13 = 8,
+    GROUTER_PH_DXP = 9,
     GROUTER_PH_DXREDUCE = 10,
     GROUTER_PH_AFFINITY = 11,  /* affinity counts, entropy, loads, MaxVio */
     GROUTER_PH_PLACEMENT = 12,

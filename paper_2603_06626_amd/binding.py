@@ -15,7 +15,7 @@ _lib = None
 
 OK, ERR_INVALID_ARG, ERR_WORKSPACE_TOO_SMALL, ERR_INDEX_OUT_OF_RANGE, ERR_HIP = 0, -1, -2, -3, -4
 IDX_INT32, IDX_UINT8 = 0, 1
-PHASES = ("plan", "permute", "gateup", "down", "combine", "dO", "dW2+dH", "dW2", "dW13", "dW13+dXp", "dX_reduce", "affinity",
+PHASES = ("plan", "permute", "gateup", "down", "combine", "dO", "dH", "dW2", "dW13", "dXp", "dX_reduce", "affinity",
           "placement", "coactivation", "fold", "sample_stats")
 
 EXPORTS = (

@@ -394,15 +394,38 @@ int grouter_moe_bwd(const void* plan_ws, int64_t T, int k, int E, int d, int f, 
     bf16_t* dU = (bf16_t*)(w + B.du);
     bf16_t* dXp = (bf16_t*)(w + B.dxp);
     hipError_t e;
-    PhaseTimer t_dh(GROUTER_PH_DW2_DH, s);
-    e = launch_dw2_dh(P, d, f, (const bf16_t*)dY, gate_w ? (const float*)(c + C.row_gate) : P.row_gate, H, (const bf16_t*)W2, dSdG, dSdU,
-                      (bf16_t*)dW2, dG, dU, s);
-    if (e != hipSuccess) return fail_hip(e);
-    PhaseTimer t_dxp(GROUTER_PH_DW13_DXP, s, &t_dh);
-    e = launch_dw13_dxp(P, d, f, (const bf16_t*)x, dG, dU, (const bf16_t*)W1, (const bf16_t*)W3, (bf16_t*)dW1, (bf16_t*)dW3, dXp, s);
-    if (e != hipSuccess) return fail_hip(e);
-    PhaseTimer t_dx(GROUTER_PH_DXREDUCE, s, &t_dxp);
-    e = launch_combine(P, d, dXp, nullptr, (bf16_t*)dX, s);
+    auto dw2_dh = [&](BwdPart part) {
+        return launch_dw2_dh(part, P, d, f, (const bf16_t*)dY, gate_w ? (const float*)(c + C.row_gate) : P.row_gate, H, (const bf16_t*)W2,
+                             dSdG, dSdU, (bf16_t*)dW2, dG, dU, s);
+    };
+    auto dw13_dxp = [&](BwdPart part) {
+        return launch_dw13_dxp(part, P, d, f, (const bf16_t*)x, dG, dU, (const bf16_t*)W1, (const bf16_t*)W3, (bf16_t*)dW1, (bf16_t*)dW3, dXp, s);
+    };
+    auto reduce = [&](PhaseTimer* after) {
+        PhaseTimer t(GROUTER_PH_DXREDUCE, s, after);
+        return launch_combine(P, d, dXp, nullptr, (bf16_t*)dX, s);
+    };
+    PhaseTimer t_dw2(GROUTER_PH_DW2, s);
+    if (t_dw2.on) {   // every product is a launch and a phase of its own
+        e = dw2_dh(kBwdWeights);
+        if (e != hipSuccess) return fail_hip(e);
+        PhaseTimer t_dh(GROUTER_PH_DH, s, &t_dw2);
+        e = dw2_dh(kBwdRows);
+        if (e != hipSuccess) return fail_hip(e);
+        PhaseTimer t_dw13(GROUTER_PH_DW13, s, &t_dh);
+        e = dw13_dxp(kBwdWeights);
+        if (e != hipSuccess) return fail_hip(e);
+        PhaseTimer t_dxp(GROUTER_PH_DXP, s, &t_dw13);
+        e = dw13_dxp(kBwdRows);
+        if (e != hipSuccess) return fail_hip(e);
+        e = reduce(&t_dxp);
+    } else {
+        e = dw2_dh(kBwdBoth);
+        if (e != hipSuccess) return fail_hip(e);
+        e = dw13_dxp(kBwdBoth);
+        if (e != hipSuccess) return fail_hip(e);
+        e = reduce(nullptr);
+    }
     return e == hipSuccess ? GROUTER_OK : fail_hip(e);
 }
 
@@ -525,7 +548,7 @@ int grouter_timing_read(double* ms, int64_t* launches) {
 
 const char* grouter_phase_name(int phase) {
     static const char* names[GROUTER_PH_COUNT] = {"plan", "permute", "gateup", "down", "combine", "dO",
-                                                  "dW2+dH", "dW2", "dW13", "dW13+dXp", "dX_reduce", "affinity",
+                                                  "dH", "dW2", "dW13", "dXp", "dX_reduce", "affinity",
                                                   "placement", "coactivation", "fold", "sample_stats"};
     return (phase >= 0 && phase < GROUTER_PH_COUNT) ? names[phase] : "?";
 }

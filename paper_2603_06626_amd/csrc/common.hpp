@@ -131,9 +131,11 @@ hipError_t launch_combine(const PlanView& P, int d, const bf16_t* in, const bf16
 hipError_t launch_gateup(const PlanView& P, int d, int f, const bf16_t* x, const float* row_gate, const bf16_t* W1,
                          const bf16_t* W3, bf16_t* dSdG, bf16_t* dSdU, bf16_t* H, hipStream_t s);
 hipError_t launch_down(const PlanView& P, int d, int f, const bf16_t* H, const bf16_t* W2, bf16_t* O, hipStream_t s);
-hipError_t launch_dw2_dh(const PlanView& P, int d, int f, const bf16_t* dY, const float* row_gate, const bf16_t* H, const bf16_t* W2,
+// Each backward launch has two products that may run side by side, a weight gradient and one over rows, or only one of them.
+enum BwdPart { kBwdBoth = 0, kBwdWeights = 1, kBwdRows = 2 };
+hipError_t launch_dw2_dh(BwdPart part, const PlanView& P, int d, int f, const bf16_t* dY, const float* row_gate, const bf16_t* H, const bf16_t* W2,
                          const bf16_t* dSdG, const bf16_t* dSdU, bf16_t* dW2, bf16_t* dG, bf16_t* dU, hipStream_t s);
-hipError_t launch_dw13_dxp(const PlanView& P, int d, int f, const bf16_t* x, const bf16_t* dG, const bf16_t* dU, const bf16_t* W1,
+hipError_t launch_dw13_dxp(BwdPart part, const PlanView& P, int d, int f, const bf16_t* x, const bf16_t* dG, const bf16_t* dU, const bf16_t* W1,
                            const bf16_t* W3, bf16_t* dW1, bf16_t* dW3, bf16_t* dXp, hipStream_t s);
 
 }  // namespace grouter

@@ -38,7 +38,15 @@ static unsigned dw_grid(int E, int n_mt, int n_nt) {
     return 8u * (unsigned)(((E + 3) / 4) * worst);
 }
 
-hipError_t launch_dw2_dh(const PlanView& P, int d, int f, const bf16_t* dY, const float* row_gate, const bf16_t* H, const bf16_t* W2,
+template <BwdMode MODE>
+static hipError_t launch_pair(BwdPart part, const PlanView& P, const DwArgs& w, const RowsArgs& a, hipStream_t s) {
+    const unsigned n_dw = part == kBwdRows ? 0u : dw_grid(P.E, w.n_mt, w.n_nt);
+    const unsigned n_rows = part == kBwdWeights ? 0u : rows_grid(P, a.n_ntiles);
+    hipLaunchKernelGGL(k_bwd_pair<MODE>, dim3(n_dw + n_rows), dim3(kThreads), 0, s, w, a, (int)n_dw);
+    return hipGetLastError();
+}
+
+hipError_t launch_dw2_dh(BwdPart part, const PlanView& P, int d, int f, const bf16_t* dY, const float* row_gate, const bf16_t* H, const bf16_t* W2,
                          const bf16_t* dSdG, const bf16_t* dSdU, bf16_t* dW2, bf16_t* dG, bf16_t* dU, hipStream_t s) {
     DwArgs w = dw_args(P);
     // H is the saved gate-weighted H, so the upstream gradient enters unscaled, straight from dY [T][d]
@@ -51,12 +59,10 @@ hipError_t launch_dw2_dh(const PlanView& P, int d, int f, const bf16_t* dY, cons
     a.row_token = P.row_token; a.a_total_bytes = w.gathered_bytes;
     a.row_gate = row_gate;
     a.col_group = 3;   // column tiles walked in groups, row tiles fastest (as in the forward GEMMs): measured -2 % against the plain order
-    const unsigned n_dw = dw_grid(P.E, w.n_mt, w.n_nt);
-    hipLaunchKernelGGL(k_bwd_pair<kDh>, dim3(n_dw + rows_grid(P, a.n_ntiles)), dim3(kThreads), 0, s, w, a, (int)n_dw);
-    return hipGetLastError();
+    return launch_pair<kDh>(part, P, w, a, s);
 }
 
-hipError_t launch_dw13_dxp(const PlanView& P, int d, int f, const bf16_t* x, const bf16_t* dG, const bf16_t* dU, const bf16_t* W1,
+hipError_t launch_dw13_dxp(BwdPart part, const PlanView& P, int d, int f, const bf16_t* x, const bf16_t* dG, const bf16_t* dU, const bf16_t* W1,
                            const bf16_t* W3, bf16_t* dW1, bf16_t* dW3, bf16_t* dXp, hipStream_t s) {
     DwArgs w = dw_args(P);
     w.A = x; w.B0 = dG; w.B1 = dU; w.C0 = dW1; w.C1 = dW3;
@@ -66,9 +72,7 @@ hipError_t launch_dw13_dxp(const PlanView& P, int d, int f, const bf16_t* x, con
     a.A0 = dG; a.A1 = dU; a.B0 = W1; a.B1 = W3; a.C0 = dXp;
     a.K = f; a.Ncols = d; a.n_ntiles = (d + 255) / 256;
     a.col_group = 4;   // measured best of 0 (plain order), 2, 3, 4: -2 %
-    const unsigned n_dw = dw_grid(P.E, w.n_mt, w.n_nt);
-    hipLaunchKernelGGL(k_bwd_pair<kDxp>, dim3(n_dw + rows_grid(P, a.n_ntiles)), dim3(kThreads), 0, s, w, a, (int)n_dw);
-    return hipGetLastError();
+    return launch_pair<kDxp>(part, P, w, a, s);
 }
 
 }  // namespace grouter

@@ -88,6 +88,15 @@ def test_argument_errors_are_reported_on_the_host(b):
     assert L.grouter_mfma_probe(0, 4, 8, None, 8 * 256, None) == b.ERR_INVALID_ARG
 
 
+def test_every_backward_product_has_a_phase_of_its_own(b):
+    hdr = open(os.path.join(ROOT, "include", "grouter.h")).read()
+    names = {n: int(v) for n, v in re.findall(r"GROUTER_PH_([A-Z0-9_]+) = (\d+)", hdr)}
+    assert names.pop("COUNT") == len(names) == len(b.PHASES)
+    assert [names[n] for n in ("DH", "DW2", "DW13", "DXP")] == [6, 7, 8, 9]
+    assert b.PHASES[6:10] == ("dH", "dW2", "dW13", "dXp")
+    assert [b.lib().grouter_phase_name(i).decode() for i in range(len(b.PHASES))] == list(b.PHASES)
+
+
 def test_missing_library_fails_loudly(b, monkeypatch):
     monkeypatch.setattr(b, "_lib", None)
     monkeypatch.setattr(b, "LIB_PATH", os.path.join(ROOT, "does_not_exist.so"))
