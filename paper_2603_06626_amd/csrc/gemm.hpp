@@ -202,17 +202,95 @@ struct IntC {
 };
 
 // ---------------------------------------------------------------------------------------------------
-// The step loop shared by every GEMM.  A step is 32 MFMAs per wave.  Per-step ("B") buffers rotate through three LDS
-// slots; when kSuperA is set the A operand lives in two super-tile buffers that each serve two consecutive steps (four
-// copies), otherwise A is part of the per-step buffers.
+// The step loop of the backward row GEMMs and of weight gradients with short reductions.  A step is 32 MFMAs per wave.
+// Per-step ("B") buffers rotate through three LDS slots and are fetched two steps ahead, four copies per thread and step; when kSuperA is set the
+// A operand lives in two super-tile buffers that each serve two consecutive steps and are fetched (four
+// copies) during the even step two ahead, otherwise A is part of the per-step buffers (two more copies).
 //
-// Two levels of prefetch.  While step j multiplies out of registers, the fragments of step j + 1 travel from LDS to the
+//   prepare_a()                           called once, after the first per-step copies are on their way
+//   issue_a(super_index, a_buffer)        kSuperA: enqueue the 4 copies of A super tile `super_index`
+//   issue_b(step, IntC<slot>)             enqueue the per-step copies of `step` into slot `slot`
+//   compute(IntC<slot>, IntC<half>, a_buffer, issue)   the 32 MFMAs of one step; `issue()` is called once
+//                                         part-way through to enqueue the copies that belong to this step
+//   compute_rt(slot, half, a_buffer, issue)   the same with run-time indices (loop tail)
+// Copies complete in issue order, so "wait until at most N are outstanding" is all the synchronisation a wave
+// needs before the step barrier: the N youngest are exactly the ones issued for later steps.
+struct NoPrepare {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <bool kSuperA, int kStepCopies, class IssueA, class IssueB, class Compute, class ComputeRt, class PrepareA = NoPrepare>
+__device__ __forceinline__ void step_pipeline(int n_steps, IssueA issue_a, IssueB issue_b, Compute compute,
+                                              ComputeRt compute_rt, PrepareA prepare_a = PrepareA{}) {
+    if (n_steps <= 0) return;
+    constexpr int kACopies = kSuperA ? 4 : 0;
+    // prologue: the per-step buffers of step 0 (their addresses are known first: a gathered A operand still
+    // waits for its row map and finishes its offsets in prepare_a), A super tile 0, then the per-step buffers
+    // of step 1
+    issue_b(0, IntC<0>{});
+    prepare_a();
+    if (kSuperA) issue_a(0, 0);
+    if (n_steps > 1) issue_b(1, IntC<1>{});
+    int j = 0;
+    int abuf = 0;  // A super buffer of the current step: (j / 2) % 2
+    // Steady state, unrolled over the three slots and the two halves of a super tile.  Every copy named in
+    // the body exists as long as step j + 7 does.
+    for (; j + 8 <= n_steps; j += 6) {
+#define GROUTER_STEP(u, SLOT, HALF)                                                                            \
+    {                                                                                                          \
+        if (kSuperA && (HALF) == 1) wait_async_copies<kStepCopies + kACopies>();                               \
+        else wait_async_copies<kStepCopies>();                                                                 \
+        __syncthreads();                                                                                       \
+        const int cur = j + (u);                                                                               \
+        compute(IntC<SLOT>{}, IntC<HALF>{}, abuf, [&]() {                                                      \
+            if (kSuperA && (HALF) == 0) issue_a(cur / 2 + 1, abuf ^ 1);                                        \
+            issue_b(cur + 2, IntC<((SLOT) + 2) % 3>{});                                                        \
+        });                                                                                                    \
+        if ((HALF) == 1) abuf ^= 1;                                                                            \
+    }
+        GROUTER_STEP(0, 0, 0)
+        GROUTER_STEP(1, 1, 1)
+        GROUTER_STEP(2, 2, 0)
+        GROUTER_STEP(3, 0, 1)
+        GROUTER_STEP(4, 1, 0)
+        GROUTER_STEP(5, 2, 1)
+#undef GROUTER_STEP
+    }
+    // Tail: the same schedule with run-time indices and existence checks; waits are exact.
+    int slot = 0;
+    for (; j < n_steps; ++j) {
+        const int half = j & 1;
+        // copies younger than the ones this step needs: those issued during step j-1
+        const bool prev_issued_b = j + 1 < n_steps;                          // per-step copies of step j+1
+        const bool prev_issued_a = kSuperA && half == 1 && (j + 1 < n_steps);  // super tile (j+1)/2, issued at even j-1
+        if (prev_issued_b && prev_issued_a) wait_async_copies<kStepCopies + kACopies>();
+        else if (prev_issued_b) wait_async_copies<kStepCopies>();
+        else wait_async_copies<0>();
+        __syncthreads();
+        const int cur = j;
+        compute_rt(slot, half, abuf, [&]() {
+            if (kSuperA && half == 0 && cur + 2 < n_steps) issue_a(cur / 2 + 1, abuf ^ 1);
+            if (cur + 2 < n_steps) {
+                const int s2 = slot >= 1 ? slot - 1 : slot + 2;
+                if (s2 == 0) issue_b(cur + 2, IntC<0>{});
+                else if (s2 == 1) issue_b(cur + 2, IntC<1>{});
+                else issue_b(cur + 2, IntC<2>{});
+            }
+        });
+        if (half == 1) abuf ^= 1;
+        slot = slot == 2 ? 0 : slot + 1;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// The step loop of the forward GEMMs and of weight gradients with long reductions: the same buffers with two levels of
+// prefetch.  While step j multiplies out of registers, the fragments of step j + 1 travel from LDS to the
 // other register set, and the copies of step j + 3 go to the LDS slot of step j, which is free because its fragments
 // were read during step j - 1.  Without the register level a workgroup's step was a chain of barrier, LDS reads and MFMAs
-// that only the other workgroup of the CU could fill.  Measured (ratio to the time without it, same box): forward pass of
-// 8192 tokens, d = 2048, f = 1408, E = 64, k = 6 0.983; forward and backward 0.997; 16384 tokens, d = 4096, f = 1536,
-// E = 128, k = 8 0.986.  Enqueueing the copies before the first MFMAs instead of after eight: forward the same, backward
-// out of registers (1.8 times the time).
+// that only the other workgroup of the CU could fill.  Measured without and with it, T = 8192, d = 2048, f = 1408, E = 64,
+// k = 6: gate/up 601 -> 593 us, down 308 -> 298, dW2 314 -> 304, dW1/dW3 604 -> 602; T = 16384, d = 4096, f = 1536, E = 128,
+// k = 8: gate/up 3064 -> 2960, dW2 1649 -> 1587, dW1/dW3 3285 -> 3142.  The backward row GEMMs have two K halves per step to
+// overlap as it is and lose with it (dH 367 -> 371 us, dXp 580 -> 600 on the first shape, 1660 -> 1700 and 3140 -> 3175 on
+// the second), and so do short weight-gradient reductions, because of the copies of steps that do not exist.
 //
 //   prepare_a()                              called once, after the first per-step copies are on their way
 //   issue_a(super_index, a_buffer, dead)     kSuperA: enqueue the 4 copies of A super tile `super_index`
@@ -225,15 +303,13 @@ struct IntC {
 //       - requests the next step's fragments and multiplies this step's.
 // dead = kOutOfRange for a step that does not exist: its copies fetch nothing (they write zeros nobody reads), so the
 // number of outstanding copies, which the waits are counted in, stays the same up to the last step.  (Checking in the
-// loop whether a step exists instead spilled 800 to 1500 registers: 20 times slower.)
+// loop whether a step exists instead spilled 800 to 1500 registers: 20 times slower; with the check in the copy's own
+// assembly dW1/dW3 takes 636 us instead of 604 on the first shape.)
 // Copies complete in issue order, so "wait until at most N are outstanding" is all the synchronisation a wave
 // needs before the step barrier: the N youngest are exactly the ones issued for later steps.
-struct NoPrepare {
-    __device__ __forceinline__ void operator()() const {}
-};
 template <bool kSuperA, int kStepCopies, class IssueA, class IssueB, class First, class Step, class PrepareA = NoPrepare>
-__device__ __forceinline__ void step_pipeline(int n_steps, IssueA issue_a, IssueB issue_b, First first, Step step,
-                                              PrepareA prepare_a = PrepareA{}) {
+__device__ __forceinline__ void step_pipeline_ahead(int n_steps, IssueA issue_a, IssueB issue_b, First first, Step step,
+                                                    PrepareA prepare_a = PrepareA{}) {
     if (n_steps <= 0) return;
     constexpr int kACopies = kSuperA ? 4 : 0;
     auto dead = [&](int at) { return at < n_steps ? 0u : kOutOfRange; };

@@ -38,11 +38,24 @@ static unsigned dw_grid(int E, int n_mt, int n_nt) {
     return 8u * (unsigned)(((E + 3) / 4) * worst);
 }
 
+// Whether the weight gradients take the step loop with fragments in two register sets (step_pipeline_ahead).  Measured over
+// uniform and skewed loads, 8 to 64 experts, d from 256 to 4096 (time without / with it):
+//   dW2       mean rows per expert 128: 0.99-1.04, 192: 0.99-1.06, 256: 0.96-1.05, 384: 1.02-1.09, 768: 0.98-1.08, 2048: 0.99-1.08
+//   dW1/dW3   below 512 rows: 0.96-1.03; from 512 on with at least 8192 tiles (16 times what is resident) 0.99-1.02,
+//             T = 16384, d = 4096, f = 1536, E = 128, k = 8 1.045; with fewer tiles 0.94-1.03
+// Short reductions lose most: 8 rows per expert (T = 128, d = 4096, f = 1536, E = 128, k = 8) dW2 298 us without, 338 with it;
+// 64 rows (T = 2048, d = f = 1024, E = 64, k = 2) dW1/dW3 73 and 80 us.
+static bool two_register_sets(BwdMode mode, const PlanView& P, const DwArgs& w) {
+    const int64_t mean_rows = P.N / P.E;
+    return mode == kDh ? mean_rows >= 256 : mean_rows >= 512 && (int64_t)P.E * w.n_mt * w.n_nt >= 8192;
+}
+
 template <BwdMode MODE>
 static hipError_t launch_pair(BwdPart part, const PlanView& P, const DwArgs& w, const RowsArgs& a, hipStream_t s) {
     const unsigned n_dw = part == kBwdRows ? 0u : dw_grid(P.E, w.n_mt, w.n_nt);
     const unsigned n_rows = part == kBwdWeights ? 0u : rows_grid(P, a.n_ntiles);
-    hipLaunchKernelGGL(k_bwd_pair<MODE>, dim3(n_dw + n_rows), dim3(kThreads), 0, s, w, a, (int)n_dw);
+    if (two_register_sets(MODE, P, w)) hipLaunchKernelGGL((k_bwd_pair<MODE, true>), dim3(n_dw + n_rows), dim3(kThreads), 0, s, w, a, (int)n_dw);
+    else hipLaunchKernelGGL((k_bwd_pair<MODE, false>), dim3(n_dw + n_rows), dim3(kThreads), 0, s, w, a, (int)n_dw);
     return hipGetLastError();
 }
 

@@ -268,7 +268,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fwd_gemm(const RowsArgs a) {
         read(fr[half ^ 1], IntC<(slot + 1) % 3>{}, IntC<half ^ 1>{}, half ? abuf ^ 1 : abuf);
         multiply(fr[half], issue);
     };
-    step_pipeline<true, 4>(n_steps, issue_a, issue_b, [&]() { read(fr[0], IntC<0>{}, IntC<0>{}, 0); }, step, prepare_a);
+    step_pipeline_ahead<true, 4>(n_steps, issue_a, issue_b, [&]() { read(fr[0], IntC<0>{}, IntC<0>{}, 0); }, step, prepare_a);
 
     // ---- epilogue: accumulators -> (fused elementwise) -> LDS -> whole-row 16-byte stores
     const int cols_valid = min(BN, Ncols - t.col0);
@@ -386,26 +386,25 @@ __device__ __forceinline__ void bwd_rows_tile(const RowsArgs& a, int block, char
             b_voff[h][p] = r < Ncols ? ((uint32_t)r * (uint32_t)K + piece * 8) * 2u : kOutOfRange;
         }
 
-    auto issue_super = [&](i32x4 buf, const uint32_t voff[4], int k0, uint32_t dst, uint32_t dead) {
+    auto issue_super = [&](i32x4 buf, const uint32_t voff[4], int k0, uint32_t dst) {
         const bool partial = k0 + 64 > K;
-        const uint32_t soff = dead ? 0u : (uint32_t)k0 * 2u;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            uint32_t v = voff[p] | dead;
+            uint32_t v = voff[p];
             if (partial) v = (k0 + piece * 8 < K) ? v : kOutOfRange;
-            async_copy16(buf, v, soff, dst + KcSuper::pass_offset(p));
+            async_copy16(buf, v, (uint32_t)k0 * 2u, dst + KcSuper::pass_offset(p));
         }
     };
-    auto issue_a = [&](int super, int abuf, uint32_t dead) {
+    auto issue_a = [&](int super, int abuf) {
         const int ph = (NPH == 2 && super >= n_super) ? 1 : 0;
-        issue_super(ph ? bufA1 : bufA0, a_voff, (super - ph * n_super) * 64, smem_addr + abuf * kSuperBytes + wave_base, dead);
+        issue_super(ph ? bufA1 : bufA0, a_voff, (super - ph * n_super) * 64, smem_addr + abuf * kSuperBytes + wave_base);
     };
-    auto issue_b = [&](int step, auto slot_c, uint32_t dead) {
+    auto issue_b = [&](int step, auto slot_c) {
         const int super = step >> 1;
         const int ph = (NPH == 2 && super >= n_super) ? 1 : 0;
         const uint32_t dst = smem_addr + kBRegion + decltype(slot_c)::value * kBTileBytes + wave_base;
-        if (step & 1) issue_super(ph ? bufB1 : bufB0, b_voff[1], (super - ph * n_super) * 64, dst, dead);
-        else issue_super(ph ? bufB1 : bufB0, b_voff[0], (super - ph * n_super) * 64, dst, dead);
+        if (step & 1) issue_super(ph ? bufB1 : bufB0, b_voff[1], (super - ph * n_super) * 64, dst);
+        else issue_super(ph ? bufB1 : bufB0, b_voff[0], (super - ph * n_super) * 64, dst);
     };
 
     Acc32 acc[4][2];  // [row block][column half]
@@ -415,38 +414,35 @@ __device__ __forceinline__ void bwd_rows_tile(const RowsArgs& a, int block, char
         for (int hf = 0; hf < 2; ++hf) clear(acc[fm][hf]);
 
     // One step: 2 K halves of the super tiles x (4 A fragments, 1 B fragment) = 32 MFMAs into the wave's column
-    // block `half`.  The register sets alternate between the K halves: the second half's fragments are requested before the
-    // first half's MFMAs, the next step's first half before the second half's.  A tile without a right half skips
-    // half 1's fragment reads and MFMAs; its copies are still issued (they are masked and fetch nothing), so the
-    // pipeline's copy counts stay as they are.
-    struct Frags {
-        Frag32 a[4], b;
-    };
-    Frags fr[2];
-    auto read = [&](Frags& to, auto slot_c, int abuf, int kh) {
-        const char* const At = smem + abuf * kSuperBytes;
-        const char* const Bt = smem + kBRegion + decltype(slot_c)::value * kBTileBytes;
-        to.b = KcSuper::read_frag(Bt, lane, wave * 32, kh);
-#pragma unroll
-        for (int fm = 0; fm < 4; ++fm) to.a[fm] = KcSuper::read_frag(At, lane, fm * 32, kh);
-    };
-    auto step = [&](auto slot_c, auto half_c, int abuf, auto arrive, auto issue) {
-        constexpr int slot = decltype(slot_c)::value, hf = decltype(half_c)::value;
-        const bool here = hf == 0 || right_half, next = hf == 1 || right_half;
-        if (here) {
-            read(fr[1], slot_c, abuf, 1);
-#pragma unroll
-            for (int fm = 0; fm < 4; ++fm) mfma32(fr[0].b, fr[0].a[fm], acc[fm][hf]);
+    // block `half`.  A tile without a right half skips half 1's fragment reads and MFMAs; its copies are still issued
+    // (they are masked and fetch nothing), so the pipeline's copy counts stay as they are.
+    auto step_body = [&](const char* At, const char* Bt, auto half_c, auto issue) {
+        constexpr int hf = decltype(half_c)::value;
+        if (hf == 1 && !right_half) {
+            issue();
+            return;
         }
-        arrive();
-        if (next) read(fr[0], IntC<(slot + 1) % 3>{}, hf ? abuf ^ 1 : abuf, 0);
-        issue();
-        if (here) {
 #pragma unroll
-            for (int fm = 0; fm < 4; ++fm) mfma32(fr[1].b, fr[1].a[fm], acc[fm][hf]);
+        for (int kh = 0; kh < 2; ++kh) {  // one K half at a time keeps the fragment registers at 40
+            Frag32 af[4];
+            const Frag32 bf = KcSuper::read_frag(Bt, lane, wave * 32, kh);
+#pragma unroll
+            for (int fm = 0; fm < 4; ++fm) af[fm] = KcSuper::read_frag(At, lane, fm * 32, kh);
+#pragma unroll
+            for (int fm = 0; fm < 4; ++fm) {
+                mfma32(bf, af[fm], acc[fm][hf]);
+                if (kh == 0 && fm == 1) issue();
+            }
         }
     };
-    step_pipeline<true, 4>(n_steps, issue_a, issue_b, [&]() { read(fr[0], IntC<0>{}, 0, 0); }, step, prepare_a);
+    auto compute = [&](auto slot_c, auto half_c, int abuf, auto issue) {
+        step_body(smem + abuf * kSuperBytes, smem + kBRegion + decltype(slot_c)::value * kBTileBytes, half_c, issue);
+    };
+    auto compute_rt = [&](int slot, int half, int abuf, auto issue) {
+        if (half) step_body(smem + abuf * kSuperBytes, smem + kBRegion + slot * kBTileBytes, IntC<1>{}, issue);
+        else step_body(smem + abuf * kSuperBytes, smem + kBRegion + slot * kBTileBytes, IntC<0>{}, issue);
+    };
+    step_pipeline<true, 4>(n_steps, issue_a, issue_b, compute, compute_rt, prepare_a);
 
     const int cols_valid = min(BN, Ncols - t.col0);
     const size_t tile_at = (size_t)t.row0 * Ncols + t.col0;
@@ -600,7 +596,8 @@ struct DwArgs {
 enum DwGather { kGatherNone = 0, kGatherA = 1, kGatherB = 2 };
 constexpr int kIdRingAt = 24 * 1024;  // between the A slots (3 x 8 KB) and the B slots (from 32 KB)
 
-template <int NB, int GATHER>
+// AHEAD: the step loop that keeps the next step's fragments in registers, for long reductions (see step_pipeline_ahead).
+template <int NB, int GATHER, bool AHEAD>
 __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) {
     static_assert(GATHER != kGatherB || NB == 1, "a gathered B operand is only provided for one B");
     constexpr int kStepCopies = GATHER == kGatherNone ? 6 : 7;
@@ -665,7 +662,8 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
     const i32x4 bufTok = make_buffer(GATHER != kGatherNone ? a.row_token + off : nullptr, (uint32_t)cnt * 4u);
     const uint32_t id_ring = smem_addr + kIdRingAt + __builtin_amdgcn_readfirstlane((uint32_t)wave * 128u);
     auto issue_ids = [&](int step) {  // rows 32*step .. 32*step+31 -> this wave's ring slot step % 8
-        const uint32_t dst = __builtin_amdgcn_readfirstlane(id_ring + (uint32_t)(step & 7) * 512u);
+        uint32_t dst = id_ring + (uint32_t)(step & 7) * 512u;
+        if constexpr (AHEAD) dst = __builtin_amdgcn_readfirstlane(dst);   // (the other loop has no register to spare for it)
         if (lane < 32) async_copy4(bufTok, (uint32_t)lane * 4u, (uint32_t)step * 128u, dst);
     };
     auto token_of = [&](int step, int krow) {
@@ -677,17 +675,18 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
     // copies in the middle of the MFMA stream find them in registers.
     constexpr int kGatherPasses = GATHER == kGatherA ? 2 : (GATHER == kGatherB ? BTile::kPasses : 1);
     int32_t tok[kGatherPasses] = {};
-    int next_issue = 3;   // the step whose copies the next multiply() issues (0, 1 and 2 belong to the prologue)
+    constexpr int kPrologue = AHEAD ? 3 : 2;   // steps whose copies the prologue issues
+    int next_issue = kPrologue;                // the step whose copies the next step of the loop issues
     auto load_ids = [&](int step) {
 #pragma unroll
         for (int p = 0; p < kGatherPasses; ++p)
             tok[p] = token_of(step, GATHER == kGatherA ? ATile::krow_of(tid, p) : BTile::krow_of(tid, p));
     };
-    auto issue_a = [&](int, int, uint32_t) {};
-    auto issue_b = [&](int step, auto slot_c, uint32_t dead) {  // per-step copies: the A tile (2), the B tile(s) (4), and the ids
+    auto issue_a = [&](int, int, uint32_t = 0u) {};
+    auto issue_b = [&](int step, auto slot_c, uint32_t dead = 0u) {  // per-step copies: the A tile (2), the B tile(s) (4), and the ids
         constexpr int slot = decltype(slot_c)::value;
         if constexpr (GATHER != kGatherNone) {
-            if (step < 3) load_ids(step);   // prologue; later steps were read ahead
+            if (step < kPrologue) load_ids(step);   // later steps were read ahead
         }
         const uint32_t k0 = dead ? 0u : (uint32_t)step * 32u;
         const uint32_t a_dst = smem_addr + slot * kMcSmallBytes + wave_base;
@@ -734,9 +733,9 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
     struct Frags {
         Frag32 a[4], b[2];
     };
-    auto read = [&](Frags& fr, auto slot_c) {
-        const char* const At = smem + decltype(slot_c)::value * kMcSmallBytes;
-        const char* const Bt = smem + kBRegion + decltype(slot_c)::value * kBTileBytes;
+    auto read = [&](Frags& fr, int slot) {
+        const char* const At = smem + slot * kMcSmallBytes;
+        const char* const Bt = smem + kBRegion + slot * kBTileBytes;
         // the 12 fragment addresses are derived from these two in every step (an XOR each) instead of being
         // held in registers over the whole loop
         uint32_t ab = a_lane, bb = b_lane;
@@ -747,7 +746,6 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
         for (int fm = 0; fm < 4; ++fm) fr.a[fm] = ATile::read_frag(At, ab, fm * 32);
     };
     auto multiply = [&](const Frags& fr, auto issue) {
-        if constexpr (GATHER != kGatherNone) load_ids(next_issue++);
 #pragma unroll
         for (int g = 0; g < 2; ++g)
 #pragma unroll
@@ -756,15 +754,28 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
                 if (g == 0 && fm == 1) issue();
             }
     };
-    Frags fr[2];
-    auto step = [&](auto slot_c, auto half_c, int, auto arrive, auto issue) {
-        constexpr int slot = decltype(slot_c)::value, half = decltype(half_c)::value;
-        arrive();
-        read(fr[half ^ 1], IntC<(slot + 1) % 3>{});
-        multiply(fr[half], issue);
-    };
-    step_pipeline<false, kStepCopies>((cnt + 31) / 32, issue_a, issue_b, [&]() { read(fr[0], IntC<0>{}); }, step);
-    if constexpr (GATHER != kGatherNone) wait_async_copies<0>();  // id copies of an expert without rows
+    const int n_steps = (cnt + 31) / 32;
+    if constexpr (AHEAD) {
+        Frags fr[2];
+        auto step = [&](auto slot_c, auto half_c, int, auto arrive, auto issue) {
+            constexpr int slot = decltype(slot_c)::value, half = decltype(half_c)::value;
+            arrive();
+            read(fr[half ^ 1], (slot + 1) % 3);
+            if constexpr (GATHER != kGatherNone) load_ids(next_issue++);
+            multiply(fr[half], issue);
+        };
+        step_pipeline_ahead<false, kStepCopies>(n_steps, issue_a, issue_b, [&]() { read(fr[0], 0); }, step);
+    } else {
+        auto compute_rt = [&](int slot, int, int, auto issue) {
+            if constexpr (GATHER != kGatherNone) load_ids(next_issue++);
+            Frags fr;
+            read(fr, slot);
+            multiply(fr, issue);
+        };
+        auto compute = [&](auto slot_c, auto, int, auto issue) { compute_rt(decltype(slot_c)::value, 0, 0, issue); };
+        step_pipeline<false, kStepCopies>(n_steps, issue_a, issue_b, compute, compute_rt);
+    }
+    if constexpr (GATHER != kGatherNone) wait_async_copies<0>();  // id copies of steps that do not exist
 
     const int rows_valid = min(kTileM, Mdim - m0);
     const int cols_valid = min(BN, Ndim - n0);
@@ -783,15 +794,14 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
 // problem leaves the chip idle behind its longest workgroup (a weight gradient's is as long as the hottest expert's rows).
 // Measured, plan + forward + backward, four backward launches -> two: T = 256, d = 128, f = 256, E = 8, k = 2: 65.8 -> 51.0
 // us; T = 3001, d = 1032, f = 680, E = 48, k = 3: 362 -> 343; T = 8192, d = 2048, f = 1408, E = 64, k = 6, where every
-// product fills the chip many times over: 2846 -> 2847.  Reductions of a few steps (T = 6846, E = 128, k = 2) are 2 % slower
-// than they were with launches of their own and a step loop without masked copies.
-template <int MODE>
+// product fills the chip many times over: 2846 -> 2847.
+template <int MODE, bool AHEAD>
 __global__ __launch_bounds__(kThreads, 2) void k_bwd_pair(const DwArgs w, const RowsArgs r, int n_dw) {
     __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
     const int block = (int)blockIdx.x;
     if (block < n_dw) {
-        if constexpr (MODE == kDh) dw_tile<1, kGatherB>(w, block, smem);
-        else dw_tile<2, kGatherA>(w, block, smem);
+        if constexpr (MODE == kDh) dw_tile<1, kGatherB, AHEAD>(w, block, smem);
+        else dw_tile<2, kGatherA, AHEAD>(w, block, smem);
     } else {
         bwd_rows_tile<MODE>(r, block - n_dw, smem);
     }
