@@ -27,15 +27,16 @@ static DwArgs dw_args(const PlanView& P) {
 
 static unsigned rows_grid(const PlanView& P, int n_ntiles) { return (unsigned)P.max_tiles_small * (unsigned)n_ntiles; }
 
-// 8 XCDs x (largest per-XCD share): the share pattern repeats every 4 experts
-static unsigned dw_grid(int E, int n_mt, int n_nt) {
+// Workgroups of the weight-gradient tiles of four experts of neighbouring load ranks: 8 XCDs x (largest per-XCD share); the
+// share pattern repeats every 4 experts.
+static unsigned dw_grid_of_four(int n_mt, int n_nt) {
     int worst = 0;
     for (int x = 0; x < 8; ++x) {
         int per_quad = 0;
         for (int tq = 0; tq < 4; ++tq) per_quad += DwShare(x, tq, n_mt, n_nt).tiles();
         worst = per_quad > worst ? per_quad : worst;
     }
-    return 8u * (unsigned)(((E + 3) / 4) * worst);
+    return 8u * (unsigned)worst;
 }
 
 // Whether the weight gradients take the step loop with fragments in two register sets (step_pipeline_ahead).  Measured over
@@ -50,12 +51,27 @@ static bool two_register_sets(BwdMode mode, const PlanView& P, const DwArgs& w) 
     return mode == kDh ? mean_rows >= 256 : mean_rows >= 512 && (int64_t)P.E * w.n_mt * w.n_nt >= 8192;
 }
 
+// Whether the row tiles open the grid.  A row tile has 2 K / 64 steps (for each of dXp's two phases), a weight-gradient tile one
+// per 32 rows of its expert, and the hottest experts hold several times the mean (2 to 10 times with Zipf exponents around
+// 1.2).  Where 4 times the mean reaches the row tiles' length, the heaviest eighth of the experts goes first.  Measured, rows
+// first / heaviest eighth first: T = 500, d = 256, f = 1536, E = 128, k = 8, skewed (mean 0 and row tiles 8 and 96 steps):
+// 167 / 193 us; T = 1334, d = 1600, f = 768, E = 16, k = 3 (7; 50, 48): 95 / 106; T = 4000, d = 512, f = 1536, E = 96, k = 4 (5; 16, 96):
+// 349 / 331, each product by this rule 320; T = 9000, d = 704, f = 1088, E = 64, k = 5 (21; 22, 68): 604 / 558, by this
+// rule 560; T = 16384, the same widths (40; 22, 68): 1076 / 972, 963.
+static bool rows_first(BwdMode mode, const PlanView& P, const RowsArgs& a) {
+    const int64_t row_steps = (mode == kDxp ? 4 : 2) * (int64_t)((a.K + 63) / 64);
+    return 4 * (P.N / P.E / 32) < row_steps;
+}
+
 template <BwdMode MODE>
 static hipError_t launch_pair(BwdPart part, const PlanView& P, const DwArgs& w, const RowsArgs& a, hipStream_t s) {
-    const unsigned n_dw = part == kBwdRows ? 0u : dw_grid(P.E, w.n_mt, w.n_nt);
-    const unsigned n_rows = part == kBwdWeights ? 0u : rows_grid(P, a.n_ntiles);
-    if (two_register_sets(MODE, P, w)) hipLaunchKernelGGL((k_bwd_pair<MODE, true>), dim3(n_dw + n_rows), dim3(kThreads), 0, s, w, a, (int)n_dw);
-    else hipLaunchKernelGGL((k_bwd_pair<MODE, false>), dim3(n_dw + n_rows), dim3(kThreads), 0, s, w, a, (int)n_dw);
+    const unsigned fours = (unsigned)((P.E + 3) / 4), per_four = dw_grid_of_four(w.n_mt, w.n_nt);
+    const unsigned n_dw = part == kBwdRows ? 0u : fours * per_four;
+    const unsigned n_rows = part == kBwdWeights ? 0u : (rows_grid(P, a.n_ntiles) + 7u) / 8u * 8u;
+    const unsigned head = part == kBwdBoth && !rows_first(MODE, P, a) ? (fours + 7u) / 8u * per_four : 0u;
+    const dim3 grid(n_dw + n_rows), block(kThreads);
+    if (two_register_sets(MODE, P, w)) hipLaunchKernelGGL((k_bwd_pair<MODE, true>), grid, block, 0, s, w, a, (int)n_dw, (int)head, (int)n_rows);
+    else hipLaunchKernelGGL((k_bwd_pair<MODE, false>), grid, block, 0, s, w, a, (int)n_dw, (int)head, (int)n_rows);
     return hipGetLastError();
 }
 

@@ -789,16 +789,22 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
 
 // ===================================================================================================
 // The backward pass in two launches.  dW2 and dH need only what the forward pass kept, dW1/dW3 and dXp only dG and
-// dU, so each pair shares a grid: the first n_dw workgroups (a multiple of 8, which keeps the XCD mapping) take the
-// weight gradient's tiles, heaviest expert first, the rest the row tiles.  Alone, each product of a small or skewed
-// problem leaves the chip idle behind its longest workgroup (a weight gradient's is as long as the hottest expert's rows).
-// Measured, plan + forward + backward, four backward launches -> two: T = 256, d = 128, f = 256, E = 8, k = 2: 65.8 -> 51.0
-// us; T = 3001, d = 1032, f = 680, E = 48, k = 3: 362 -> 343; T = 8192, d = 2048, f = 1408, E = 64, k = 6, where every
-// product fills the chip many times over: 2846 -> 2847.
+// dU, so each pair shares a grid.  Alone, each product of a small or skewed problem leaves the chip idle behind its longest
+// workgroup (a weight gradient's is as long as the hottest expert's rows, a row tile's as long as the width).
+// What is long has to begin early: the grid is the weight-gradient tiles of the heaviest experts (head, possibly none), the
+// row tiles, the remaining weight-gradient tiles, which are short and fill the gaps.  head, n_dw and n_rows are multiples
+// of 8, which keeps the XCD mapping.
+// Measured, backward pass, four launches -> pairs with all weight gradients first -> pairs in this order: T = 2048,
+// d = f = 1024, E = 64, k = 2: 204 -> 222 -> 194 us (256 row tiles of 64 steps had started last, two on some CUs and none on
+// others); T = 246, d = 2880, f = 640, E = 48, k = 2: 240 -> 259 -> 210; T = 3001, d = 1032, f = 680, E = 48, k = 3, skewed:
+// 236 -> 217 -> 195; T = 256, d = 128, f = 256, E = 8, k = 2: 38 -> 23 -> 23; T = 8192, d = 2048, f = 1408, E = 64, k = 6,
+// where every product fills the chip many times over: 1874 -> 1870 -> 1847.
 template <int MODE, bool AHEAD>
-__global__ __launch_bounds__(kThreads, 2) void k_bwd_pair(const DwArgs w, const RowsArgs r, int n_dw) {
+__global__ __launch_bounds__(kThreads, 2) void k_bwd_pair(const DwArgs w, const RowsArgs r, int n_dw, int head, int n_rows) {
     __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
-    const int block = (int)blockIdx.x;
+    const int b = (int)blockIdx.x;
+    // weight-gradient tiles are numbered 0 .. n_dw - 1, row tiles from n_dw on
+    const int block = __builtin_amdgcn_readfirstlane(b < head ? b : b < head + n_rows ? b - head + n_dw : b - n_rows);
     if (block < n_dw) {
         if constexpr (MODE == kDh) dw_tile<1, kGatherB, AHEAD>(w, block, smem);
         else dw_tile<2, kGatherA, AHEAD>(w, block, smem);
