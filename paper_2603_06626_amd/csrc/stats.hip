@@ -29,7 +29,8 @@ __device__ __forceinline__ uint64_t unique_slots(const IdxT* ids, int k, int E) 
     for (int j = 0; j < k; ++j) {
         const int64_t e = (int64_t)ids[j];
         bool ok = e >= 0 && e < E;
-        for (int i = 0; i < j; ++i) ok = ok && ((int64_t)ids[i] != e);
+#pragma unroll 4
+        for (int i = 0; i < j; ++i) ok &= (int64_t)ids[i] != e;   // no early exit: the loads of a round are independent
         if (ok) m |= 1ull << j;
     }
     return m;
@@ -129,7 +130,10 @@ __device__ __forceinline__ double block_entropy(long long tot, double clogc, dou
 //   AFF    histogram of token membership, entropy of the normalised histogram (fp64, fixed summation order)
 //   PLACE  expert_nodes[e] has bit n set when expert e lives on node n, so the nodes a token reaches are the OR
 //          over its experts; per node the wave counts its lanes with one ballot
-template <class IdxT, bool AFF, bool PLACE>
+// WIDE: k > 8.  Apart, because what one of the two forms needs in registers costs the other occupancy.  2048 samples of 4096
+// tokens (512 for k = 16), E = 128, placement alone: k = 8 45 us as one
+// kernel, 40 apart; k = 16 285 -> 190 with the independent loads (affinity 287, then 298 for a while -> 201).
+template <class IdxT, bool AFF, bool PLACE, bool WIDE>
 __global__ __launch_bounds__(kStatThreads) void k_sample_stats(const IdxT* __restrict__ idx, int L, int k, int E,
                                                                int32_t* __restrict__ counts, double* __restrict__ entropy,
                                                                const uint64_t* __restrict__ expert_nodes, int n_nodes,
@@ -155,7 +159,7 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats(const IdxT* __res
         const int t = tb + tid;
         uint64_t reach = 0;
         if (t < L) {
-            if (k <= 8) {
+            if constexpr (!WIDE) {
                 int e[8];
                 load_token8(base, t, k, E, e);
 #pragma unroll
@@ -808,8 +812,12 @@ hipError_t launch_sample_stats(const void* idx, int idx_dtype, int64_t S, int L,
     auto* l = reinterpret_cast<unsigned long long*>(loads);
     const dim3 grid((unsigned)S), block(kStatThreads);
 #define GROUTER_STATS(T_, A_, P_)                                                                                  \
-    hipLaunchKernelGGL((k_sample_stats<T_, A_, P_>), grid, block, 0, s, (const T_*)idx, L, k, E, counts, entropy,  \
-                       expert_nodes, n_nodes, comm, best_node)
+    do {                                                                                                           \
+        if (k <= 8) hipLaunchKernelGGL((k_sample_stats<T_, A_, P_, false>), grid, block, 0, s, (const T_*)idx, L, k, E, counts, entropy, \
+                                       expert_nodes, n_nodes, comm, best_node);                                    \
+        else hipLaunchKernelGGL((k_sample_stats<T_, A_, P_, true>), grid, block, 0, s, (const T_*)idx, L, k, E, counts, entropy, \
+                                expert_nodes, n_nodes, comm, best_node);                                           \
+    } while (0)
 #define GROUTER_STATS8(T_, A_, P_, R_)                                                                             \
     hipLaunchKernelGGL((k_sample_stats8<T_, A_, P_, R_>), grid, block, 0, s, (const T_*)idx, L, k, E, counts, entropy, \
                        expert_nodes, n_nodes, comm, best_node)
