@@ -250,10 +250,12 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __re
     const IdxT* base = idx + (size_t)s * L * k;
     RawIds8 ahead{};
     if (tid < L) ahead = fetch_token8(base, tid, k);
-    for (int i = tid; i < (E + 1) * (R / 4); i += kStatThreads) {
-        const int e = i / (R / 4);
-        const uint32_t w = PLACE && e < E ? (uint32_t)expert_nodes[e] << 16 : 0u;
-        reinterpret_cast<uint4*>(s_tab)[i] = uint4{w, w, w, w};
+    if (!PLACE) {
+        for (int i = tid; i < (E + 1) * (R / 4); i += kStatThreads) reinterpret_cast<uint4*>(s_tab)[i] = uint4{0u, 0u, 0u, 0u};
+    } else if (tid <= E) {   // a thread fills a row, so that it loads one node set; each begins at another bank
+        const uint32_t w = tid < E ? (uint32_t)expert_nodes[tid] << 16 : 0u;
+#pragma unroll
+        for (int q = 0; q < R / 4; ++q) reinterpret_cast<uint4*>(s_tab)[tid * (R / 4) + ((q + tid) & (R / 4 - 1))] = uint4{w, w, w, w};
     }
     if (tid <= E) s_cnt[tid] = 0;
     if (tid < kFastStatNodes) s_comm[tid] = 0;
@@ -304,12 +306,19 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __re
         }
     }
     if (PLACE) {
-        for (int n = 0; n < n_nodes; ++n) {
-            const uint32_t w = (n >> 2) == 0 ? votes[0] : (n >> 2) == 1 ? votes[1] : (n >> 2) == 2 ? votes[2] : votes[3];
-            int v = (int)((w >> (8 * (n & 3))) & 255u);
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-            if (lane == 0) atomicAdd(&s_comm[n], v);
-        }
+        // four byte counts become two words of two 16-bit sums (at most 64 * 255 each), which are added over the wave: chains that
+        // run side by side instead of one after the other per node (32 samples of 256 tokens, 16 nodes: 13.1 -> 9.8 us)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (4 * q < n_nodes) {
+                uint32_t even = votes[q] & 0x00ff00ffu, odd = (votes[q] >> 8) & 0x00ff00ffu;
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) {
+                    even += __shfl_xor(even, o);
+                    odd += __shfl_xor(odd, o);
+                }
+                if (lane < 4 && 4 * q + lane < n_nodes) atomicAdd(&s_comm[4 * q + lane], (int)(((lane & 1 ? odd : even) >> (lane & 2 ? 16 : 0)) & 0xffffu));
+            }
     }
     __syncthreads();
     if (PLACE) {
@@ -805,6 +814,24 @@ __global__ __launch_bounds__(kStatThreads) void k_fold_weights(const float* __re
 
 }  // namespace
 
+// Whether k_sample_stats8 pays for its table, which it fills and adds up once per sample.  With a workgroup per CU that is
+// one table in a row; up to 1024 samples the CUs hold all tables at once; beyond, tables follow each other, and a placement
+// alone, which has no atomics to save, needs longer samples still.  Measured, general kernel / k_sample_stats8:
+//   32 to 256 samples, k = 8: 256 tokens 4.1 / 4.3 us (placement), 9.5 / 10.0 (both statistics); 512: 5.1 / 5.0, 10.8 / 10.7;
+//   1024: 7.3 / 6.3, 13.1 / 12.0; 4096: 20.3 / 14.0, 26.8 / 20.2; k = 2: 512 4.5 / 4.6, 768 5.4 / 5.2
+//   700 samples, k = 2: 1536 tokens 8.4 / 7.8 (placement), 14.6 / 14.0
+//   200 to 1024 samples, affinity alone, k = 2 to 8: 512 tokens 9.3 / 9.1, 768 11.5 / 11.1
+//   2048 samples, both statistics, k = 8: 512 tokens 20.5 / 22.0; 1024: 25.4 / 24.5; 2048: 38.1 / 31.5; placement alone: 512
+//   8.2 / 9.8; 1024: 12.4 / 12.9; 2048: 22.1 / 19.8; 4096: 39.9 / 32.9; k = 2: 2048 16.9 / 17.9, 4096 30.0 / 29.5
+//   16384 samples of 8 tokens: placement 20 / 43, both 80 / 110
+static bool packed_pays(int64_t S, int L, int k, bool affinity, bool placement) {
+    const int64_t ids = (int64_t)L * k;
+    if (S <= 1024 && !placement) return L >= 512;
+    if (S <= 256) return L >= 768 || ids >= 4096;
+    if (S <= 1024) return L >= 1024;
+    return ids >= (affinity ? 8192 : 16384);
+}
+
 // counts == nullptr skips the affinity half, comm == nullptr the placement half.
 hipError_t launch_sample_stats(const void* idx, int idx_dtype, int64_t S, int L, int k, int E, int32_t* counts,
                                double* entropy, int64_t* loads, double* maxvio, const uint64_t* expert_nodes, int n_nodes,
@@ -821,7 +848,7 @@ hipError_t launch_sample_stats(const void* idx, int idx_dtype, int64_t S, int L,
 #define GROUTER_STATS8(T_, A_, P_, R_)                                                                             \
     hipLaunchKernelGGL((k_sample_stats8<T_, A_, P_, R_>), grid, block, 0, s, (const T_*)idx, L, k, E, counts, entropy, \
                        expert_nodes, n_nodes, comm, best_node)
-    const bool fast = k <= 8 && E <= kFastStatE && n_nodes <= kFastStatNodes && L <= kFastStatL;
+    const bool fast = k <= 8 && E <= kFastStatE && n_nodes <= kFastStatNodes && L <= kFastStatL && packed_pays(S, L, k, counts != nullptr, comm != nullptr);
     // a column per lane where the table then fits 33 KB
 #define GROUTER_STATS_T(A_, P_)                                                      \
     do {                                                                             \

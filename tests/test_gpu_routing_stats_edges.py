@@ -23,6 +23,18 @@ from tests.test_gpu_routing_stats import DEV, check_all     # noqa: E402
     (1, 65280, 2, 5, 3, np.uint8),      # longest sample whose votes fit a byte per lane
     (1, 65281, 2, 5, 3, np.uint8),
     (4, 1, 1, 1, 1, np.int32),
+    (3, 511, 8, 128, 16, np.uint8),     # the last size of the general kernel
+    (3, 512, 8, 128, 16, np.uint8),     # the first of the packed one: a column per lane, widest table, most nodes
+    (3, 513, 8, 129, 5, np.uint8),      # narrower table; one token more than two rounds
+    (2, 767, 8, 247, 16, np.int32),     # last E of the packed form
+    (2, 768, 1, 247, 1, np.uint8),      # one id per token
+    (3, 769, 5, 33, 7, np.uint8),       # ids of a token not in one word
+    (2, 600, 8, 248, 4, np.uint8),      # general kernel by E
+    (2, 600, 8, 64, 17, np.int32),      # by the number of nodes
+    (1, 65281, 4, 9, 3, np.int32),      # by the length
+    (257, 1023, 2, 8, 4, np.uint8),     # more samples than CUs: general kernel
+    (257, 1024, 2, 8, 4, np.uint8),     # packed
+    (1025, 1024, 8, 64, 3, np.uint8),   # more samples than fit at once: packed with the affinity, general for placement alone
     (512, 3, 2, 64, 4, np.uint8),       # loads in one workgroup
     (513, 3, 2, 64, 4, np.uint8),       # and in two launches
 ])
