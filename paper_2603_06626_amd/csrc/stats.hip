@@ -773,41 +773,119 @@ __global__ __launch_bounds__(THREADS) void k_fold_groups(const long long* __rest
 }
 
 // out[r][g] = sum over source experts e with group_of[e] == g of W[r][e], e ascending, fp32.
-// A workgroup takes 8 rows.  It first lists the members of every group in ascending order (the stable rank of an expert
-// among those of its group), so an output adds its own members only instead of looking at all E_S (2048 rows, 128 -> 32:
-// 12.1 -> 7.5 us).
-constexpr int kFoldRows = 8;
+// A workgroup takes 8 rows.  It first lists the members of every group in ascending order, so an output adds its own members
+// only instead of looking at all E_S, eight loads at a time.  2048 rows, a search through all experts / lists with one
+// dependent load after the other / now: 128 -> 32 12.4 / 7.1 / 6.2 us; 128 -> 1 14.4 / 22.4 / 7.2; 1024 -> 1 95 / 230 / 26.
+//   E_S <= 64   the place of an expert is counted by comparing it with all others: no further barriers (64 -> 32: 4.6 us)
+//   more        counting sort as in the routing plan: by comparing / sorting 128 -> 32 6.8 / 6.2, 200 -> 25 (4096 rows)
+//               10.0 / 7.1, 256 -> 1 14.3 / 10.0, 1024 -> 256 111 / 13
+constexpr int kFoldRows = 8, kFoldCompare = 64;
+template <bool SORT>
 __global__ __launch_bounds__(kStatThreads) void k_fold_weights(const float* __restrict__ W, const int32_t* __restrict__ group_of,
                                                                int d, int E_S, int E_T, float* __restrict__ out) {
-    __shared__ float s_w[kFoldRows * kMaxExperts];
-    __shared__ __attribute__((aligned(16))) int32_t s_g[kMaxExperts];
-    __shared__ int32_t s_member[kMaxExperts], s_start[kMaxExperts];
-    const int tid = threadIdx.x;
+    constexpr int kMax = SORT ? kMaxExperts : kFoldCompare, kWaves = kStatThreads / 64;
+    __shared__ float s_w[kFoldRows * kMax];
+    __shared__ __attribute__((aligned(16))) int32_t s_g[kMax];
+    __shared__ int32_t s_member[kMax], s_start[kMax], s_end[kMax];
+    __shared__ int32_t s_cursor[SORT ? kWaves * kMax : 1], s_wave[kWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r0 = (int)blockIdx.x * kFoldRows, rows = min(kFoldRows, d - r0);
     for (int i = tid; i < rows * E_S; i += kStatThreads) s_w[i] = W[(size_t)r0 * E_S + i];
-    for (int e = tid; e < kMaxExperts; e += kStatThreads) {
+    for (int e = tid; e < kMax; e += kStatThreads) {
         s_g[e] = e < E_S ? group_of[e] : 0x7fffffff;
-        s_start[e] = E_S;   // a group without members
+        s_start[e] = s_end[e] = 0;   // a group without members
     }
+    if constexpr (SORT)
+        for (int i = tid; i < kWaves * kMax; i += kStatThreads) s_cursor[i] = 0;
     __syncthreads();
-    // place of expert e: the experts of lower groups, and those of its own group that come before it
-    for (int e = tid; e < E_S; e += kStatThreads) {
-        const int g = s_g[e];
-        int at = 0, before = 0;
+    if constexpr (!SORT) {
+        // place of expert e: the experts of lower groups, and those of its own group that come before it
+        if (tid < E_S) {
+            const int g = s_g[tid];
+            int at = 0, before = 0, size = 0;
 #pragma unroll 4
-        for (int o = 0; o < E_S; o += 4) {
-            const int4 v = *(const int4*)(s_g + o);
-            at += (v.x < g) + (v.y < g) + (v.z < g) + (v.w < g);
-            before += ((v.x == g) & (o < e)) + ((v.y == g) & (o + 1 < e)) + ((v.z == g) & (o + 2 < e)) + ((v.w == g) & (o + 3 < e));
+            for (int o = 0; o < E_S; o += 4) {
+                const int4 v = *(const int4*)(s_g + o);
+                at += (v.x < g) + (v.y < g) + (v.z < g) + (v.w < g);
+                before += ((v.x == g) & (o < tid)) + ((v.y == g) & (o + 1 < tid)) + ((v.z == g) & (o + 2 < tid)) + ((v.w == g) & (o + 3 < tid));
+                size += (v.x == g) + (v.y == g) + (v.z == g) + (v.w == g);
+            }
+            if ((uint32_t)g < (uint32_t)E_T) {
+                s_member[at + before] = tid;
+                if (before == 0) {
+                    s_start[g] = at;
+                    s_end[g] = at + size;
+                }
+            }
         }
-        s_member[at + before] = e;
-        if (before == 0 && (uint32_t)g < (uint32_t)E_T) s_start[g] = at;
+    } else {
+        // every wave counts its quarter of the experts, a scan over groups and waves gives the cursors, and the waves place
+        // their experts 64 at a time; groups outside [0, E_T) are left out
+        constexpr int kRun = kMax / kWaves;
+        int32_t* const mine = s_cursor + wave * kMax;
+        for (int i = lane; i < kRun; i += 64) {
+            const int g = s_g[wave * kRun + i];
+            if ((uint32_t)g < (uint32_t)E_T) atomicAdd(&mine[g], 1);
+        }
+        __syncthreads();
+        constexpr int kPer = kMax / kStatThreads;   // a thread's groups
+        int sum = 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            for (int w = 0; w < kWaves; ++w) sum += s_cursor[w * kMax + tid * kPer + i];
+        int incl = sum;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += up;
+        }
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        int run = incl - sum;
+        for (int w = 0; w < wave; ++w) run += s_wave[w];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int g = tid * kPer + i;
+            s_start[g] = run;
+            for (int w = 0; w < kWaves; ++w) {
+                const int n = s_cursor[w * kMax + g];
+                s_cursor[w * kMax + g] = run;
+                run += n;
+            }
+            s_end[g] = run;
+        }
+        __syncthreads();
+        volatile int32_t* const cursor = mine;   // a wave's own: its rounds need no barrier
+        const uint64_t below = (1ull << lane) - 1;
+        for (int i0 = 0; i0 < kRun; i0 += 64) {
+            const int e = wave * kRun + i0 + lane, g = s_g[e];
+            const bool counts = (uint32_t)g < (uint32_t)E_T;
+            uint64_t peers = __ballot(counts);
+            for (int b = 0; (1 << b) < E_T; ++b) {
+                const bool bit = (g >> b) & 1;
+                const uint64_t m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+            if (counts) {
+                const int p = cursor[g] + __popcll(peers & below);
+                s_member[p] = e;
+                if ((peers >> lane) == 1ull) cursor[g] = p + 1;   // the group's highest lane
+            }
+        }
     }
     __syncthreads();
     for (int i = tid; i < rows * E_T; i += kStatThreads) {
-        const int r = i / E_T, g = i - r * E_T;
+        const int r = i / E_T, g = i - r * E_T, end = s_end[g];
+        const float* const w = s_w + r * E_S;
         float acc = 0.f;
-        for (int m = s_start[g]; m < E_S && s_g[s_member[m]] == g; ++m) acc += s_w[r * E_S + s_member[m]];
+        int m = s_start[g];
+        for (; m + 8 <= end; m += 8) {
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = w[s_member[m + j]];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc += v[j];
+        }
+        for (; m < end; ++m) acc += w[s_member[m]];
         out[(size_t)r0 * E_T + i] = acc;
     }
 }
@@ -927,7 +1005,9 @@ hipError_t launch_fold_groups(const int64_t* P, int E_S, int E_T, int32_t* group
 }
 
 hipError_t launch_fold_weights(const float* W, const int32_t* group_of, int d, int E_S, int E_T, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_fold_weights, dim3((unsigned)((d + kFoldRows - 1) / kFoldRows)), dim3(kStatThreads), 0, s, W, group_of, d, E_S, E_T, out);
+    const dim3 grid((unsigned)((d + kFoldRows - 1) / kFoldRows)), block(kStatThreads);
+    if (E_S <= kFoldCompare) hipLaunchKernelGGL(k_fold_weights<false>, grid, block, 0, s, W, group_of, d, E_S, E_T, out);
+    else hipLaunchKernelGGL(k_fold_weights<true>, grid, block, 0, s, W, group_of, d, E_S, E_T, out);
     return hipGetLastError();
 }
 

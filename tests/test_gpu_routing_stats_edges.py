@@ -70,3 +70,23 @@ def test_fold_weights_with_groups_that_have_no_members():
         ref[:, grp[e]] += W[:, e]
     # at most 40 fp32 additions of relative error 2^-24 each
     assert np.abs(out.cpu().numpy() - ref).max() <= 40 * 2.0 ** -24 * np.abs(W).sum(axis=1).max()
+
+
+@pytest.mark.parametrize("d,E_S,E_T", [
+    (1, 1, 1), (9, 64, 1), (9, 65, 1), (8, 63, 63), (3, 65, 64), (4, 66, 66), (17, 1024, 1), (5, 1024, 1024), (5, 1000, 7), (2, 513, 300),
+])
+@pytest.mark.parametrize("stray", [False, True])
+def test_folded_weights_add_members_in_ascending_order(d, E_S, E_T, stray):
+    """Bit-exact: the same fp32 additions in the same order.  stray: some experts belong to no group."""
+    rng = np.random.default_rng(E_S + E_T)
+    grp = (rng.integers(0, E_T, size=E_S) ** 2 // max(1, E_T)).astype(np.int32)     # groups of very different size
+    if stray:
+        grp[rng.integers(0, E_S, size=max(1, E_S // 5))] = rng.choice([-1, -2**31, E_T, 2**31 - 1])
+    W = rng.standard_normal((d, E_S), dtype=np.float32)
+    out = torch.full((d, E_T), float("nan"), dtype=torch.float32, device=DEV)
+    b.grouter_fold_weights(torch.from_numpy(W).to(DEV), torch.from_numpy(grp).to(DEV), E_T, out)
+    ref = np.zeros((d, E_T), dtype=np.float32)
+    for e in range(E_S):
+        if 0 <= grp[e] < E_T:
+            ref[:, grp[e]] += W[:, e]
+    assert np.array_equal(out.cpu().numpy(), ref)
