@@ -24,18 +24,25 @@ static unsigned rows_grid(const PlanView& P, int n_ntiles) { return (unsigned)P.
 // second pass over the weights (the first shape at T = 100: 33 -> 35 us).
 // Stages: with K of at most one block per wave a second stage would only load zeros (d = 256, f = 576, E = 128, k = 7,
 // T = 16: 28.5 -> 25.1 us); otherwise two stages are up to 1 % faster.
+// Order: runs of ceil(blocks / 8) column blocks per XCD are even where the blocks come in eights, and then 3 to 6 % faster than
+// the plain order (d = 4096, f = 1536, E = 128, k = 8, T = 12: gate/up 314 / 331 us, down 149 / 159).  Otherwise some XCDs get less
+// or nothing (runs / plain): 12 blocks, d = 2048, f = 768, E = 128, k = 8, T = 6 gate/up 60.6 / 47.7 us; 22 blocks, d = 2048,
+// f = 1408, E = 64, k = 6, T = 12 101 / 91; 4 blocks, d = f = 256, E = 48, k = 2, T = 32 12.1 / 8.6; 2 and 4 blocks, d = 128, f = 256,
+// E = 128, k = 1, T = 48 the layer 20.2 / 14.7 (19 with the 128-row tiles).
 // By expert: with rows of 592 bytes (d = 704, f = 296, E = 64, k = 5, T = 10), where neighbouring column blocks share lines,
 // three layers take 121 us with an expert's blocks spread over the XCDs and 87 us on one.
 constexpr int64_t kStreamTiles = 128;
 template <int MODE>
-static bool launch_stream(const PlanView& P, RowsArgs a, hipStream_t s) {
+static bool launch_stream(const PlanView& P, const RowsArgs& rows, hipStream_t s) {
     constexpr int kCpl = 4, kWaves = 8;
     const int64_t tiles = P.max_tiles_small < P.N ? P.max_tiles_small : P.N;   // no tile is empty
     const bool few_rows = P.T <= kStreamRows;
-    if (!few_rows && (P.T > 4 * kStreamRows || tiles * a.n_ntiles > kStreamTiles)) return false;
+    if (!few_rows && (P.T > 4 * kStreamRows || tiles * rows.n_ntiles > kStreamTiles)) return false;
+    StreamArgs a{rows, kStreamPlain};
     a.n_ntiles = (a.Ncols + 16 * kCpl - 1) / (16 * kCpl);
-    a.col_group = a.Ncols % 64 != 0 && tiles >= 32;   // 64 columns are a line; with fewer experts some XCDs would idle
-    const dim3 grid((unsigned)(a.col_group ? (tiles + 7) / 8 * 8 * a.n_ntiles : tiles * ((a.n_ntiles + 7) / 8 * 8))), block(kWaves * 64);
+    if (a.Ncols % 64 != 0) a.order = tiles >= 32 ? kStreamByExpert : kStreamRuns;   // 64 columns are a line; with fewer experts some XCDs would idle
+    else if (a.n_ntiles % 8 == 0) a.order = kStreamRuns;
+    const dim3 grid((unsigned)stream_grid(a.order, (int)tiles, a.n_ntiles)), block(kWaves * 64);
     if (few_rows && a.K <= 32 * kWaves) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 1, 1>), grid, block, 0, s, a);
     else if (few_rows) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 2, 1>), grid, block, 0, s, a);
     else if (P.T <= 2 * kStreamRows) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 2, 2>), grid, block, 0, s, a);

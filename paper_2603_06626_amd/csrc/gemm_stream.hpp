@@ -25,9 +25,13 @@ namespace grouter {
 
 enum StreamMode { kStreamGateUp = 0, kStreamGateUpOnly = 1, kStreamDown = 2 };
 
+struct StreamArgs : RowsArgs {
+    StreamOrder order;   // of the workgroups; the column blocks of n_ntiles are 64 wide
+};
+
 // RB: row blocks of 16 that share one pass over the weights
 template <int MODE, int CPL, int W, int STAGES, int RB>
-__global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stream_gemm(const RowsArgs a) {
+__global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stream_gemm(const StreamArgs a) {
     constexpr bool GATEUP = MODE != kStreamDown;
     constexpr int NB = GATEUP ? 2 : 1;
     constexpr int kCols = 16 * CPL;
@@ -39,7 +43,7 @@ __global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stre
     typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
     i32x8 rec;
     StreamTile tile;
-    if (!tile.pick((int)blockIdx.x, a.n_ntiles, a.col_group != 0, [&]() { return a.plan.row_tiles(); },
+    if (!tile.pick((int)blockIdx.x, a.n_ntiles, a.order, [&]() { return a.plan.row_tiles(); },
                    [&](int mt) { rec = *(const i32x8*)(a.tiles + 8 * (size_t)mt); }))
         return;
     const int col0 = tile.cb * kCols;

@@ -10,26 +10,40 @@
 
 namespace grouter {
 
-// Workgroup -> (row tile mt, column block cb).
-// Workgroups of one expert: the 8 XCDs take one contiguous run of column blocks each, so a line that two blocks share is
-// fetched by one L2.  Where rows do not begin on a line, every block shares its first and last line with its neighbours:
-// given enough experts, one XCD then takes all blocks of an expert (by_expert).
+// Workgroup -> (row tile mt, column block cb).  Consecutive workgroups go to the 8 XCDs in turn, each with its own L2.
+//   kStreamPlain     block after block: the XCDs share the work evenly.  For rows that begin on a 128-byte line, where no two
+//                    blocks share a line.
+//   kStreamRuns      the XCDs take one contiguous run of an expert's column blocks each, so a line that two blocks share is
+//                    mostly fetched by one L2
+//   kStreamByExpert  one XCD takes all blocks of an expert
+enum StreamOrder { kStreamPlain = 0, kStreamRuns = 1, kStreamByExpert = 2 };
+
+// Workgroups that cover max_tiles row tiles.
+GROUTER_HOST_DEVICE int stream_grid(StreamOrder order, int max_tiles, int n_col_blocks) {
+    if (order == kStreamPlain) return max_tiles * n_col_blocks;
+    if (order == kStreamRuns) return max_tiles * ((n_col_blocks + 7) / 8 * 8);
+    return (max_tiles + 7) / 8 * 8 * n_col_blocks;
+}
+
 // n_tiles() loads the plan header and gives the number of row tiles, negative for a plan of other dimensions; record(mt) loads
 // the record of tile mt.  The record is loaded only after the header has vouched for it: a plan of other
 // dimensions may be a smaller allocation that ends before the place where the caller's dimensions put the record.
 struct StreamTile {
     int mt, cb;
     template <class NTiles, class Record>
-    GROUTER_HOST_DEVICE bool pick(int block, int n_col_blocks, bool by_expert, NTiles n_tiles, Record record) {
-        if (by_expert) {
-            const int q = block >> 3;
-            mt = q / n_col_blocks * 8 + (block & 7);
-            cb = q % n_col_blocks;
-        } else {
+    GROUTER_HOST_DEVICE bool pick(int block, int n_col_blocks, StreamOrder order, NTiles n_tiles, Record record) {
+        if (order == kStreamPlain) {
+            mt = block / n_col_blocks;
+            cb = block - mt * n_col_blocks;
+        } else if (order == kStreamRuns) {
             const int per_xcd = (n_col_blocks + 7) >> 3;
             mt = block / (per_xcd * 8);
             const int b = block - mt * per_xcd * 8;
             cb = (b & 7) * per_xcd + (b >> 3);
+        } else {
+            const int q = block >> 3;
+            mt = q / n_col_blocks * 8 + (block & 7);
+            cb = q % n_col_blocks;
         }
         if (mt >= n_tiles() || cb >= n_col_blocks) return false;
         record(mt);

@@ -64,15 +64,15 @@ using namespace grouter;
 int main() {
     for (int bound = 1; bound <= 40; ++bound)              // row tiles the launch allows for
         for (int ncb = 1; ncb <= 20; ++ncb)
-            for (int by_expert = 0; by_expert < 2; ++by_expert) {
-                const int grid = by_expert ? (bound + 7) / 8 * 8 * ncb : bound * ((ncb + 7) / 8 * 8);
+            for (const StreamOrder order : {kStreamPlain, kStreamRuns, kStreamByExpert}) {
+                const int grid = stream_grid(order, bound, ncb);
                 for (int n = -1; n <= bound; ++n) {        // row tiles the plan header names; -1: a plan of other dimensions
                     std::vector<int> taken(bound * ncb, 0);
                     for (int block = 0; block < grid; ++block) {
                         bool vouched = false;
                         int read = -1;
                         StreamTile t;
-                        const bool ok = t.pick(block, ncb, by_expert, [&]() { vouched = true; return n; },
+                        const bool ok = t.pick(block, ncb, order, [&]() { vouched = true; return n; },
                                                [&](int mt) { if (!vouched || mt < 0 || mt >= n) read = -2; else if (read == -1) read = mt; });
                         if (read == -2 || (n < 0 && ok) || (ok && read != t.mt))
                             return std::printf("bound %d, %d column blocks, %d tiles: workgroup %d reads a record nobody vouched for\n", bound, ncb, n, block), 1;
