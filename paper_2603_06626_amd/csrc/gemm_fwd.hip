@@ -18,12 +18,17 @@ static unsigned rows_grid(const PlanView& P, int n_ntiles) { return (unsigned)P.
 
 // When the streaming kernels take over.  Up to 16 tokens no expert holds more than 16 rows (unless a token names it twice)
 // and they read the weights once at full width.  From 17 to 64 tokens they still read them once, with 2 or 4 row
-// blocks, which pays where the 128-row tiles are too few to occupy the chip: d = 568, f = 1088, E = 8, k = 2 (72 and 24
-// tiles), T = 20: 31.5 -> 19.9 us a layer, T = 64: 32.1 -> 24.4; d = f = 1024, E = 16, k = 2 (128 and 64 tiles): 47.2 -> 29.0
-// and 47.6 -> 41.1.  With more tiles they lose (d = 2048, f = 1408, E = 64, k = 6, T = 64: 195 -> 219 us), and so does a
-// second pass over the weights (the first shape at T = 100: 33 -> 35 us).
+// blocks, which pays where the 128-row tiles are too few to occupy the chip.  Measured, time of the 128-row tiles over the
+// streaming kernels' by number of tiles (128 columns for gate/up, 256 for down):
+//   17 to 32 tokens   gate/up 64 to 126 tiles 1.35-1.64, 135 to 200 0.84-1.08, 230 to 310 0.95-1.11; down to 126 1.2-1.9, 140 to 200
+//                     1.0-1.2, 220 to 450 0.85-1.0
+//   33 to 64 tokens   gate/up 64 to 128 1.27-1.50, 130 to 190 0.88-1.0; down to 128 1.05-1.8 (but 0.94 with K = 256), 130 to 140
+//                     0.82-0.97, 180 to 510 0.65-0.92
+// and a second pass over the weights loses (d = 568, f = 1088, E = 8, k = 2, T = 100: 33 -> 35 us).
 // Stages: with K of at most one block per wave a second stage would only load zeros (d = 256, f = 576, E = 128, k = 7,
-// T = 16: 28.5 -> 25.1 us); otherwise two stages are up to 1 % faster.
+// T = 16: 28.5 -> 25.1 us).  With more workgroups than CUs one stage lets two share a CU, which pays as long as a wave has few
+// blocks (two stages / one: K = 768 gate/up 45 / 39 us and down 39 / 36.5, K = 1024 gate/up 27.5 / 26.5; but K = 1000 down 27.9 / 28.3,
+// K = 3072 gate/up 67 / 67); where every CU has a workgroup at most, two stages are 3 to 10 % faster.
 // Order: runs of ceil(blocks / 8) column blocks per XCD are even where the blocks come in eights, and then 3 to 6 % faster than
 // the plain order (d = 4096, f = 1536, E = 128, k = 8, T = 12: gate/up 314 / 331 us, down 149 / 159).  Otherwise some XCDs get less
 // or nothing (runs / plain): 12 blocks, d = 2048, f = 768, E = 128, k = 8, T = 6 gate/up 60.6 / 47.7 us; 22 blocks, d = 2048,
@@ -32,18 +37,35 @@ static unsigned rows_grid(const PlanView& P, int n_ntiles) { return (unsigned)P.
 // By expert: with rows of 592 bytes (d = 704, f = 296, E = 64, k = 5, T = 10), where neighbouring column blocks share lines,
 // three layers take 121 us with an expert's blocks spread over the XCDs and 87 us on one.
 constexpr int64_t kStreamTiles = 128;
+
+// Up to 16 tokens the streaming kernels lose where the 128-row tiles number 160 to 256, that is one workgroup on nearly every
+// CU and no second round, while the streaming ones take two rounds: gate/up with K = 3072 or 4096 0.91-0.96 of the
+// tiles' speed, and with rows that do not begin on a line (d = 1928, f = 1000) 0.88-0.92; otherwise 0.94-1.2.  Down
+// with K > 768 (two stages) and 192 tiles or more 0.87-0.97.  Beyond 256 tiles they are as fast or faster again (T = 12,
+// d = 1928, f = 1000, E = 60, k = 5: 113 -> 105 us a layer).  The host does not know how many experts the tokens pick; this is the
+// number expected of evenly spread picks.  Skewed picks touch fewer: the same layer with Zipf loads has 216 tiles where 311 are
+// expected and takes 80 us instead of 73.
+static bool tiles_fill_one_round(const PlanView& P, const RowsArgs& a, bool down) {
+    double missed = 1.0;
+    for (int64_t t = 0; t < P.T; ++t) missed *= 1.0 - (double)P.k / P.E;
+    const double tiles = P.E * (1.0 - missed) * a.n_ntiles;
+    if (tiles > 256.0) return false;
+    return down ? a.K > 768 && tiles >= 192.0 : (a.K >= 3072 || a.Ncols % 64 != 0) && tiles > 160.0;
+}
+
 template <int MODE>
 static bool launch_stream(const PlanView& P, const RowsArgs& rows, hipStream_t s) {
     constexpr int kCpl = 4, kWaves = 8;
     const int64_t tiles = P.max_tiles_small < P.N ? P.max_tiles_small : P.N;   // no tile is empty
     const bool few_rows = P.T <= kStreamRows;
-    if (!few_rows && (P.T > 4 * kStreamRows || tiles * rows.n_ntiles > kStreamTiles)) return false;
+    if (few_rows ? tiles_fill_one_round(P, rows, MODE == kStreamDown) : P.T > 4 * kStreamRows || tiles * rows.n_ntiles > kStreamTiles) return false;
     StreamArgs a{rows, kStreamPlain};
     a.n_ntiles = (a.Ncols + 16 * kCpl - 1) / (16 * kCpl);
     if (a.Ncols % 64 != 0) a.order = tiles >= 32 ? kStreamByExpert : kStreamRuns;   // 64 columns are a line; with fewer experts some XCDs would idle
     else if (a.n_ntiles % 8 == 0) a.order = kStreamRuns;
+    const bool one_stage = a.K <= 32 * kWaves || (tiles * a.n_ntiles > 256 && a.K <= (MODE == kStreamDown ? 768 : 1024));
     const dim3 grid((unsigned)stream_grid(a.order, (int)tiles, a.n_ntiles)), block(kWaves * 64);
-    if (few_rows && a.K <= 32 * kWaves) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 1, 1>), grid, block, 0, s, a);
+    if (few_rows && one_stage) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 1, 1>), grid, block, 0, s, a);
     else if (few_rows) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 2, 1>), grid, block, 0, s, a);
     else if (P.T <= 2 * kStreamRows) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 2, 2>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, MODE == kStreamDown ? 2 : 1, 4>), grid, block, 0, s, a);

@@ -31,6 +31,15 @@ TOL = 1e-2
     (12, 72, 136, 40, 3, False),    # rows that begin inside a line and 32 tiles or more: one XCD per expert
     (16, 200, 264, 64, 4, False),   # the same with five column blocks
     (20, 1032, 1032, 64, 4, False), # more than 16 tokens on many experts: tiled
+    (16, 72, 72, 250, 16, False),   # about 163 row tiles on rows that begin inside a line: tiled up to 16 tokens, too
+    (13, 72, 72, 250, 16, False),   # about 144: streamed
+    (3, 3072, 72, 100, 30, False),  # 66 tiles of gate/up (K = 3072) and 788 of down: both streamed
+    (9, 3072, 64, 190, 40, False),  # 168 tiles of gate/up on 3072 rows of weights: tiled; down streamed
+    (12, 256, 776, 240, 30, False), # about 192 tiles of down: tiled with K > 768
+    (12, 256, 768, 240, 30, False), # the same with K = 768: streamed
+    (5, 1024, 256, 70, 20, False),  # more workgroups than CUs, K = 1024: one stage
+    (5, 1032, 256, 70, 20, False),  # K = 1032: two
+    (8, 704, 512, 8, 2, False),     # 11 column blocks in plain order, 8 in runs
 ])
 def test_few_tokens_match_the_oracle(T, d, f, E, k, repeat):
     if not torch.cuda.is_available():
