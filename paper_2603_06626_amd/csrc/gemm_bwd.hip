@@ -9,7 +9,6 @@ namespace grouter {
 static RowsArgs rows_args(const PlanView& P) {
     RowsArgs a{};
     a.tiles = P.tiles_small;
-    a.max_tiles = P.max_tiles_small;
     a.plan = P.dims();
     return a;
 }

@@ -8,7 +8,6 @@ namespace grouter {
 static RowsArgs base_args(const PlanView& P) {
     RowsArgs a{};
     a.tiles = P.tiles_small;
-    a.max_tiles = P.max_tiles_small;
     a.plan = P.dims();
     a.col_group = 3;  // measured best of 0 (plain order), 1, 2, 3 on the forward GEMMs
     return a;
@@ -55,20 +54,20 @@ static bool tiles_fill_one_round(const PlanView& P, const RowsArgs& a, bool down
 
 template <int MODE>
 static bool launch_stream(const PlanView& P, const RowsArgs& rows, hipStream_t s) {
-    constexpr int kCpl = 4, kWaves = 8;
+    constexpr int kWaves = 8;
     const int64_t tiles = P.max_tiles_small < P.N ? P.max_tiles_small : P.N;   // no tile is empty
     const bool few_rows = P.T <= kStreamRows;
     if (few_rows ? tiles_fill_one_round(P, rows, MODE == kStreamDown) : P.T > 4 * kStreamRows || tiles * rows.n_ntiles > kStreamTiles) return false;
     StreamArgs a{rows, kStreamPlain};
-    a.n_ntiles = (a.Ncols + 16 * kCpl - 1) / (16 * kCpl);
-    if (a.Ncols % 64 != 0) a.order = tiles >= 32 ? kStreamByExpert : kStreamRuns;   // 64 columns are a line; with fewer experts some XCDs would idle
+    a.n_ntiles = (a.Ncols + kStreamCols - 1) / kStreamCols;
+    if (a.Ncols % kStreamCols != 0) a.order = tiles >= 32 ? kStreamByExpert : kStreamRuns;   // a block is as wide as a line; with fewer experts some XCDs would idle
     else if (a.n_ntiles % 8 == 0) a.order = kStreamRuns;
     const bool one_stage = a.K <= 32 * kWaves || (tiles * a.n_ntiles > 256 && a.K <= (MODE == kStreamDown ? 768 : 1024));
     const dim3 grid((unsigned)stream_grid(a.order, (int)tiles, a.n_ntiles)), block(kWaves * 64);
-    if (few_rows && one_stage) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 1, 1>), grid, block, 0, s, a);
-    else if (few_rows) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 2, 1>), grid, block, 0, s, a);
-    else if (P.T <= 2 * kStreamRows) hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, 2, 2>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_stream_gemm<MODE, kCpl, kWaves, MODE == kStreamDown ? 2 : 1, 4>), grid, block, 0, s, a);
+    if (few_rows && one_stage) hipLaunchKernelGGL((k_stream_gemm<MODE, kWaves, 1, 1>), grid, block, 0, s, a);
+    else if (few_rows) hipLaunchKernelGGL((k_stream_gemm<MODE, kWaves, 2, 1>), grid, block, 0, s, a);
+    else if (P.T <= 2 * kStreamRows) hipLaunchKernelGGL((k_stream_gemm<MODE, kWaves, 2, 2>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_stream_gemm<MODE, kWaves, MODE == kStreamDown ? 2 : 1, 4>), grid, block, 0, s, a);
     return true;
 }
 

@@ -35,7 +35,6 @@ __device__ __forceinline__ void write_tile(char* smem, int tid, bf16_t* dst, siz
 
 struct RowsArgs {
     const int32_t* tiles;        // [max_tiles][8]: expert, the expert's first row, row count, first tile, tile count
-    int max_tiles;
     PlanDims plan;               // header[1] = number of row tiles actually present
     const bf16_t* A0; const bf16_t* A1;   // [Nrows][K]
     const bf16_t* B0; const bf16_t* B1;   // [E] slabs of K*Ncols elements
@@ -587,26 +586,25 @@ struct DwArgs {
     uint32_t gathered_bytes;     // size of the token-ordered matrix the gathered operand is read from
 };
 
-// GATHER: 0 = both operands lie in expert-sorted row order; 1 = A, 2 = B (NB == 1) is instead read from a
-// token-ordered matrix [T][.] through row_token, so the expert-sorted copy of that matrix need not exist.
+// One operand, x (A, for NB == 2) or dY (B, for NB == 1), is read from a token-ordered matrix [T][.] through row_token, so
+// the expert-sorted copy of that matrix need not exist; the other lies in expert-sorted row order.
 // Rows are the reduction dimension here, so a lane's copy offsets change every step: each wave keeps the
 // token ids of the next steps' 32 rows in a small LDS ring, filled by one more direct copy per step four
 // steps ahead (by then certainly landed: the step's wait leaves only the previous step's copies outstanding).
 // Past the expert's last row the ids read as token 0; the other operand is zero there, so nothing is added.
-enum DwGather { kGatherNone = 0, kGatherA = 1, kGatherB = 2 };
 constexpr int kIdRingAt = 24 * 1024;  // between the A slots (3 x 8 KB) and the B slots (from 32 KB)
 
 // AHEAD: the step loop that keeps the next step's fragments in registers, for long reductions (see step_pipeline_ahead).
-template <int NB, int GATHER, bool AHEAD>
+template <int NB, bool AHEAD>
 __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) {
-    static_assert(GATHER != kGatherB || NB == 1, "a gathered B operand is only provided for one B");
-    constexpr int kStepCopies = GATHER == kGatherNone ? 6 : 7;
+    constexpr bool GATHER_A = NB == 2;
+    constexpr int kStepCopies = 7;   // A tile 2, B tile(s) 4, token ids 1
     constexpr int BN = (NB == 2) ? 128 : 256;
     constexpr int FN = BN / 128;
     constexpr int kBHalf = kBTileBytes / 2;
     using ATile = McTile<128>;
     using BTile = McTile<BN>;
-    static_assert(ATile::kPasses == 2 && NB * BTile::kPasses == 4, "six copies per thread and step");
+    static_assert(ATile::kPasses == 2 && NB * BTile::kPasses == 4, "six tile copies per thread and step");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t wave_base = __builtin_amdgcn_readfirstlane((uint32_t)wave * 1024u);
@@ -640,10 +638,10 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
     const int Mdim = a.Mdim, Ndim = a.Ndim;
 
     // The buffers cover exactly the expert's rows, so the last step reads zeros past the expert's end.
-    const i32x4 bufA = GATHER == kGatherA ? make_buffer(a.A, a.gathered_bytes)
-                                          : make_buffer(a.A + (size_t)off * Mdim, (uint32_t)cnt * (uint32_t)Mdim * 2u);
-    const i32x4 bufB0 = GATHER == kGatherB ? make_buffer(a.B0, a.gathered_bytes)
-                                           : make_buffer(a.B0 + (size_t)off * Ndim, (uint32_t)cnt * (uint32_t)Ndim * 2u);
+    const i32x4 bufA = GATHER_A ? make_buffer(a.A, a.gathered_bytes)
+                                : make_buffer(a.A + (size_t)off * Mdim, (uint32_t)cnt * (uint32_t)Mdim * 2u);
+    const i32x4 bufB0 = !GATHER_A ? make_buffer(a.B0, a.gathered_bytes)
+                                  : make_buffer(a.B0 + (size_t)off * Ndim, (uint32_t)cnt * (uint32_t)Ndim * 2u);
     const i32x4 bufB1 = NB == 2 ? make_buffer(a.B1 + (size_t)off * Ndim, (uint32_t)cnt * (uint32_t)Ndim * 2u) : bufB0;
     int a_col[2], b_col[BTile::kPasses];   // the piece a lane copies depends on the K-row, hence on the pass
     uint32_t a_voff[2], b_voff[BTile::kPasses];
@@ -659,7 +657,7 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
     }
 
     // token ids of the expert's rows, for the gathered operand
-    const i32x4 bufTok = make_buffer(GATHER != kGatherNone ? a.row_token + off : nullptr, (uint32_t)cnt * 4u);
+    const i32x4 bufTok = make_buffer(a.row_token + off, (uint32_t)cnt * 4u);
     const uint32_t id_ring = smem_addr + kIdRingAt + __builtin_amdgcn_readfirstlane((uint32_t)wave * 128u);
     auto issue_ids = [&](int step) {  // rows 32*step .. 32*step+31 -> this wave's ring slot step % 8
         uint32_t dst = id_ring + (uint32_t)(step & 7) * 512u;
@@ -673,27 +671,25 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
     // The ids a thread needs for the copies of one step (one per pass of the gathered operand) are read from the
     // ring at the start of the step that issues those copies, together with the step's fragment reads, so the
     // copies in the middle of the MFMA stream find them in registers.
-    constexpr int kGatherPasses = GATHER == kGatherA ? 2 : (GATHER == kGatherB ? BTile::kPasses : 1);
+    constexpr int kGatherPasses = GATHER_A ? 2 : BTile::kPasses;
     int32_t tok[kGatherPasses] = {};
     constexpr int kPrologue = AHEAD ? 3 : 2;   // steps whose copies the prologue issues
     int next_issue = kPrologue;                // the step whose copies the next step of the loop issues
     auto load_ids = [&](int step) {
 #pragma unroll
         for (int p = 0; p < kGatherPasses; ++p)
-            tok[p] = token_of(step, GATHER == kGatherA ? ATile::krow_of(tid, p) : BTile::krow_of(tid, p));
+            tok[p] = token_of(step, GATHER_A ? ATile::krow_of(tid, p) : BTile::krow_of(tid, p));
     };
     auto issue_a = [&](int, int, uint32_t = 0u) {};
     auto issue_b = [&](int step, auto slot_c, uint32_t dead = 0u) {  // per-step copies: the A tile (2), the B tile(s) (4), and the ids
         constexpr int slot = decltype(slot_c)::value;
-        if constexpr (GATHER != kGatherNone) {
-            if (step < kPrologue) load_ids(step);   // later steps were read ahead
-        }
+        if (step < kPrologue) load_ids(step);   // later steps were read ahead
         const uint32_t k0 = dead ? 0u : (uint32_t)step * 32u;
         const uint32_t a_dst = smem_addr + slot * kMcSmallBytes + wave_base;
         const uint32_t b_dst = smem_addr + kBRegion + slot * kBTileBytes + wave_base;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            if constexpr (GATHER == kGatherA) {
+            if constexpr (GATHER_A) {
                 const uint32_t row = (uint32_t)tok[p] * (uint32_t)Mdim;
                 async_copy16(bufA, a_col[p] < Mdim ? ((row + a_col[p]) * 2u) | dead : kOutOfRange, 0u, a_dst + ATile::pass_offset(p));
             } else {
@@ -704,7 +700,7 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int p = 0; p < BTile::kPasses; ++p) {
-                if constexpr (GATHER == kGatherB) {
+                if constexpr (!GATHER_A) {
                     const uint32_t row = (uint32_t)tok[p] * (uint32_t)Ndim;
                     async_copy16(bufB0, b_col[p] < Ndim ? ((row + b_col[p]) * 2u) | dead : kOutOfRange, 0u, b_dst + BTile::pass_offset(p));
                 } else {
@@ -712,13 +708,11 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
                                  b_dst + nb * kBHalf + BTile::pass_offset(p));
                 }
             }
-        if constexpr (GATHER != kGatherNone) issue_ids(step + 4);
+        issue_ids(step + 4);
     };
-    if constexpr (GATHER != kGatherNone) {
 #pragma unroll
-        for (int s0 = 0; s0 < 4; ++s0) issue_ids(s0);
-        wait_async_copies<0>();
-    }
+    for (int s0 = 0; s0 < 4; ++s0) issue_ids(s0);
+    wait_async_copies<0>();
 
     Acc32 acc[NB][4][FN];
 #pragma unroll
@@ -761,13 +755,13 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
             constexpr int slot = decltype(slot_c)::value, half = decltype(half_c)::value;
             arrive();
             read(fr[half ^ 1], (slot + 1) % 3);
-            if constexpr (GATHER != kGatherNone) load_ids(next_issue++);
+            load_ids(next_issue++);
             multiply(fr[half], issue);
         };
         step_pipeline_ahead<false, kStepCopies>(n_steps, issue_a, issue_b, [&]() { read(fr[0], 0); }, step);
     } else {
         auto compute_rt = [&](int slot, int, int, auto issue) {
-            if constexpr (GATHER != kGatherNone) load_ids(next_issue++);
+            load_ids(next_issue++);
             Frags fr;
             read(fr, slot);
             multiply(fr, issue);
@@ -775,7 +769,7 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, int block, char* smem) 
         auto compute = [&](auto slot_c, auto, int, auto issue) { compute_rt(decltype(slot_c)::value, 0, 0, issue); };
         step_pipeline<false, kStepCopies>(n_steps, issue_a, issue_b, compute, compute_rt);
     }
-    if constexpr (GATHER != kGatherNone) wait_async_copies<0>();  // id copies of steps that do not exist
+    wait_async_copies<0>();  // id copies of steps that do not exist
 
     const int rows_valid = min(kTileM, Mdim - m0);
     const int cols_valid = min(BN, Ndim - n0);
@@ -806,8 +800,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_bwd_pair(const DwArgs w, const 
     // weight-gradient tiles are numbered 0 .. n_dw - 1, row tiles from n_dw on
     const int block = __builtin_amdgcn_readfirstlane(b < head ? b : b < head + n_rows ? b - head + n_dw : b - n_rows);
     if (block < n_dw) {
-        if constexpr (MODE == kDh) dw_tile<1, kGatherB, AHEAD>(w, block, smem);
-        else dw_tile<2, kGatherA, AHEAD>(w, block, smem);
+        if constexpr (MODE == kDh) dw_tile<1, AHEAD>(w, block, smem);
+        else dw_tile<2, AHEAD>(w, block, smem);
     } else {
         bwd_rows_tile<MODE>(r, block - n_dw, smem);
     }

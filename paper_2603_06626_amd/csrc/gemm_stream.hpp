@@ -5,11 +5,11 @@
 // The 128-row tiles do not manage that: for one token they are 66 workgroups that walk the whole of K in steps of 32
 // rows, each step waiting for LDS copies and a barrier.
 //
-// Here a workgroup owns 16 CPL columns of one expert and its waves share out K: wave w takes every W-th block of 32 K-rows
+// Here a workgroup owns 64 columns of one expert and its waves share out K: wave w takes every W-th block of 32 K-rows
 // and has STAGES of them in flight.  Weights go straight from memory to registers, with no LDS and no barrier in the
-// loop.  A lane loads CPL columns of 8 K-rows and turns them into MFMA operands with one v_perm per two elements: the K-rows
-// 8 (l / 16) .. + 7 of column CPL (l % 16) + j are the 8 consecutive K values per lane that the 16x16x32 operand of block
-// j wants, if block j is taken to be the columns CPL c + j.  A lane of the accumulators then holds 4 CPL consecutive columns
+// loop.  A lane loads 4 columns of 8 K-rows and turns them into MFMA operands with one v_perm per two elements: the K-rows
+// 8 (l / 16) .. + 7 of column 4 (l % 16) + j are the 8 consecutive K values per lane that the 16x16x32 operand of block
+// j wants, if block j is taken to be the columns 4 c + j.  A lane of the accumulators then holds 16 consecutive columns
 // of one row.  The activations' operand (RB blocks of 16 rows, 8 consecutive K per lane) is loaded directly, too.  At the end the waves'
 // partial sums meet in LDS and are added in wave order, so results do not depend on timing.
 //
@@ -30,14 +30,13 @@ struct StreamArgs : RowsArgs {
 };
 
 // RB: row blocks of 16 that share one pass over the weights
-template <int MODE, int CPL, int W, int STAGES, int RB>
+template <int MODE, int W, int STAGES, int RB>
 __global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stream_gemm(const StreamArgs a) {
     constexpr bool GATEUP = MODE != kStreamDown;
     constexpr int NB = GATEUP ? 2 : 1;
-    constexpr int kCols = 16 * CPL;
-    constexpr int DW = CPL / 2;                                // dwords a lane loads per K-row
+    constexpr int CPL = kStreamCols / 16, kCols = kStreamCols;
     using Sums = StreamSums<NB, kCols>;
-    static_assert(CPL == 2 || CPL == 4, "columns per lane");
+    static_assert(CPL == 4, "8 bytes of every K-row per lane");
     __shared__ __attribute__((aligned(16))) char smem[W * Sums::kWaveBytes];
 
     typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
@@ -70,7 +69,7 @@ __global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stre
     for (int r0 = 0; r0 < tile_rows; r0 += kStreamRows * RB) {
         const int rows = min(kStreamRows * RB, tile_rows - r0);
         struct Block {
-            uint32_t b[NB][8][DW];
+            uint32_t b[NB][8][2];   // not register pairs: those spill with one stage
             u32x4 a[RB];
         };
         Block st[STAGES];
@@ -82,13 +81,9 @@ __global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stre
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    if constexpr (CPL == 4) {
-                        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(bufB[nb], (int)voff, (int)(soff + i * row_b), 0);
-                        s.b[nb][i][0] = v.x;
-                        s.b[nb][i][DW - 1] = v.y;
-                    } else {
-                        s.b[nb][i][0] = __builtin_amdgcn_raw_buffer_load_b32(bufB[nb], (int)voff, (int)(soff + i * row_b), 0);
-                    }
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(bufB[nb], (int)voff, (int)(soff + i * row_b), 0);
+                    s.b[nb][i][0] = v.x;
+                    s.b[nb][i][1] = v.y;
                 }
         };
 #pragma unroll
@@ -147,7 +142,7 @@ __global__ __launch_bounds__(W * 64, RB == 1 && STAGES == 1 ? 4 : 2) void k_stre
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int h = 0; h < CPL; ++h) {   // columns 4 h .. + 3 of this lane's 4 CPL
+                for (int h = 0; h < CPL; ++h) {   // columns 4 h .. + 3 of this lane's 16
                     f32x4 v;
 #pragma unroll
                     for (int c = 0; c < 4; ++c) v[c] = acc[rb][nb][(4 * h + c) % CPL][(4 * h + c) / CPL];

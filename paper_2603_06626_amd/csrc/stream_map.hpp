@@ -52,6 +52,7 @@ struct StreamTile {
 };
 
 constexpr int kStreamRows = 16;   // rows of one MFMA, and of one round of partial sums
+constexpr int kStreamCols = 64;   // columns of a workgroup
 
 // Partial sums of 16 rows x NB * COLS columns, fp32, one area per wave.
 template <int NB, int COLS>

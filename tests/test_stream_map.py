@@ -14,7 +14,7 @@ using namespace grouter;
 // every form of the kernel: NB weight matrices, RB row blocks; 8 waves, 64 columns a workgroup
 template <int NB, int RB>
 int check() {
-    constexpr int W = 8, COLS = 64;
+    constexpr int W = 8, COLS = kStreamCols;
     using Sums = StreamSums<NB, COLS>;
     for (int rows = 1; rows <= 16 * RB; ++rows)
         for (int cols = 8; cols <= 72; cols += 8) {        // columns from the workgroup's first one to the matrix's end
