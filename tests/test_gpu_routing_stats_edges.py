@@ -46,16 +46,56 @@ def test_statistics_at_the_edges_of_their_kernels(S, L, k, E, n_nodes, dtype):
     check_all(idx, E, [perm[n::n_nodes] for n in range(n_nodes)], E_T_list=(max(1, E // 5),), label=f"{S}x{L}x{k} E={E}")
 
 
+@pytest.mark.parametrize("L", [65280, 65281])
+@pytest.mark.parametrize("n_nodes", [1, 4])
+def test_votes_of_the_longest_samples(L, n_nodes):
+    """Every token reaches node 0, so that a lane of the packed kernel counts 255 votes for it at 65280 tokens, which is what a
+    byte holds; 65281 tokens make 256."""
+    rng = np.random.default_rng(L)
+    E, k = 8, 2
+    idx = np.zeros((2, L, k), dtype=np.uint8)
+    idx[:, :, 1] = rng.integers(1, E, size=(2, L))
+    nodes = [np.array([0])] + [np.arange(1, E)[n::n_nodes - 1] for n in range(n_nodes - 1)]
+    check_all(idx, E, nodes, label=f"{L} tokens, all on node 0 of {n_nodes}")
+
+
 @pytest.mark.parametrize("E_S,E_T,scale", [(1, 1, 1), (63, 5, 1), (64, 64, 1), (65, 7, 1), (128, 1, 1), (129, 40, 1), (256, 100, 1),
                                            (257, 60, 1), (128, 31, 1 << 44), (200, 9, 1 << 44)])
 def test_fold_groups_sizes_ties_and_large_entries(E_S, E_T, scale):
-    """Few distinct values make many ties; entries of 2^44 and more do not fit the fp64 form of the loop exactly."""
+    """Few distinct values make many ties; entries of 2^44 and more go through the integer loop (their sums would still be
+    exact in doubles)."""
     rng = np.random.default_rng(E_S)
     P = rng.integers(0, 4, size=(E_S, E_S)).astype(np.int64) * scale + (rng.integers(0, 2, size=(E_S, E_S)) if scale > 1 else 0)
     P = P + P.T
     grp = torch.full((E_S,), -1, dtype=torch.int32, device=DEV)
     b.grouter_fold_groups(torch.from_numpy(P).to(DEV), E_T, grp)
     assert (grp.cpu().numpy() == rs.fold_groups(P, E_T)).all()
+
+
+def _groups_in_doubles(P, E_T):
+    """The same greedy grouping with scores in float64."""
+    P, E_S = P.astype(np.float64), len(P)
+    group_of = np.full(E_S, -1, dtype=np.int32)
+    for g in range(E_T):
+        score = np.zeros(E_S)
+        for _ in range(E_S // E_T + (g < E_S % E_T)):
+            pick = int(np.argmax(np.where(group_of < 0, score, -np.inf)))
+            group_of[pick] = g
+            score = score + P[pick]
+    return group_of
+
+
+@pytest.mark.parametrize("E_S,E_T", [(30, 6), (64, 20), (128, 31), (200, 50)])
+def test_fold_groups_beyond_the_exact_range_of_doubles(E_S, E_T):
+    """Entries of 2^54 and more, where doubles are four apart, that differ in the two bits below."""
+    P = (1 << 54) + np.random.default_rng(E_S).integers(0, 4, size=(E_S, E_S)).astype(np.int64)
+    P = np.triu(P) + np.triu(P, 1).T
+    ref = rs.fold_groups(P, E_T)
+    assert (rs.fold_groups(P >> 44, E_T) == _groups_in_doubles(P >> 44, E_T)).all()      # the same rule where doubles are exact
+    assert (_groups_in_doubles(P, E_T) != ref).any()
+    grp = torch.full((E_S,), -1, dtype=torch.int32, device=DEV)
+    b.grouter_fold_groups(torch.from_numpy(P).to(DEV), E_T, grp)
+    assert (grp.cpu().numpy() == ref).all()
 
 
 def test_fold_weights_with_groups_that_have_no_members():
