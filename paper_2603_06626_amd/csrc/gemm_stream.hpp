@@ -13,9 +13,9 @@
 // of one row.  The activations' operand (RB blocks of 16 rows, 8 consecutive K per lane) is loaded directly, too.  At the end the waves'
 // partial sums meet in LDS and are added in wave order, so results do not depend on timing.
 //
-// Measured (d = 2048, f = 1408, E = 64, k = 6, one token, kernel time): gate/up 39.7 -> 20 us, down 26.6 -> 10.5 us, that
-// is 3.4 TB/s; T = 4: a layer 86 -> 84 us; T = 16: 188 -> 175 us (5 TB/s), d = 4096 and E = 128 at T = 16 unchanged (5.7
-// TB/s, what this memory gives).  4 columns per lane (whole 128-byte lines per K-row) beat 2 (27 us) and 8 (30 us, too
+// Measured, 128-row tiles -> here (d = 2048, f = 1408, E = 64, k = 6, between events): one token gate/up 31.5 -> 16 us, down
+// 23.7 -> 11, that is 4.3 and 3.2 TB/s; a layer with its combine 61 -> 26; T = 4 79 -> 72; T = 16 181 -> 164 (5.4 TB/s); d = 4096 and
+// E = 128 at T = 16 unchanged (5.6 TB/s, what this memory gives).  4 columns per lane (whole 128-byte lines per K-row) beat 2 (27 us) and 8 (30 us, too
 // few workgroups); 8 waves beat 4 and 16; 1 to 8 stages are within 1 % once every wave has a block for each.
 #pragma once
 #include "gemm_kernels.hpp"

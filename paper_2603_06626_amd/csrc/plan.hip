@@ -12,7 +12,8 @@
 // In the placing pass a wave walks its slots 64 at a time in order; a lane's rank among the lanes of the same expert
 // comes from wave ballots, the running per-expert cursor from the wave's own LDS column.
 // Back-to-back builds, three launches (histogram, finish, scatter) before and now: N = 6, E = 64 13.8 -> 7.8 us; N = 4995,
-// E = 60 16.9 -> 10.0; N = 49152, E = 64 19.1 -> 10.2; N = 131072, E = 128 37.4 -> 13.7.  One launch against two at N = 4995:
+// E = 60 16.9 -> 10.0; N = 49152, E = 64 19.1 -> 10.2; N = 131072, E = 128 37.4 -> 13.7.  The most counts to add up, 256 x 1024
+// in each of 257 workgroups: N = 131072, E = 1024 206 -> 70; N = 524288 681 -> 239; N = 2^23 10264 -> 471.  One launch against two at N = 4995:
 // 10.7 against 10.0 us, at 8192: 16.7 against 10.3.
 // Nothing is accumulated into memory that an earlier launch must have cleared, so a plan can be rebuilt in
 // place and the build can be captured into a HIP graph as it is.

@@ -213,15 +213,18 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats(const IdxT* __res
     if (tid == 0) entropy[s] = h;
 }
 
-// The same for k <= 8, E <= 247, at most 16 nodes and samples of at most 255 * 256 tokens, i.e. for everything the cached
-// format holds in practice.  The general kernel above is bound by LDS bank conflicts (64 lanes add to and look up random
-// experts: about five rounds per access) and by 28 compares per token.  Here
-//   * a word of the table is (node set << 16 | count) and every lane of a wave has a column of its own in it (R columns), so
-//     one conflict-free atomic per id counts the expert and returns its nodes;
+// The same for k <= 8, E <= 247, at most 16 nodes and samples of at most 255 * 256 tokens that are long enough (packed_pays).
+// The general kernel above is bound by LDS bank conflicts (64 lanes add to and look up random experts: about five rounds per
+// access) and by 28 compares per token.  Here
+//   * a word of the table is (node set << 16 | count) and there are R columns of them, so one atomic per id counts the expert
+//     and returns its nodes.  R = 64 up to 128 experts: every lane of a wave has a column of its own and no access
+//     conflicts.  R = 32 beyond, where 64 would not leave room for four workgroups on a CU: lanes l and l + 32 share a column,
+//     two rounds per access at most;
 //   * ids that do not count (out of range, repeated, tokens past the end) go to a spare row;
 //   * repeats are detected four bytes at a time on the packed ids; only a wave that has one compares slot by slot;
 //   * a lane keeps its votes per node as bytes and adds them up at the end.
-// Measured on 2048 x 4096 tokens, k = 8, E = 128, uint8, 4 nodes: 82 -> 42 us (a lane-atomic costs about 20 cycles per wave even without conflicts).
+// Measured on 2048 x 4096 tokens, k = 8, uint8, 4 nodes, both statistics (a call of three launches): E = 128 86 -> 44 us, E = 200
+// 86 -> 44, E = 247 with 16 nodes (int32) 103 -> 59 (a lane-atomic costs about 20 cycles per wave even without conflicts).
 constexpr int kFastStatE = 247, kFastStatNodes = 16, kFastStatL = 255 * kStatThreads;
 
 // nonzero if two of the eight bytes of (x, y) are equal

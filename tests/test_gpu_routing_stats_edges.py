@@ -11,15 +11,15 @@ from tests.test_gpu_routing_stats import DEV, check_all     # noqa: E402
 
 
 @pytest.mark.parametrize("S,L,k,E,n_nodes,dtype", [
-    (3, 255, 8, 128, 16, np.uint8),     # widest table with a column per lane, one token short of a workgroup
-    (3, 257, 8, 129, 4, np.uint8),      # narrower table
-    (2, 300, 8, 247, 16, np.int32),     # last E of the packed form
-    (2, 300, 8, 248, 4, np.uint8),      # general kernel by E
-    (2, 100, 9, 64, 4, np.uint8),       # by k
+    (3, 255, 8, 128, 16, np.uint8),     # short samples: general kernel; one token short of a workgroup
+    (3, 257, 8, 129, 4, np.uint8),      # one more
+    (2, 300, 8, 247, 16, np.int32),
+    (2, 300, 8, 248, 4, np.uint8),
+    (2, 100, 9, 64, 4, np.uint8),       # more than 8 ids: the wide form
     (2, 130, 64, 256, 4, np.uint8),     # most slots a token can have
     (3, 90, 13, 6, 2, np.int32),        # more slots than experts: every token repeats some
     (1, 257, 10, 250, 5, np.int32),     # k and E beyond the packed form
-    (2, 100, 8, 64, 17, np.int32),      # by the number of nodes
+    (2, 100, 8, 64, 17, np.int32),
     (1, 65280, 2, 5, 3, np.uint8),      # longest sample whose votes fit a byte per lane
     (1, 65281, 2, 5, 3, np.uint8),
     (4, 1, 1, 1, 1, np.int32),
