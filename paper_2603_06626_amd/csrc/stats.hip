@@ -7,11 +7,8 @@
 //
 // The per-sample statistics (affinity counts, entropy, loads, placement) come from one kernel that reads every id
 // once: a lane takes one token, loads its k ids with one coalesced access (8 bytes for the cached format of
-// k = 8 one-byte ids), counts membership with LDS atomics and votes per node with wave ballots.  The
-// co-activation matrix is a Gram matrix, P = sum over tokens of ind_t ind_t^T with ind_t the 0/1 membership vector of
-// a token: a workgroup writes the indicator bytes of 256 tokens into LDS (expert-major, so that 16 consecutive
-// tokens of one expert are one 16-byte read) and accumulates P on the matrix cores with 8-bit integer MFMAs,
-// exact in int32.  Membership is an indicator per token: an id repeated inside a token counts once, ids outside
+// k = 8 one-byte ids), counts membership with LDS atomics and votes per node with wave ballots.  (The co-activation
+// matrix has a file of its own.)  Membership is an indicator per token: an id repeated inside a token counts once, ids outside
 // [0,E) are ignored.  Integer arithmetic throughout, so every result is bit-reproducible.
 #include "common.hpp"
 
@@ -417,11 +414,6 @@ __global__ __launch_bounds__(kLoadsThreads) void k_loads_maxvio(const int32_t* _
     }
 }
 
-__global__ void k_fill_u64(unsigned long long* p, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ull;
-}
-
 // (max L - mean L) / mean L over the E loads; one workgroup.
 __global__ __launch_bounds__(kStatThreads) void k_maxvio(const unsigned long long* __restrict__ loads, int E,
                                                          double* __restrict__ out) {
@@ -447,161 +439,6 @@ __global__ __launch_bounds__(kStatThreads) void k_maxvio(const unsigned long lon
         const double mean = (double)s_sum[0] / (double)E;
         out[0] = s_sum[0] > 0 ? ((double)s_max[0] - mean) / mean : 0.0;
     }
-}
-
-// ---------------------------------------------------------------------------------------------------
-// Co-activation counts P[i][j] = number of tokens whose top-k set holds both i and j: the Gram matrix of the
-// token x expert indicator matrix.  A workgroup owns a contiguous run of tokens and walks it TOK tokens at a
-// time: every lane sets the (at most k) bytes of its token in an expert-major byte matrix ind[e][t] in LDS (and
-// clears them again after use), and the workgroup multiplies ind by its transpose with v_mfma_i32_32x32x32_i8.
-// Both MFMA operands are 16 consecutive token bytes of one expert, i.e. one 16-byte LDS read, and the same read
-// serves as row operand and as column operand.  P is symmetric, so only the 32 x 32 blocks on and above the
-// diagonal are computed: wave pair p owns block rows p and NBLK-1-p, together NBLK+1 blocks whatever p is.
-// The waves of part q of a pair take the 32-token slabs q, q + SPLIT, ... of a pass, so several MFMA chains and
-// LDS reads are in flight per SIMD.  Counts stay exact: a workgroup adds at most 1 per token and cell, far
-// below 2^31.  At the end the parts are summed through LDS and part 0 adds the blocks into the 64-bit global
-// matrix with integer atomics; k_coact_mirror then fills the blocks below the diagonal.
-typedef int i32x16_t __attribute__((ext_vector_type(16)));
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
-
-template <int EP, int SPLIT, int TOK, int PAIR>
-struct CoactPair {
-    static constexpr int NBLK = EP / 32;
-    static constexpr int NSLOT = NBLK + 1;           // blocks this pair owns
-    static constexpr int NF = NBLK - PAIR;           // operand fragments it reads per slab: blocks PAIR .. NBLK-1
-    static constexpr int ROW_B = NBLK - 1 - PAIR;
-    static constexpr int PITCH = TOK + 16;
-    // block (row, col) of slot s
-    static constexpr int row_of(int s) { return s < NF ? PAIR : ROW_B; }
-    static constexpr int col_of(int s) { return s < NF ? PAIR + s : ROW_B + (s - NF); }
-
-    static __device__ __forceinline__ void slabs(const unsigned char* s_ind, int frag_at, int part, i32x16_t (&acc)[NSLOT]) {
-#pragma unroll
-        for (int i = 0; i < TOK / (32 * SPLIT); ++i) {
-            const int s32 = part + i * SPLIT;
-            i32x4_t f[NF];
-#pragma unroll
-            for (int c = 0; c < NF; ++c)
-                f[c] = *reinterpret_cast<const i32x4_t*>(s_ind + (PAIR + c) * 32 * PITCH + frag_at + s32 * 32);
-#pragma unroll
-            for (int s = 0; s < NSLOT; ++s)
-                acc[s] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f[row_of(s) - PAIR], f[col_of(s) - PAIR], acc[s], 0, 0, 0);
-        }
-    }
-};
-
-template <class IdxT, int EP, int SPLIT, int TOK>
-__global__ __launch_bounds__(EP / 64 * SPLIT * 64) void k_coactivation(const IdxT* __restrict__ idx, int64_t T, int k, int E,
-                                                                    int64_t tokens_per_group, unsigned long long* __restrict__ P) {
-    constexpr int NBLK = EP / 32;        // 32-expert blocks per side
-    constexpr int NPAIR = NBLK / 2;      // wave pairs: block rows p and NBLK-1-p
-    constexpr int NSLOT = NBLK + 1;
-    constexpr int THREADS = NPAIR * 64 * SPLIT;
-    constexpr int PITCH = TOK + 16;      // bytes per expert row: 16-byte reads of neighbouring experts miss each other's banks
-    static_assert(NBLK % 2 == 0 && NPAIR <= 4, "block rows are owned in pairs");
-    static_assert(TOK % (32 * SPLIT) == 0 && TOK <= THREADS, "one token per lane, whole slabs per part");
-    static_assert(EP * PITCH >= NPAIR * 16 * 64 * 4, "the indicator buffer can hold one accumulator per pair");
-    // one more row than experts: ids that do not count (out of range, slots past k, lanes without a token) are
-    // pointed at it, so the set and clear passes are eight unconditional byte stores each.  (Two indicator
-    // buffers, with the clear of pass i-1 and the set of pass i+1 issued under the MFMAs of pass i and one
-    // barrier per pass, measured slower: 0.128 vs 0.118 ms on the 8.4 M-token corpus.)
-    __shared__ __attribute__((aligned(16))) unsigned char s_ind[(EP + 1) * PITCH];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int rp = wave % NPAIR, part = wave / NPAIR;
-    const int64_t begin = (int64_t)blockIdx.x * tokens_per_group;
-    const int64_t end = min(T, begin + tokens_per_group);
-    i32x16_t acc[NSLOT];
-#pragma unroll
-    for (int s = 0; s < NSLOT; ++s)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[s][v] = 0;
-    const int frag_at = (lane & 31) * PITCH + 16 * (lane >> 5);   // this lane's 16 tokens of expert (block * 32 + lane % 32)
-    static_assert((TOK & (TOK - 1)) == 0, "TOK is a power of two");
-    const int kDummy = EP * PITCH + (tid & (TOK - 1));   // this lane's byte of the spare row (never read)
-    // k <= 8: the ids of the next pass are fetched before the MFMAs of this one, so their latency is hidden
-    RawIds8 ahead{};
-    if (k <= 8 && tid < TOK && begin + tid < end) ahead = fetch_token8(idx, begin + tid, k);
-    for (int i = tid; i < (EP + 1) * PITCH / 16; i += THREADS) reinterpret_cast<uint4*>(s_ind)[i] = uint4{0u, 0u, 0u, 0u};
-    __syncthreads();
-    for (int64_t t0 = begin; t0 < end; t0 += TOK) {
-        const int toks = (int)min((int64_t)TOK, end - t0);
-        // set this pass's bytes; after the MFMAs every lane clears the bytes it set, so the matrix is never swept
-        int mine[8];
-        if (k <= 8) {
-            unpack_token8(idx, ahead, k, mine);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {   // a repeated id sets the same byte again
-                mine[j] = (tid < toks && (unsigned)mine[j] < (unsigned)E) ? mine[j] * PITCH + tid : kDummy;
-                s_ind[mine[j]] = 1;
-            }
-            if (tid < TOK && t0 + TOK + tid < end) ahead = fetch_token8(idx, t0 + TOK + tid, k);
-        } else if (tid < toks) {
-            const IdxT* ids = idx + (size_t)(t0 + tid) * k;
-            for (int j = 0; j < k; ++j) {
-                const int64_t e = (int64_t)ids[j];
-                if (e >= 0 && e < E) s_ind[e * PITCH + tid] = 1;   // a repeated id sets the same byte again
-            }
-        }
-        __syncthreads();
-        // (columns past the last token of a short pass are zero, so the slabs need no bound of their own)
-        if (rp == 0) CoactPair<EP, SPLIT, TOK, 0>::slabs(s_ind, frag_at, part, acc);
-        if constexpr (NPAIR > 1) { if (rp == 1) CoactPair<EP, SPLIT, TOK, 1>::slabs(s_ind, frag_at, part, acc); }
-        if constexpr (NPAIR > 2) { if (rp == 2) CoactPair<EP, SPLIT, TOK, 2>::slabs(s_ind, frag_at, part, acc); }
-        if constexpr (NPAIR > 3) { if (rp == 3) CoactPair<EP, SPLIT, TOK, 3>::slabs(s_ind, frag_at, part, acc); }
-        __syncthreads();   // every wave has read the indicator
-        if (k <= 8) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) s_ind[mine[j]] = 0;
-        } else if (tid < toks) {
-            const IdxT* ids = idx + (size_t)(t0 + tid) * k;
-            for (int j = 0; j < k; ++j) {
-                const int64_t e = (int64_t)ids[j];
-                if (e >= 0 && e < E) s_ind[e * PITCH + tid] = 0;
-            }
-        }
-        // no barrier needed here: a lane clears and then sets only bytes of its own token column
-    }
-    // sum the parts: part q hands its accumulators to part 0 through LDS, one slot of every pair at a time
-    int* const xchg = reinterpret_cast<int*>(s_ind);
-#pragma unroll 1
-    for (int q = 1; q < SPLIT; ++q) {
-#pragma unroll
-        for (int s = 0; s < NSLOT; ++s) {
-            __syncthreads();
-            if (part == q) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) xchg[(rp * 16 + v) * 64 + lane] = acc[s][v];
-            }
-            __syncthreads();
-            if (part == 0) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[s][v] += xchg[(rp * 16 + v) * 64 + lane];
-            }
-        }
-    }
-    if (part != 0) return;
-    // accumulator element v of a lane is row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32 of the block
-#pragma unroll
-    for (int s = 0; s < NSLOT; ++s) {
-        // slot -> block (uniform per wave; same mapping as CoactPair)
-        const int nf = NBLK - rp;
-        const int brow = s < nf ? rp : NBLK - 1 - rp;
-        const int bcol = s < nf ? rp + s : (NBLK - 1 - rp) + (s - nf);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = brow * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-            const int col = bcol * 32 + (lane & 31);
-            const int c = acc[s][v];
-            if (row < E && col < E && c) atomicAdd(&P[(size_t)row * E + col], (unsigned long long)c);
-        }
-    }
-}
-
-// The blocks below the diagonal are the transposes of the ones above it (a mirrored atomic per cell would touch
-// one cache line per lane): filled in afterwards, one workgroup per row.
-__global__ __launch_bounds__(256) void k_coact_mirror(int E, unsigned long long* __restrict__ P) {
-    const int row = blockIdx.x;
-    for (int col = threadIdx.x; col < (row & ~31); col += 256) P[(size_t)row * E + col] = P[(size_t)col * E + row];
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -968,34 +805,6 @@ hipError_t launch_placement(const void* idx, int idx_dtype, int64_t S, int L, in
                             int n_nodes, int32_t* comm, int32_t* best_node, hipStream_t s) {
     return launch_sample_stats(idx, idx_dtype, S, L, k, E, nullptr, nullptr, nullptr, nullptr, expert_nodes, n_nodes, comm,
                                best_node, s);
-}
-
-template <class IdxT>
-static void launch_coact_t(const IdxT* idx, int64_t T, int k, int E, unsigned long long* P, hipStream_t s) {
-    // Every workgroup ends by adding its whole matrix into the global one, so no more groups than there are CUs.
-    constexpr int kTok = 512;
-    constexpr int max_groups = 256;   // measured on 8.4 M tokens: 128 groups 0.31 ms, 256 groups 0.18 ms, 512 groups 0.20 ms
-    int64_t groups = (T + 2 * kTok - 1) / (2 * kTok);
-    if (groups > max_groups) groups = max_groups;
-    if (groups < 1) groups = 1;
-    const int64_t per = ((T + groups - 1) / groups + kTok - 1) / kTok * kTok;
-    const dim3 grid((unsigned)((T + per - 1) / per));
-    if (E <= 64)
-        hipLaunchKernelGGL((k_coactivation<IdxT, 64, 8, kTok>), grid, dim3(512), 0, s, idx, T, k, E, per, P);
-    else if (E <= 128)
-        hipLaunchKernelGGL((k_coactivation<IdxT, 128, 4, kTok>), grid, dim3(512), 0, s, idx, T, k, E, per, P);
-    else
-        hipLaunchKernelGGL((k_coactivation<IdxT, 256, 2, kTok>), grid, dim3(512), 0, s, idx, T, k, E, per, P);
-}
-
-hipError_t launch_coactivation(const void* idx, int idx_dtype, int64_t T, int k, int E, int64_t* P, hipStream_t s) {
-    auto* p = reinterpret_cast<unsigned long long*>(P);
-    const int64_t n = (int64_t)E * E;
-    hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
-    if (idx_dtype == 1) launch_coact_t((const uint8_t*)idx, T, k, E, p, s);
-    else launch_coact_t((const int32_t*)idx, T, k, E, p, s);
-    if (E > 32) hipLaunchKernelGGL(k_coact_mirror, dim3((unsigned)E), dim3(256), 0, s, E, p);
-    return hipGetLastError();
 }
 
 hipError_t launch_fold_groups(const int64_t* P, int E_S, int E_T, int32_t* group_of, hipStream_t s) {

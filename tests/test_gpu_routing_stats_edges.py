@@ -59,6 +59,38 @@ def test_votes_of_the_longest_samples(L, n_nodes):
     check_all(idx, E, nodes, label=f"{L} tokens, all on node 0 of {n_nodes}")
 
 
+@pytest.mark.parametrize("dtype", [np.uint8, np.int32])
+@pytest.mark.parametrize("T,k,E", [
+    (1, 1, 1), (1, 8, 9), (3, 2, 33),               # fewer ids than one fetch takes
+    (513, 2, 64), (1537, 1, 32), (2049, 3, 128), (1025, 7, 256),    # a last run of one token, whose fetch begins before it
+    (511, 4, 65), (1024, 5, 97), (4097, 8, 129),    # one block, several, an odd number; 4 and 8 slots kept
+    (5000, 8, 200), (30000, 6, 63), (700, 9, 60), (900, 64, 250),
+])
+def test_coactivation_at_the_edges_of_its_kernels(T, k, E, dtype):
+    """Exact counts.  Ids repeat inside tokens, and some lie outside [0, E)."""
+    rng = np.random.default_rng(T + k + E)
+    idx = (rng.integers(0, 1 << 30, size=(T, k)) % rng.integers(1, E + 1, size=(T, 1))).astype(dtype)
+    stray = rng.random((T, k)) < 0.1
+    idx[stray] = rng.choice([min(E, 255), 255] if dtype is np.uint8 else [-1, E, E + 70, 2**31 - 1, -2**31], size=stray.sum())
+    P = torch.full((E, E), -1, dtype=torch.int64, device=DEV)
+    b.grouter_coactivation(torch.from_numpy(idx).to(DEV), E, P)
+    wide = idx.astype(np.int64)
+    wide[(wide < 0) | (wide >= E)] = E      # an expert more, left out again, for the ids that do not count
+    assert (P.cpu().numpy() == rs.coactivation(wide, E + 1)[:E, :E]).all()
+
+
+def test_coactivation_of_more_tokens_than_half_a_word_counts():
+    """2^32 tokens of one expert and three of another: counts that two to a word could not hold, and 2^21 in every wave's fp32."""
+    E, T = 200, (1 << 32) + 3
+    idx = torch.zeros((T, 1), dtype=torch.uint8, device=DEV)
+    idx[T // 2] = idx[5] = idx[T - 1] = 199
+    P = torch.full((E, E), -1, dtype=torch.int64, device=DEV)
+    b.grouter_coactivation(idx, E, P)
+    ref = torch.zeros((E, E), dtype=torch.int64)
+    ref[0, 0], ref[199, 199] = T - 3, 3
+    assert torch.equal(P.cpu(), ref)
+
+
 @pytest.mark.parametrize("E_S,E_T,scale", [(1, 1, 1), (63, 5, 1), (64, 64, 1), (65, 7, 1), (128, 1, 1), (129, 40, 1), (256, 100, 1),
                                            (257, 60, 1), (128, 31, 1 << 44), (200, 9, 1 << 44)])
 def test_fold_groups_sizes_ties_and_large_entries(E_S, E_T, scale):
