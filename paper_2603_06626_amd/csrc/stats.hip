@@ -10,7 +10,9 @@
 // k = 8 one-byte ids), counts membership with LDS atomics and votes per node with wave ballots.  (The co-activation
 // matrix has a file of its own.)  Membership is an indicator per token: an id repeated inside a token counts once, ids outside
 // [0,E) are ignored.  Integer arithmetic throughout, so every result is bit-reproducible.
-#include "common.hpp"
+#include <type_traits>
+
+#include "stats_ids.hpp"
 
 namespace grouter {
 
@@ -57,21 +59,6 @@ __device__ __forceinline__ RawIds8 fetch_token8(const IdxT* __restrict__ base, i
         for (int j = 0; j < 8; ++j) r.e[j] = j < k ? (int)ids[j] : -1;
     }
     return r;
-}
-// the 8 ids as fetched (slots past k hold -1), without any filtering
-template <class IdxT>
-__device__ __forceinline__ void unpack_token8(const IdxT* __restrict__ base, const RawIds8& r, int k, int (&e)[8]) {
-    if (sizeof(IdxT) == 1 && k == 8 && (reinterpret_cast<uintptr_t>(base) & 7u) == 0) {
-        const uint32_t x = (uint32_t)r.e[0], y = (uint32_t)r.e[1];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            e[j] = (int)((x >> (8 * j)) & 0xffu);
-            e[4 + j] = (int)((y >> (8 * j)) & 0xffu);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) e[j] = r.e[j];
-    }
 }
 template <class IdxT>
 __device__ __forceinline__ void decode_token8(const IdxT* __restrict__ base, const RawIds8& r, int k, int E, int (&e)[8]) {
@@ -213,15 +200,17 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats(const IdxT* __res
 // The same for k <= 8, E <= 247, at most 16 nodes and samples of at most 255 * 256 tokens that are long enough (packed_pays).
 // The general kernel above is bound by LDS bank conflicts (64 lanes add to and look up random experts: about five rounds per
 // access) and by 28 compares per token.  Here
-//   * a word of the table is (node set << 16 | count) and there are R columns of them, so one atomic per id counts the expert
-//     and returns its nodes.  R = 64 up to 128 experts: every lane of a wave has a column of its own and no access
-//     conflicts.  R = 32 beyond, where 64 would not leave room for four workgroups on a CU: lanes l and l + 32 share a column,
-//     two rounds per access at most;
+//   * a word of the table is (node set << 16 | count) and there are R columns of them: per id one read that tells the nodes and one
+//     add that returns nothing (together cheaper than one that returns the word).  R = 64 up to 128 experts: every lane of a wave
+//     has a column of its own and no access conflicts.  R = 32 beyond, where 64 would not leave room for four workgroups on a
+//     CU: lanes l and l + 32 share a column, two rounds per access at most;
+//   * the ids of the next two tokens are on their way while one is counted, and all its reads are issued before the first is used;
 //   * ids that do not count (out of range, repeated, tokens past the end) go to a spare row;
 //   * repeats are detected four bytes at a time on the packed ids; only a wave that has one compares slot by slot;
 //   * a lane keeps its votes per node as bytes and adds them up at the end.
-// Measured on 2048 x 4096 tokens, k = 8, uint8, 4 nodes, both statistics (a call of three launches): E = 128 86 -> 44 us, E = 200
-// 86 -> 44, E = 247 with 16 nodes (int32) 103 -> 59 (a lane-atomic costs about 20 cycles per wave even without conflicts).
+// Measured, both statistics (a call of three launches; general kernel / this one with returning adds and one token ahead / now):
+// 2048 x 4096 tokens, k = 8, uint8, 4 nodes, E = 128 86 / 45.6 / 40 us; 700 x 3000, k = 5, uint8, E = 200 - / 22.5 / 19; 512 x 2048,
+// k = 8, int32, E = 128 - / 16.2 / 14.7.
 constexpr int kFastStatE = 247, kFastStatNodes = 16, kFastStatL = 255 * kStatThreads;
 
 // nonzero if two of the eight bytes of (x, y) are equal
@@ -235,7 +224,7 @@ __device__ __forceinline__ uint32_t equal_bytes8(uint32_t x, uint32_t y) {
 }
 
 template <class IdxT, bool AFF, bool PLACE, int R>
-__global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __restrict__ idx, int L, int k, int E,
+__global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __restrict__ idx, int64_t S, int L, int k, int E,
                                                                 int32_t* __restrict__ counts, double* __restrict__ entropy,
                                                                 const uint64_t* __restrict__ expert_nodes, int n_nodes,
                                                                 int32_t* __restrict__ comm, int32_t* __restrict__ best_node) {
@@ -247,9 +236,12 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __re
     __shared__ long long s_tot[kStatThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t s = blockIdx.x;
-    const IdxT* base = idx + (size_t)s * L * k;
-    RawIds8 ahead{};
-    if (tid < L) ahead = fetch_token8(base, tid, k);
+    const IdxT* const base = idx + (size_t)s * L * k;
+    using Ids = IdWindow<IdxT, 8>;
+    const int last = (int)min((S - s) * L * k - Ids::kWindow, (int64_t)0x7fffffff);
+    Ids ids[2];   // the next two tokens of this lane
+    ids[0].fetch(base, tid * k, last);
+    ids[1].fetch(base, (tid + kStatThreads) * k, last);
     if (!PLACE) {
         for (int i = tid; i < (E + 1) * (R / 4); i += kStatThreads) reinterpret_cast<uint4*>(s_tab)[i] = uint4{0u, 0u, 0u, 0u};
     } else if (tid <= E) {   // a thread fills a row, so that it loads one node set; each begins at another bank
@@ -262,26 +254,24 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __re
     __syncthreads();
     uint32_t* const column = s_tab + (lane & (R - 1));
     uint32_t votes[4] = {0u, 0u, 0u, 0u};
-    for (int t0 = 0; t0 < L; t0 += kStatThreads) {
-        const RawIds8 raw = ahead;
-        if (t0 + kStatThreads + tid < L) ahead = fetch_token8(base, t0 + kStatThreads + tid, k);
-        int e[8];
-        unpack_token8(base, raw, k, e);
-        const bool live = t0 + tid < L;
+    // bytes of slots past k: values that no expert has
+    const uint32_t keep_x = k >= 4 ? ~0u : (1u << (8 * k)) - 1u, keep_y = k >= 8 ? ~0u : k <= 4 ? 0u : (1u << (8 * (k - 4))) - 1u;
+    auto turn = [&](Ids& window, int t) {
+        window.settle();
+        uint32_t e[8], x, y;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) e[j] = live ? (int)min((uint32_t)e[j], (uint32_t)E) : E;
-        uint32_t x, y;
-        if (sizeof(IdxT) == 1 && k == 8 && (reinterpret_cast<uintptr_t>(base) & 7u) == 0) {
-            x = (uint32_t)raw.e[0];
-            y = (uint32_t)raw.e[1];
-        } else {   // slots past k: values that no expert has
-            uint32_t p[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) p[j] = j < k ? (uint32_t)e[j] : 0xf8u + j;
-            x = p[0] | (p[1] << 8) | (p[2] << 16) | (p[3] << 24);
-            y = p[4] | (p[5] << 8) | (p[6] << 16) | (p[7] << 24);
+        for (int j = 0; j < 8; ++j) e[j] = t < L && j < k ? min(window.id(j), (uint32_t)E) : (uint32_t)E;
+        if constexpr (sizeof(IdxT) == 1) {
+            x = window.w[0];
+            y = window.w[1];
+        } else {
+            x = e[0] | (e[1] << 8) | (e[2] << 16) | (e[3] << 24);
+            y = e[4] | (e[5] << 8) | (e[6] << 16) | (e[7] << 24);
         }
-        if (__any(live && equal_bytes8(x, y))) {
+        x = (x & keep_x) | (0xfbfaf9f8u & ~keep_x);
+        y = (y & keep_y) | (0xfffefdfcu & ~keep_y);
+        window.fetch(base, (t + 2 * kStatThreads) * k, last);
+        if (__any(t < L && equal_bytes8(x, y))) {
 #pragma unroll
             for (int j = 1; j < 8; ++j) {
                 bool dup = false;
@@ -290,20 +280,33 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __re
                 if (dup) e[j] = E;
             }
         }
+        // all reads, then all adds; slots past k go to the spare row too (with a branch per slot every read was waited for)
         uint32_t seen = 0;
+        auto slots = [&](auto n) {
+            constexpr int N = decltype(n)::value;
+            uint32_t word[N];
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (j < k) {
-                if (AFF && PLACE) seen |= atomicAdd(&column[e[j] * R], 1u);
-                else if (AFF) atomicAdd(&column[e[j] * R], 1u);
-                else seen |= column[e[j] * R];
-            }
+            for (int j = 0; j < N; ++j)
+                if (PLACE) word[j] = column[e[j] * R];
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                if (AFF) atomicAdd(&column[e[j] * R], 1u);   // (the returned word would cost twice a read and an add without)
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                if (PLACE) seen |= word[j];
+        };
+        if (k > 4) slots(std::integral_constant<int, 8>{});
+        else slots(std::integral_constant<int, 4>{});
         if (PLACE) {
             const uint32_t reach = seen >> 16;
 #pragma unroll
             for (int q = 0; q < 4; ++q)   // four bits to four bytes
                 if (4 * q < n_nodes) votes[q] += (((reach >> (4 * q)) & 15u) * 0x00204081u) & 0x01010101u;
         }
+    };
+    for (int t0 = 0; t0 < L; t0 += 2 * kStatThreads) {
+        turn(ids[0], t0 + tid);
+        turn(ids[1], t0 + kStatThreads + tid);   // past the end: spare rows only
     }
     if (PLACE) {
         // four byte counts become two words of two 16-bit sums (at most 64 * 255 each), which are added over the wave: chains that
@@ -764,7 +767,7 @@ hipError_t launch_sample_stats(const void* idx, int idx_dtype, int64_t S, int L,
                                 expert_nodes, n_nodes, comm, best_node);                                           \
     } while (0)
 #define GROUTER_STATS8(T_, A_, P_, R_)                                                                             \
-    hipLaunchKernelGGL((k_sample_stats8<T_, A_, P_, R_>), grid, block, 0, s, (const T_*)idx, L, k, E, counts, entropy, \
+    hipLaunchKernelGGL((k_sample_stats8<T_, A_, P_, R_>), grid, block, 0, s, (const T_*)idx, S, L, k, E, counts, entropy, \
                        expert_nodes, n_nodes, comm, best_node)
     const bool fast = k <= 8 && E <= kFastStatE && n_nodes <= kFastStatNodes && L <= kFastStatL && packed_pays(S, L, k, counts != nullptr, comm != nullptr);
     // a column per lane where the table then fits 33 KB
