@@ -450,10 +450,11 @@ __global__ __launch_bounds__(kStatThreads) void k_maxvio(const unsigned long lon
 // chain of E_S rounds, so what counts is the length of one round.
 //
 // Up to 256 experts one wave runs it, lane l holding the experts l, l + 64, ...: a round is a maximum over the wave in six
-// DPP steps, ballots that find who holds it, and one row of the matrix from LDS (E_S <= 128, staged by the whole
-// workgroup first) or L2.  No barrier is involved.  Scores are exact in double below 2^53; a matrix with larger entries is
-// grouped in 64-bit integers by the same loop.  Measured, 128 -> 32 groups: 131 -> 31 us (a workgroup of 128 threads with
-// three barriers per round before).
+// DPP steps, and one row of the matrix from LDS, staged by the whole workgroup first, or L2.  No barrier is involved.  Scores
+// below 2^24 make one 32-bit key with the expert (fold_keys); otherwise they are doubles, exact below 2^53, and ballots find who
+// holds the maximum; a matrix with larger entries is grouped in 64-bit integers by the same loop.  Measured, a workgroup with
+// three barriers per round / doubles / keys: 128 -> 32 groups 131 / 28 / 21 us; 64 -> 10 - / 12.6 / 9.9; 200 -> 50, which as doubles
+// does not fit the LDS, - / 80 / 47.
 template <int ctrl, class V>
 __device__ __forceinline__ V dpp_max(V v) {
     union { V v; int w[2]; } a, b;
@@ -477,6 +478,19 @@ __device__ __forceinline__ V wave_max(V v) {
     a.w[0] = __builtin_amdgcn_readlane(a.w[0], 63);
     a.w[1] = __builtin_amdgcn_readlane(a.w[1], 63);
     return a.v;
+}
+
+// unsigned: a lane without a source takes 0, and every step is one instruction
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#define GROUTER_STEP(ctrl) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, true))
+    GROUTER_STEP(0x111);
+    GROUTER_STEP(0x112);
+    GROUTER_STEP(0x114);
+    GROUTER_STEP(0x118);
+    GROUTER_STEP(0x142);
+    GROUTER_STEP(0x143);
+#undef GROUTER_STEP
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 // row(e, i): entry (e, lane + 64 i) of the matrix
@@ -529,32 +543,101 @@ __device__ __forceinline__ void fold_loop(int E_S, int E_T, int lane, int32_t* _
         if (lane + 64 * i < E_S) group_of[lane + 64 * i] = group[i];
 }
 
+// The same loop on keys of 32 bits, score * 256 + 255 - expert: their maximum over the wave is one instruction a step and names the
+// expert, the lowest of those that tie.  For scores below 2^24 and up to 255 experts; the matrix in LDS holds scores * 256.
+template <int PER>
+__device__ __forceinline__ void fold_keys(int E_S, int E_T, int lane, int32_t* __restrict__ group_of, const uint32_t* s_P) {
+    uint64_t open[PER];   // unassigned experts, by lane
+    uint32_t alive[PER];  // the same, as a mask of each lane's own
+    int group[PER] = {};
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        open[i] = __ballot(lane + 64 * i < E_S);
+        alive[i] = lane + 64 * i < E_S ? ~0u : 0u;
+    }
+    const int g_avg = E_S / E_T, n_extra = E_S % E_T;
+    const uint32_t* const mine = s_P + min(lane, E_S - 1);
+    for (int g = 0; g < E_T; ++g) {
+        const int size = g_avg + (g < n_extra ? 1 : 0);
+        uint32_t key[PER];
+        int pick = 0;   // the group's first member: the lowest unassigned expert
+#pragma unroll
+        for (int i = PER - 1; i >= 0; --i)
+            if (open[i]) pick = 64 * i + (int)__builtin_ctzll(open[i]);
+        for (int m = 0;; ++m) {
+            const bool done = m + 1 >= size;
+            uint32_t p[PER];
+            if (!done) {   // requested first: the rest of the bookkeeping runs meanwhile (what a lane without an expert reads is masked)
+#pragma unroll
+                for (int i = 0; i < PER; ++i) p[i] = mine[min(pick * E_S + 64 * i, E_S * E_S - min(lane, E_S - 1) - 1)];
+            }
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                if (pick >> 6 == i) open[i] &= ~(1ull << (pick & 63));
+                if (pick == lane + 64 * i) {
+                    alive[i] = 0u;
+                    group[i] = g;
+                }
+            }
+            if (done) break;
+            uint32_t mx = 0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                key[i] = m == 0 ? p[i] + 255u - (uint32_t)(lane + 64 * i) : key[i] + p[i];
+                mx = max(mx, key[i] & alive[i]);
+            }
+            pick = 255 - (int)(wave_max_u32(mx) & 255u);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        if (lane + 64 * i < E_S) group_of[lane + 64 * i] = group[i];
+}
+
+// The matrix is staged in LDS as keys (E_S <= 200) if no score of a group can reach 2^24, otherwise as doubles (E_S <= 128) if all
+// scores are exact in them; what does not fit is read from L2.
+constexpr int kFoldStaged = 200;
 template <int PER>   // E_S <= 64 PER
 __global__ __launch_bounds__(1024) void k_fold_groups_wave(const long long* __restrict__ P, int E_S, int E_T, int32_t* __restrict__ group_of) {
-    constexpr bool STAGED = PER <= 2;
+    constexpr bool DOUBLES = PER <= 2;
+    constexpr int kWords = DOUBLES ? 2 * 64 * PER * 64 * PER : kFoldStaged * kFoldStaged;
     constexpr long long kExact = 1ll << 43;   // entries below this: sums of up to 1024 of them are exact in double
-    __shared__ double s_P[STAGED ? 64 * PER * 64 * PER : 1];
-    __shared__ int s_large;
+    __shared__ __attribute__((aligned(16))) uint32_t s_words[kWords];
+    __shared__ int s_large, s_wide;
+    double* const s_P = reinterpret_cast<double*>(s_words);
     const int tid = threadIdx.x;
-    if (tid == 0) s_large = 0;
+    if (tid == 0) s_large = s_wide = 0;
     __syncthreads();
-    bool large = false;
+    const bool fits = DOUBLES || E_S <= kFoldStaged;
+    const unsigned long long limit = 0xffffffull / (unsigned)((E_S + E_T - 1) / E_T);
+    bool large = false, wide = !fits;
+#pragma unroll 8
     for (int i = tid; i < E_S * E_S; i += 1024) {
         const long long v = P[i];
-        large |= v >= kExact || v <= -kExact;
-        if (STAGED) s_P[i] = (double)v;
+        if (i % (E_S + 1) != 0) {   // (the diagonal decides nothing)
+            large |= v >= kExact || v <= -kExact;
+            wide |= (unsigned long long)v > limit;
+        }
+        if (fits) s_words[i] = (uint32_t)v << 8;
     }
     if (large) s_large = 1;
+    if (wide) s_wide = 1;
     __syncthreads();
+    if (DOUBLES && s_wide && !s_large) {
+        for (int i = tid; i < E_S * E_S; i += 1024) s_P[i] = (double)P[i];
+        __syncthreads();
+    }
     if (tid >= 64) return;
-    auto entry = [&](int e, int i) { return (int64_t)e * E_S + min(tid + 64 * i, E_S - 1); };
-    if (s_large) {
-        fold_loop<long long, PER>(E_S, E_T, tid, group_of, -0x7fffffffffffffffLL - 1, [&](int e, int i) { return P[entry(e, i)]; });
-    } else {
+    auto entry = [&](int e, int i) { return e * E_S + min(tid + 64 * i, E_S - 1); };
+    if (!s_wide) {
+        fold_keys<PER>(E_S, E_T, tid, group_of, s_words);
+    } else if (!s_large) {
         fold_loop<double, PER>(E_S, E_T, tid, group_of, -1e300, [&](int e, int i) -> double {
-            if constexpr (STAGED) return s_P[entry(e, i)];
+            if constexpr (DOUBLES) return s_P[entry(e, i)];
             else return (double)P[entry(e, i)];
         });
+    } else {
+        fold_loop<long long, PER>(E_S, E_T, tid, group_of, -0x7fffffffffffffffLL - 1, [&](int e, int i) { return P[entry(e, i)]; });
     }
 }
 

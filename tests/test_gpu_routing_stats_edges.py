@@ -92,10 +92,13 @@ def test_coactivation_of_more_tokens_than_half_a_word_counts():
 
 
 @pytest.mark.parametrize("E_S,E_T,scale", [(1, 1, 1), (63, 5, 1), (64, 64, 1), (65, 7, 1), (128, 1, 1), (129, 40, 1), (256, 100, 1),
-                                           (257, 60, 1), (128, 31, 1 << 44), (200, 9, 1 << 44)])
+                                           (257, 60, 1), (128, 31, 1 << 44), (200, 9, 1 << 44), (201, 30, 1),
+                                           # groups of 8 with entries up to 6 * scale + 2: the last whose sums fit a key, and one more
+                                           (64, 8, 349524), (64, 8, 349525), (128, 16, 349524), (128, 16, 349525),
+                                           (200, 25, 349524), (200, 25, 349525)])
 def test_fold_groups_sizes_ties_and_large_entries(E_S, E_T, scale):
     """Few distinct values make many ties; entries of 2^44 and more go through the integer loop (their sums would still be
-    exact in doubles)."""
+    exact in doubles), sums of 2^24 and more through the one in doubles."""
     rng = np.random.default_rng(E_S)
     P = rng.integers(0, 4, size=(E_S, E_S)).astype(np.int64) * scale + (rng.integers(0, 2, size=(E_S, E_S)) if scale > 1 else 0)
     P = P + P.T
