@@ -26,8 +26,8 @@
 // block itself, and k_coact_finish spreads them out and fills the blocks below the diagonal.
 //
 // Measured (three launches; byte cells, two barriers per pass and one cell per atomic before): 2048 x 4096 tokens, E = 128, k = 8,
-// uint8 117 -> 70 us, of which the ORs, reads and clearing take about 41 and the sums 15; 512 x 2048 tokens, E = 128, k = 8, int32
-// 49 -> 28; 700 x 3000, E = 200, k = 5, uint8 113 -> 73 (one cell per atomic 92); 300 x 1500, E = 60, k = 3, int32 21 -> 14.  Cells of one bit
+// uint8 117 -> 63 us, of which the ORs, reads and clearing take about 41 and the sums 8; 512 x 2048 tokens, E = 128, k = 8, int32
+// 49 -> 27; 700 x 3000, E = 200, k = 5, uint8 113 -> 73 (one cell per atomic 92); 300 x 1500, E = 60, k = 3, int32 21 -> 14.  Cells of one bit
 // (32 tokens a word) or two need fewer reads, but more lanes then OR the same word: 113 -> 89 and 80 instead of 73.
 #include <cmath>
 #include <type_traits>
@@ -76,11 +76,15 @@ struct CoactShape {
 };
 
 // Where the word of rows (2 rp, 2 rp + 1) and column c of block (bi, bj) is summed.  The storage used is that of block (bj, bi):
-// `cols` rows of `width` cells, taken in order.  16 row pairs (or half of an odd last block) x cols words always fit.
+// `cols` rows of `width` cells, taken in order; 16 row pairs (or half of an odd last block) x cols words always fit.  Every
+// second row of blocks uses the lower half of its rows instead of the upper: at E = 128 the 256-byte segments of the upper
+// halves alone fall on half of the memory channels, up to four on one, and the atomics of all workgroups queue there (2048 x
+// 4096 tokens: 71 us, so 63).
 __device__ __forceinline__ size_t coact_word(int E, int bi, int bj, int rp, int c) {
     const int cols = min(32, E - 32 * bj), width = bi == bj ? cols : 32;
     const int at = rp * cols + c;
-    return (size_t)(32 * bj + at / width) * E + 32 * bi + at % width;
+    const int half = cols == 32 ? 16 * (bj & 1) : 0;
+    return (size_t)(32 * bj + half + at / width) * E + 32 * bi + at % width;
 }
 
 __device__ __forceinline__ i32x8_t coact_frag(const unsigned char* at) {
@@ -326,7 +330,8 @@ template <class IdxT>
 static void launch_coact_t(const IdxT* idx, int64_t T, int k, int E, bool packed, unsigned long long* P, hipStream_t s) {
     // A workgroup has a CU for itself, so there are no more than CUs.  Fewer groups have longer runs (about 1.25 ns a token) but fewer
     // sums queue at the end (0.06 us each), which is even at sqrt(T / 48) groups.  Measured with 256 / 192 / 128 groups: T = 450000,
-    // E = 60 16.3 / 15.5 / 14.6 us; T = 2^20, E = 128 33.5 / 30.0 / 27.9; T = 2^21 42.5 / 40.6 / 42.2; T = 2^23 70 / 76 / 93.
+    // E = 60 16.3 / 15.5 / 14.6 us; T = 2^20, E = 128 33.5 / 30.0 / 27.9; T = 2^21 42.5 / 40.6 / 42.2; T = 2^23 70 / 76 / 93 (all with
+    // twice the queueing, see coact_word).
     constexpr int kTok = 512, kMaxGroups = 256;
     int64_t groups = (int64_t)std::sqrt((double)T / 48.0);
     if (groups > kMaxGroups) groups = kMaxGroups;
