@@ -99,18 +99,31 @@ def _check(code: int, where: str):
 
 
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()     # (the argument types make a pointer of it)
+
+
+def _first_raw_stream() -> int:
+    """The current stream's handle; from the second call on without building a torch.cuda.Stream, which costs about as much as
+    a kernel launch."""
+    global _raw_stream
+    import torch
+
+    handle = torch.cuda.current_stream().cuda_stream     # initialises the device on the first call
+    get, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
+    if get is not None and get(device()) == handle:
+        _raw_stream = lambda: get(device())              # noqa: E731
+    return handle
+
+
+_raw_stream = _first_raw_stream
 
 
 def _stream(stream=None):
-    import torch
-
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return _raw_stream() if stream is None else stream.cuda_stream
 
 
 def _dev(t, name, dtype=None):
-    if not t.is_cuda or not t.is_contiguous():
+    if not (t.is_cuda and t.is_contiguous()):
         raise ValueError(f"{name} must be a contiguous GPU tensor")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name} must have dtype {dtype}")
@@ -194,7 +207,7 @@ def grouter_moe_fwd(plan_ws, x, gate_w, W1, W3, W2, y, ctx_ws, stream=None, k=No
     T, d = x.shape
     k = gate_w.shape[1] if gate_w is not None else int(k)
     E, d1, f = W1.shape
-    if d1 != d or tuple(W3.shape) != (E, d, f) or tuple(W2.shape) != (E, f, d) or tuple(y.shape) != (T, d):
+    if d1 != d or W3.shape != (E, d, f) or W2.shape != (E, f, d) or y.shape != (T, d):
         raise ValueError("shape mismatch")
     for t, n in ((x, "x"), (gate_w, "gate_w"), (W1, "W1"), (W3, "W3"), (W2, "W2"), (y, "y")):
         if t is not None:
@@ -214,7 +227,7 @@ def grouter_moe_fwd_only(plan_ws, x, gate_w, W1, W3, W2, y, ws, stream=None, k=N
     T, d = x.shape
     k = gate_w.shape[1] if gate_w is not None else int(k)
     E, d1, f = W1.shape
-    if d1 != d or tuple(W3.shape) != (E, d, f) or tuple(W2.shape) != (E, f, d) or tuple(y.shape) != (T, d):
+    if d1 != d or W3.shape != (E, d, f) or W2.shape != (E, f, d) or y.shape != (T, d):
         raise ValueError("shape mismatch")
     for t, n in ((x, "x"), (gate_w, "gate_w"), (W1, "W1"), (W3, "W3"), (W2, "W2"), (y, "y")):
         if t is not None:
@@ -235,7 +248,7 @@ def grouter_moe_fwd_only_static(plan_ws, x, gate_w, W1, W3, W2, y, stream=None, 
     T, d = x.shape
     k = gate_w.shape[1] if gate_w is not None else int(k)
     E, d1, f = W1.shape
-    if d1 != d or tuple(W3.shape) != (E, d, f) or tuple(W2.shape) != (E, f, d) or tuple(y.shape) != (T, d):
+    if d1 != d or W3.shape != (E, d, f) or W2.shape != (E, f, d) or y.shape != (T, d):
         raise ValueError("shape mismatch")
     for t, n in ((x, "x"), (gate_w, "gate_w"), (W1, "W1"), (W3, "W3"), (W2, "W2"), (y, "y")):
         if t is not None:
@@ -251,8 +264,8 @@ def grouter_moe_bwd(plan_ws, x, gate_w, W1, W3, W2, dY, ctx_ws, dX, dW1, dW3, dW
     T, d = x.shape
     k = gate_w.shape[1] if gate_w is not None else int(k)
     E, _, f = W1.shape
-    if (tuple(dY.shape) != (T, d) or tuple(dX.shape) != (T, d) or tuple(dW1.shape) != (E, d, f)
-            or tuple(dW3.shape) != (E, d, f) or tuple(dW2.shape) != (E, f, d)):
+    if (dY.shape != (T, d) or dX.shape != (T, d) or dW1.shape != (E, d, f)
+            or dW3.shape != (E, d, f) or dW2.shape != (E, f, d)):
         raise ValueError("shape mismatch")
     for t, n in ((x, "x"), (gate_w, "gate_w"), (W1, "W1"), (W3, "W3"), (W2, "W2"), (dY, "dY"), (dX, "dX"),
                  (dW1, "dW1"), (dW3, "dW3"), (dW2, "dW2")):
@@ -284,7 +297,7 @@ def grouter_affinity(topk_idx, E, counts, entropy_bits, loads, maxvio, stream=No
     _dev(entropy_bits, "entropy_bits", torch.float64)
     _dev(loads, "loads", torch.int64)
     _dev(maxvio, "maxvio", torch.float64)
-    if tuple(counts.shape) != (S, E) or entropy_bits.numel() != S or loads.numel() != E or maxvio.numel() != 1:
+    if counts.shape != (S, E) or entropy_bits.numel() != S or loads.numel() != E or maxvio.numel() != 1:
         raise ValueError("shape mismatch")
     _check(lib().grouter_affinity(_p(topk_idx), _idx_dtype(topk_idx), S, L, k, E, _p(counts), _p(entropy_bits),
                                   _p(loads), _p(maxvio), _stream(stream)), "grouter_affinity")
@@ -299,7 +312,7 @@ def grouter_sample_placement(topk_idx, E, expert_nodes, n_nodes, comm, best_node
     _dev(expert_nodes, "expert_nodes", torch.int64)
     _dev(comm, "comm", torch.int32)
     _dev(best_node, "best_node", torch.int32)
-    if expert_nodes.numel() != E or tuple(comm.shape) != (S, n_nodes) or best_node.numel() != S:
+    if expert_nodes.numel() != E or comm.shape != (S, n_nodes) or best_node.numel() != S:
         raise ValueError("shape mismatch")
     _check(lib().grouter_sample_placement(_p(topk_idx), _idx_dtype(topk_idx), S, L, k, E, _p(expert_nodes), n_nodes,
                                           _p(comm), _p(best_node), _stream(stream)), "grouter_sample_placement")
@@ -319,8 +332,8 @@ def grouter_sample_stats(topk_idx, E, counts, entropy_bits, loads, maxvio, exper
     _dev(expert_nodes, "expert_nodes", torch.int64)
     _dev(comm, "comm", torch.int32)
     _dev(best_node, "best_node", torch.int32)
-    if (tuple(counts.shape) != (S, E) or entropy_bits.numel() != S or loads.numel() != E or maxvio.numel() != 1
-            or expert_nodes.numel() != E or tuple(comm.shape) != (S, n_nodes) or best_node.numel() != S):
+    if (counts.shape != (S, E) or entropy_bits.numel() != S or loads.numel() != E or maxvio.numel() != 1
+            or expert_nodes.numel() != E or comm.shape != (S, n_nodes) or best_node.numel() != S):
         raise ValueError("shape mismatch")
     _check(lib().grouter_sample_stats(_p(topk_idx), _idx_dtype(topk_idx), S, L, k, E, _p(counts), _p(entropy_bits),
                                       _p(loads), _p(maxvio), _p(expert_nodes), n_nodes, _p(comm), _p(best_node),
@@ -334,7 +347,7 @@ def grouter_coactivation(topk_idx, E, P, stream=None):
     T, k = topk_idx.shape
     _dev(topk_idx, "topk_idx")
     _dev(P, "P", torch.int64)
-    if tuple(P.shape) != (E, E):
+    if P.shape != (E, E):
         raise ValueError("shape mismatch")
     _check(lib().grouter_coactivation(_p(topk_idx), _idx_dtype(topk_idx), T, k, E, _p(P), _stream(stream)),
            "grouter_coactivation")
@@ -347,7 +360,7 @@ def grouter_fold_groups(P, E_T, group_of, stream=None):
     E_S = P.shape[0]
     _dev(P, "P", torch.int64)
     _dev(group_of, "group_of", torch.int32)
-    if tuple(P.shape) != (E_S, E_S) or group_of.numel() != E_S:
+    if P.shape != (E_S, E_S) or group_of.numel() != E_S:
         raise ValueError("shape mismatch")
     _check(lib().grouter_fold_groups(_p(P), E_S, E_T, _p(group_of), _stream(stream)), "grouter_fold_groups")
 
@@ -369,7 +382,7 @@ def grouter_fold_weights(W_s, group_of, E_T, out, stream=None):
     _dev(W_s, "W_s", torch.float32)
     _dev(group_of, "group_of", torch.int32)
     _dev(out, "out", torch.float32)
-    if group_of.numel() != E_S or tuple(out.shape) != (d, E_T):
+    if group_of.numel() != E_S or out.shape != (d, E_T):
         raise ValueError("shape mismatch")
     _check(lib().grouter_fold_weights(_p(W_s), _p(group_of), d, E_S, E_T, _p(out), _stream(stream)),
            "grouter_fold_weights")
