@@ -10,8 +10,8 @@ typedef uint16_t bf16_t;  // raw bfloat16 bit pattern
 
 constexpr int kMaxExperts = 1024;
 constexpr int kPlanWaves = 16;       // waves of a plan workgroup; each takes a contiguous run of the workgroup's slots
-constexpr int kPlanOne = 4096;       // up to this many routed slots one workgroup builds the whole plan
-constexpr int kPlanMaxChunks = 256;  // beyond that the slots are cut into at most this many chunks, one per workgroup
+constexpr int kPlanCounting = 8192;  // up to this many routed slots a plan is built in one launch
+constexpr int kPlanMaxChunks = 256;  // the slots are cut into at most this many chunks, one per workgroup
 constexpr int kTileRowsSmall = 128;  // row-tile heights for which the plan keeps a tile list
 
 static inline __host__ __device__ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }

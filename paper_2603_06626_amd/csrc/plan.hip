@@ -5,16 +5,19 @@
 // come from prefix counts, never from the arrival order of atomics.
 //
 // What bounds a plan is latency: launches, dependent memory round trips, and the serial walk over a wave's slots.
-//   N <= kPlanOne   one launch of one workgroup: its 16 waves count their runs of slots in LDS, scan, and place
-//   larger N        two launches: k_plan_hist counts the chunks; then every chunk's workgroup adds up the counts of the
-//                   chunks before it (at most 256 x E numbers out of L2, cheaper than a launch of its own for a scan)
-//                   and places its slots, while one further workgroup writes counts, offsets, order and tile list
+//   N <= kPlanCounting  one launch: the workgroup of every chunk counts all slots, in LDS, and places its own
+//   larger N            two launches: k_plan_hist counts the chunks; then every chunk's workgroup adds up the counts of the
+//                       chunks before it (at most 256 x E numbers out of L2, cheaper than a launch of its own for a scan)
+//                       and places its slots
+// In both, one further workgroup writes counts, offsets, load order and tile list meanwhile.
 // In the placing pass a wave walks its slots 64 at a time in order; a lane's rank among the lanes of the same expert
 // comes from wave ballots, the running per-expert cursor from the wave's own LDS column.
-// Back-to-back builds, three launches (histogram, finish, scatter) before and now: N = 6, E = 64 13.8 -> 7.8 us; N = 4995,
-// E = 60 16.9 -> 10.0; N = 49152, E = 64 19.1 -> 10.2; N = 131072, E = 128 37.4 -> 13.7.  The most counts to add up, 256 x 1024
-// in each of 257 workgroups: N = 131072, E = 1024 206 -> 70; N = 524288 681 -> 239; N = 2^23 10264 -> 471.  One launch against two at N = 4995:
-// 10.7 against 10.0 us, at 8192: 16.7 against 10.3.
+// Back-to-back builds in a graph, one workgroup that does everything (up to 4096 slots) or two launches / one launch of chunks that
+// count / and with the load ranks shared by all threads: N = 6, E = 64 6.5 / 5.9 / 4.6 us; 1600, E = 64 7.8 / 6.2 / 5.5; 2400, E = 128
+// 10.5 / 8.1 / 5.8; 4096, E = 64 9.8 / 6.6 / 6.4; 4995, E = 60, skewed 8.3 / 6.6 / 6.5; two launches, 20000, E = 128 10.8 / - / 8.9; 49152,
+// E = 64 9.2 / - / 8.5.
+// One launch against two where the line is drawn: N = 4995, E = 60, skewed 6.6 against 8.3 us; 8192, E = 64 7.1 / 8.4; 9003, E = 48,
+// skewed 8.4 / 8.3; 16384, skewed 9.5 / 8.6.  The most counts to add up in two launches, 256 x 1024 in each of 257 workgroups: N = 131072, E = 1024 70 us.
 // Nothing is accumulated into memory that an earlier launch must have cleared, so a plan can be rebuilt in
 // place and the build can be captured into a HIP graph as it is.
 #include "common.hpp"
@@ -86,9 +89,9 @@ struct PlanOut {
     int32_t* tiles; int max_tiles;
 };
 
-// ONE: the only workgroup, which does everything.  Otherwise workgroup c < n_chunks places chunk c and workgroup
-// n_chunks writes what concerns the plan as a whole.
-template <typename IdxT, bool ONE>
+// Workgroup c < n_chunks places chunk c, workgroup n_chunks writes what concerns the plan as a whole.  COUNTING: every workgroup
+// counts all slots itself; otherwise the counts of the chunks come from k_plan_hist.
+template <typename IdxT, bool COUNTING>
 __global__ __launch_bounds__(kPlanThreads) void k_plan_place(const IdxT* __restrict__ idx, int N, int E, int k, int bits, int chunk,
                                                              int n_chunks, const int32_t* __restrict__ chunk_hist,
                                                              const int32_t* __restrict__ chunk_bad, const PlanOut out) {
@@ -100,24 +103,24 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_place(const IdxT* __restr
     __shared__ int32_t s_w[kPlanWaves + 1];
     __shared__ int32_t s_bad;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool place = ONE || (int)blockIdx.x < n_chunks;
-    const bool finish = ONE || (int)blockIdx.x == n_chunks;
-    const int64_t begin = ONE ? 0 : (int64_t)blockIdx.x * chunk;
-    const int64_t end = min((int64_t)N, ONE ? (int64_t)N : begin + chunk);
-    const int per_wave = (ONE ? (N + kPlanThreads - 1) / kPlanThreads : chunk / kPlanThreads) * 64;
+    const bool place = (int)blockIdx.x < n_chunks;
+    const int64_t begin = (int64_t)blockIdx.x * chunk;
+    const int64_t end = min((int64_t)N, begin + chunk);
+    const int per_wave = chunk / kPlanThreads * 64;
     const int64_t w_begin = begin + (int64_t)wave * per_wave, w_end = min(end, w_begin + per_wave);
     int32_t* const my_hist = s_hist + wave * E;
 
     if (tid == 0) s_bad = 0;
     s_cnt[tid] = tid < E ? 0 : -1;   // (no expert: ranks behind every expert)
-    if (!ONE && tid < E) s_before[tid] = 0;
+    s_before[tid] = 0;
+    s_first[tid] = 0;
     if (place)
         for (int e = lane; e < E; e += 64) my_hist[e] = 0;
     __syncthreads();
     bool bad = false;
     if (place)
         for (int64_t i = w_begin + lane; i < w_end; i += 64) atomicAdd(&my_hist[load_expert(idx, i, E, &bad)], 1);
-    if constexpr (!ONE) {
+    if constexpr (!COUNTING) {
         const int n = n_chunks * E, mine = (int)blockIdx.x * E;
         for (int i = tid; i < n; i += kPlanThreads) {
             const int v = chunk_hist[i], e = (int)((uint32_t)i % (uint32_t)E);
@@ -126,27 +129,25 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_place(const IdxT* __restr
                 if (i < mine) atomicAdd(&s_before[e], v);
             }
         }
-        if (finish)
+        if (!place)
             for (int c = tid; c < n_chunks; c += kPlanThreads) bad |= chunk_bad[c] != 0;
+    } else {
+#pragma unroll 8
+        for (int i = tid; i < N; i += kPlanThreads) {
+            const int e = load_expert(idx, i, E, &bad);
+            atomicAdd(&s_cnt[e], 1);
+            if (place && i < begin) atomicAdd(&s_before[e], 1);
+        }
     }
     if (bad) atomicOr(&s_bad, 1);
     __syncthreads();
-    int cnt = 0;
-    if (tid < E) {
-        if constexpr (ONE) {
-#pragma unroll
-            for (int w = 0; w < kPlanWaves; ++w) cnt += s_hist[w * E + tid];
-            s_cnt[tid] = cnt;
-        } else {
-            cnt = s_cnt[tid];
-        }
-    }
+    const int cnt = tid < E ? s_cnt[tid] : 0;
     int total;
     const int off = block_exclusive_scan(cnt, s_w, tid, &total);
     if (tid < E) {
         s_off[tid] = off;
         if (place) {
-            int run = off + (ONE ? 0 : s_before[tid]);
+            int run = off + s_before[tid];
 #pragma unroll
             for (int w = 0; w < kPlanWaves; ++w) {
                 const int t = s_hist[w * E + tid];
@@ -180,23 +181,33 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_place(const IdxT* __restr
             }
         }
     }
-    if (!finish) return;
+    if (place) return;
 
     // offsets, load order, tile list, header
     int32_t* const s_order = s_before;  // expert id at each load rank
     if (tid < E) {
         out.counts[tid] = cnt;
         out.offsets[tid] = off;
-        // heaviest first, ties by lower id
+    }
+    // load ranks, heaviest first, ties by lower id: an expert's comparisons are shared by kPlanThreads / 2^bits threads, which add
+    // up what they find in s_first
+    {
+        const int e = tid & ((1 << bits) - 1), parts = kPlanThreads >> bits;
+        const int per = ((E + parts - 1) / parts + 3) & ~3, from = (tid >> bits) * per;
+        const int mine = s_cnt[e];
         int rank = 0;
 #pragma unroll 4
-        for (int o = 0; o < E; o += 4) {
+        for (int o = from; o < min(E, from + per); o += 4) {   // (entries from E on are -1)
             const int4 co = *(const int4*)(s_cnt + o);
-            rank += ((co.x > cnt) | ((co.x == cnt) & (o < tid))) + ((co.y > cnt) | ((co.y == cnt) & (o + 1 < tid))) +
-                    ((co.z > cnt) | ((co.z == cnt) & (o + 2 < tid))) + ((co.w > cnt) | ((co.w == cnt) & (o + 3 < tid)));
+            rank += ((co.x > mine) | ((co.x == mine) & (o < e))) + ((co.y > mine) | ((co.y == mine) & (o + 1 < e))) +
+                    ((co.z > mine) | ((co.z == mine) & (o + 2 < e))) + ((co.w > mine) | ((co.w == mine) & (o + 3 < e)));
         }
-        s_order[rank] = tid;
-        out.by_load[rank] = tid;
+        if (e < E && rank) atomicAdd(&s_first[e], rank);
+    }
+    __syncthreads();
+    if (tid < E) {
+        s_order[s_first[tid]] = tid;
+        out.by_load[s_first[tid]] = tid;
     }
     if (tid == 0) out.offsets[E] = total;
     __syncthreads();
@@ -241,13 +252,15 @@ static void launch_plan_t(const IdxT* idx, const PlanLayout& L, char* b, hipStre
                       (int32_t*)(b + L.off_row_token), (int32_t*)(b + L.off_tiles_small), L.max_tiles_small};
     int bits = 0;
     while ((1 << bits) < L.E) ++bits;
-    if (L.N <= kPlanOne) {
-        hipLaunchKernelGGL((k_plan_place<IdxT, true>), dim3(1), dim3(kPlanThreads), 0, s, idx, (int)L.N, L.E, L.k, bits, L.chunk, 1, hist, bad, out);
+    const dim3 grid((unsigned)L.n_chunks + 1);
+    if (L.N <= kPlanCounting) {
+        hipLaunchKernelGGL((k_plan_place<IdxT, true>), grid, dim3(kPlanThreads), 0, s, idx, (int)L.N, L.E, L.k, bits, L.chunk, L.n_chunks,
+                           (const int32_t*)nullptr, (const int32_t*)nullptr, out);
         return;
     }
     hipLaunchKernelGGL(k_plan_hist<IdxT>, dim3((unsigned)L.n_chunks), dim3(kPlanThreads), 0, s, idx, L.N, L.E, L.chunk, hist, bad);
-    hipLaunchKernelGGL((k_plan_place<IdxT, false>), dim3((unsigned)L.n_chunks + 1), dim3(kPlanThreads), 0, s, idx, (int)L.N, L.E, L.k, bits,
-                       L.chunk, L.n_chunks, (const int32_t*)hist, (const int32_t*)bad, out);
+    hipLaunchKernelGGL((k_plan_place<IdxT, false>), grid, dim3(kPlanThreads), 0, s, idx, (int)L.N, L.E, L.k, bits, L.chunk, L.n_chunks,
+                       (const int32_t*)hist, (const int32_t*)bad, out);
 }
 
 hipError_t launch_plan_build(const void* idx, int idx_dtype, const PlanLayout& L, void* plan_ws, hipStream_t s) {

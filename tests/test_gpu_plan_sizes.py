@@ -1,4 +1,4 @@
-"""The routing plan at the sizes where its launch shape changes: one workgroup up to 4096 slots, chunks of 2048 slots
+"""The routing plan at the sizes where its launch shape changes: chunks of 2048 slots, one launch up to 8192 slots and two
 beyond, larger chunks past 256 of them.  All arrays are bit-exact against the stable counting sort of the oracle."""
 import numpy as np
 import pytest
@@ -25,6 +25,38 @@ def test_plan_at_the_edges_of_its_launch_shapes(T, k, E, dtype):
     layer.build_plan(torch.from_numpy(idx).to(gpu.DEV))
     for name, got, ref in zip(("counts", "offsets", "row_to_src", "src_to_row"), layer.plan_views(), oracle.plan(idx.astype(np.int32), E)):
         assert np.array_equal(got, ref), name
+
+
+@pytest.mark.parametrize("T,k,E,dtype", [
+    (2048, 1, 3, np.uint8), (2049, 1, 129, np.int32),       # one chunk, one slot in a second
+    (1024, 8, 200, np.uint8), (8193, 1, 200, np.int32),     # last plan of one launch, first of two
+    (1024, 8, 1024, np.int32), (2731, 3, 513, np.int32),    # one thread per expert compares all loads
+    (40, 3, 4, np.int32), (900, 4, 5, np.uint8),            # 256 threads per expert, 128 with ids that do not exist
+])
+def test_plan_and_load_order_at_the_edges_of_one_launch(T, k, E, dtype):
+    """The plan and what depends on the order of experts by load, which the views do not show: a layer whose expert outputs
+    differ by expert.  Equal loads occur."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_06626_amd import workloads as wl
+    from tests import gpu_util as gpu
+    from tests.helpers import rel_max_err
+
+    d = f = 8
+    idx = np.minimum(np.random.default_rng(T + E).geometric(min(0.9, 6.0 / E), size=(T, k)) - 1, E - 1).astype(dtype)
+    _, gates, t = wl.make_custom(T, d, f, E, k, routing="uniform", seed=22, stream=800)
+    layer = gpu.Layer(T, k, E, d, f)
+    layer.build_plan(torch.from_numpy(idx).to(gpu.DEV))
+    for name, got, ref in zip(("counts", "offsets", "row_to_src", "src_to_row"), layer.plan_views(), oracle.plan(idx.astype(np.int32), E)):
+        assert np.array_equal(got, ref), name
+    dev = {n: gpu.to_dev(v) for n, v in t.items()}
+    gw = gpu.to_dev(gates)
+    layer.fwd(dev["x"], gw, dev["W1"], dev["W3"], dev["W2"])
+    grads = layer.bwd(dev["x"], gw, dev["W1"], dev["W3"], dev["W2"], dev["dY"])
+    w = oracle.bf16_bits_to_f32
+    ref = oracle.moe_bwd(w(t["x"]), w(gates), idx.astype(np.int32), w(t["W1"]), w(t["W3"]), w(t["W2"]), w(t["dY"]))
+    for name, g, r in zip(("dX", "dW1", "dW3", "dW2"), grads, ref):     # bar as for the other shapes
+        assert rel_max_err(gpu.to_f64(g), r) <= 1e-2, name
 
 
 @pytest.mark.parametrize("E,dtype", [(33, np.uint8), (1024, np.int32)])
