@@ -240,8 +240,11 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __re
     using Ids = IdWindow<IdxT, 8>;
     const int last = (int)min((S - s) * L * k - Ids::kWindow, (int64_t)0x7fffffff);
     Ids ids[2];   // the next two tokens of this lane
-    ids[0].fetch(base, tid * k, last);
-    ids[1].fetch(base, (tid + kStatThreads) * k, last);
+    // past the sample's end its last token is fetched again, not the next sample's, which then came from memory twice (k = 8, int32,
+    // E = 128, both statistics: 2048 samples of 2048 tokens 37.2 -> 34.4 us, of 1100 tokens 32.8 -> 28.0; 1024 of 1024 17.8 -> 15.9)
+    auto fetch = [&](Ids& window, int t) { window.fetch(base, min(t, L - 1) * k, last); };
+    fetch(ids[0], tid);
+    fetch(ids[1], tid + kStatThreads);
     if (!PLACE) {
         for (int i = tid; i < (E + 1) * (R / 4); i += kStatThreads) reinterpret_cast<uint4*>(s_tab)[i] = uint4{0u, 0u, 0u, 0u};
     } else if (tid <= E) {   // a thread fills a row, so that it loads one node set; each begins at another bank
@@ -270,7 +273,7 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __re
         }
         x = (x & keep_x) | (0xfbfaf9f8u & ~keep_x);
         y = (y & keep_y) | (0xfffefdfcu & ~keep_y);
-        window.fetch(base, (t + 2 * kStatThreads) * k, last);
+        fetch(window, t + 2 * kStatThreads);
         if (__any(t < L && equal_bytes8(x, y))) {
 #pragma unroll
             for (int j = 1; j < 8; ++j) {
