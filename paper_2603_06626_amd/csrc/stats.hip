@@ -822,21 +822,23 @@ __global__ __launch_bounds__(kStatThreads) void k_fold_weights(const float* __re
 }  // namespace
 
 // Whether k_sample_stats8 pays for its table, which it fills and adds up once per sample.  With a workgroup per CU that is
-// one table in a row; up to 1024 samples the CUs hold all tables at once; beyond, tables follow each other, and a placement
-// alone, which has no atomics to save, needs longer samples still.  Measured, general kernel / k_sample_stats8:
-//   32 to 256 samples, k = 8: 256 tokens 4.1 / 4.3 us (placement), 9.5 / 10.0 (both statistics); 512: 5.1 / 5.0, 10.8 / 10.7;
-//   1024: 7.3 / 6.3, 13.1 / 12.0; 4096: 20.3 / 14.0, 26.8 / 20.2; k = 2: 512 4.5 / 4.6, 768 5.4 / 5.2
-//   700 samples, k = 2: 1536 tokens 8.4 / 7.8 (placement), 14.6 / 14.0
-//   200 to 1024 samples, affinity alone, k = 2 to 8: 512 tokens 9.3 / 9.1, 768 11.5 / 11.1
-//   2048 samples, both statistics, k = 8: 512 tokens 20.5 / 22.0; 1024: 25.4 / 24.5; 2048: 38.1 / 31.5; placement alone: 512
-//   8.2 / 9.8; 1024: 12.4 / 12.9; 2048: 22.1 / 19.8; 4096: 39.9 / 32.9; k = 2: 2048 16.9 / 17.9, 4096 30.0 / 29.5
-//   16384 samples of 8 tokens: placement 20 / 43, both 80 / 110
-static bool packed_pays(int64_t S, int L, int k, bool affinity, bool placement) {
+// one table in a row, and a second round of tokens (L > 256) pays for it; up to 1024 samples the CUs hold all tables at once and a
+// fourth round does; beyond, tables follow each other.  A placement alone only reads its table, so it pays earlier, unless k is small.
+// Measured, general kernel / k_sample_stats8, E = 128, 4 nodes, uint8 unless stated:
+//   256 samples, both statistics: k = 8 256 tokens 8.4 / 8.7 us, 257 10.3 / 9.7, 600 11.5 / 10.4; k = 1 257 9.8 / 9.7, 600 10.5 / 10.3;
+//   placement alone: k = 8 257 4.6 / 3.9, k = 1 257 4.2 / 3.9
+//   600 and 1024 samples, both: k = 8 600 tokens 14.2 / 14.6 (1024 samples), 900 15.7 / 14.8; k = 1 900 14.3 / 14.3, int32 14.3 / 14.7;
+//   affinity alone, k = 4: 600 12.0 / 12.4, 900 13.0 / 12.6; placement alone: k = 4 300 4.8 / 4.6 (600), 400 5.2 / 5.0, k = 1 600
+//   5.9 / 6.1, 900 7.0 / 6.3
+//   2048 samples, both: k = 8 1100 24.9 / 25.3, 1300 26.9 / 25.6 (int32 27.9 / 28.7), 2048 32.7 / 28.9; k = 4 1300 24.8 / 24.2, 2048
+//   29.4 / 26.7; k = 1 2048 27.9 / 26.9 (int32, 8192 samples 83 / 86), 4096 41.7 / 35.7; placement alone: k = 4 1024 10.7 / 9.6, k = 1
+//   1100 11.4 / 11.3 (8192 samples 32.9 / 34.8), 2048 17.0 / 13.7; 1500 samples, k = 8: 700 7.9 / 8.2
+static bool packed_pays(int64_t S, int L, int k, bool affinity) {
     const int64_t ids = (int64_t)L * k;
-    if (S <= 1024 && !placement) return L >= 512;
-    if (S <= 256) return L >= 768 || ids >= 4096;
-    if (S <= 1024) return L >= 1024;
-    return ids >= (affinity ? 8192 : 16384);
+    if (S <= 256) return L > 256;
+    if (!affinity) return S <= 1024 ? L > 768 || (L > 256 && k >= 4) : L >= 2048 || (L >= 1024 && k >= 4);
+    if (S <= 1024) return L > 768 && ids >= 1024;
+    return (L > 1280 && ids >= 8192) || (L >= 2048 && ids >= 4096);
 }
 
 // counts == nullptr skips the affinity half, comm == nullptr the placement half.
@@ -855,7 +857,7 @@ hipError_t launch_sample_stats(const void* idx, int idx_dtype, int64_t S, int L,
 #define GROUTER_STATS8(T_, A_, P_, R_)                                                                             \
     hipLaunchKernelGGL((k_sample_stats8<T_, A_, P_, R_>), grid, block, 0, s, (const T_*)idx, S, L, k, E, counts, entropy, \
                        expert_nodes, n_nodes, comm, best_node)
-    const bool fast = k <= 8 && E <= kFastStatE && n_nodes <= kFastStatNodes && L <= kFastStatL && packed_pays(S, L, k, counts != nullptr, comm != nullptr);
+    const bool fast = k <= 8 && E <= kFastStatE && n_nodes <= kFastStatNodes && L <= kFastStatL && packed_pays(S, L, k, counts != nullptr);
     // a column per lane where the table then fits 33 KB
 #define GROUTER_STATS_T(A_, P_)                                                      \
     do {                                                                             \

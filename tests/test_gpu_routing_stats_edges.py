@@ -12,7 +12,9 @@ from tests.test_gpu_routing_stats import DEV, check_all     # noqa: E402
 
 @pytest.mark.parametrize("S,L,k,E,n_nodes,dtype", [
     (3, 255, 8, 128, 16, np.uint8),     # short samples: general kernel; one token short of a workgroup
-    (3, 257, 8, 129, 4, np.uint8),      # one more
+    (3, 256, 8, 128, 16, np.int32),     # the last size of the general kernel
+    (3, 257, 8, 129, 4, np.uint8),      # the first of the packed one
+    (256, 257, 1, 128, 4, np.int32),    # with one id per token
     (2, 300, 8, 247, 16, np.int32),
     (2, 300, 8, 248, 4, np.uint8),
     (2, 100, 9, 64, 4, np.uint8),       # more than 8 ids: the wide form
@@ -23,8 +25,8 @@ from tests.test_gpu_routing_stats import DEV, check_all     # noqa: E402
     (1, 65280, 2, 5, 3, np.uint8),      # longest sample whose votes fit a byte per lane
     (1, 65281, 2, 5, 3, np.uint8),
     (4, 1, 1, 1, 1, np.int32),
-    (3, 511, 8, 128, 16, np.uint8),     # the last size of the general kernel
-    (3, 512, 8, 128, 16, np.uint8),     # the first of the packed one: a column per lane, widest table, most nodes
+    (3, 511, 8, 128, 16, np.uint8),     # one token short of two rounds
+    (3, 512, 8, 128, 16, np.uint8),     # a column per lane, widest table, most nodes
     (3, 513, 8, 129, 5, np.uint8),      # narrower table; one token more than two rounds
     (2, 767, 8, 247, 16, np.int32),     # last E of the packed form
     (2, 768, 1, 247, 1, np.uint8),      # one id per token
@@ -32,9 +34,17 @@ from tests.test_gpu_routing_stats import DEV, check_all     # noqa: E402
     (2, 600, 8, 248, 4, np.uint8),      # general kernel by E
     (2, 600, 8, 64, 17, np.int32),      # by the number of nodes
     (1, 65281, 4, 9, 3, np.int32),      # by the length
-    (257, 1023, 2, 8, 4, np.uint8),     # more samples than CUs: general kernel
-    (257, 1024, 2, 8, 4, np.uint8),     # packed
-    (1025, 1024, 8, 64, 3, np.uint8),   # more samples than fit at once: packed with the affinity, general for placement alone
+    (257, 256, 8, 128, 4, np.int32),    # more samples than CUs: general kernel
+    (257, 257, 4, 128, 4, np.uint8),    # packed for placement alone
+    (300, 768, 3, 60, 4, np.uint8),     # the last size of the general kernel
+    (300, 769, 3, 60, 4, np.int32),     # packed
+    (257, 1023, 1, 8, 4, np.uint8),     # one id per token: general with the affinity, packed for placement alone
+    (257, 1023, 2, 8, 4, np.uint8),
+    (257, 1024, 2, 8, 4, np.uint8),
+    (1025, 1024, 8, 64, 3, np.uint8),   # more samples than fit at once: packed for placement alone, general with the affinity
+    (1025, 1281, 7, 64, 3, np.int32),   # packed
+    (1025, 2047, 2, 200, 4, np.uint8),  # general
+    (1025, 2048, 2, 200, 4, np.uint8),  # packed
     (512, 3, 2, 64, 4, np.uint8),       # loads in one workgroup
     (513, 3, 2, 64, 4, np.uint8),       # and in two launches
 ])
