@@ -20,8 +20,8 @@
 // fp32 accumulators count exactly to 2^24; kCoactMaxRun keeps a wave's counts at 2^21.
 //
 // At the end the waves' parts are summed as integers through LDS and added into P with 64-bit integer atomics, every
-// workgroup beginning elsewhere.  These atomics cost about 0.06 us per workgroup at E = 128, all workgroups queueing for the
-// same cells, so two cells, (r, c) and (r + 1, c), travel in one word while they are summed (T below 2^32, so that the lower
+// workgroup beginning elsewhere.  These atomics cost about 0.03 us per workgroup at E = 128, all workgroups queueing for the
+// same cells (0.06 with one cell per atomic), so two cells, (r, c) and (r + 1, c), travel in one word while they are summed (T below 2^32, so that the lower
 // one never carries).  The words of block (i, j) lie in the storage of block (j, i) below the diagonal, or of the diagonal
 // block itself, and k_coact_finish spreads them out and fills the blocks below the diagonal.
 //
@@ -29,6 +29,7 @@
 // uint8 117 -> 63 us, of which the ORs, reads and clearing take about 41 and the sums 8; 512 x 2048 tokens, E = 128, k = 8, int32
 // 49 -> 27; 700 x 3000, E = 200, k = 5, uint8 113 -> 73 (one cell per atomic 92); 300 x 1500, E = 60, k = 3, int32 21 -> 14.  Cells of one bit
 // (32 tokens a word) or two need fewer reads, but more lanes then OR the same word: 113 -> 89 and 80 instead of 73.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -328,16 +329,21 @@ __global__ void k_fill_u64(unsigned long long* p, int64_t n) {
 
 template <class IdxT>
 static void launch_coact_t(const IdxT* idx, int64_t T, int k, int E, bool packed, unsigned long long* P, hipStream_t s) {
-    // A workgroup has a CU for itself, so there are no more than CUs.  Fewer groups have longer runs (about 1.25 ns a token) but fewer
-    // sums queue at the end (0.06 us each), which is even at sqrt(T / 48) groups.  Measured with 256 / 192 / 128 groups: T = 450000,
-    // E = 60 16.3 / 15.5 / 14.6 us; T = 2^20, E = 128 33.5 / 30.0 / 27.9; T = 2^21 42.5 / 40.6 / 42.2; T = 2^23 70 / 76 / 93 (all with
-    // twice the queueing, see coact_word).
-    constexpr int kTok = 512, kMaxGroups = 256;
-    int64_t groups = (int64_t)std::sqrt((double)T / 48.0);
-    if (groups > kMaxGroups) groups = kMaxGroups;
-    if (groups < (T + kCoactMaxRun - 1) / kCoactMaxRun) groups = (T + kCoactMaxRun - 1) / kCoactMaxRun;
-    if (groups < 1) groups = 1;
-    const int64_t per = ((T + groups - 1) / groups + kTok - 1) / kTok * kTok;
+    // A workgroup has a CU for itself, so there are no more than CUs.  Fewer groups have longer runs but fewer sums queue at the end.
+    // Up to about a hundred groups the queueing does not show, so short lists are cut into the shortest useful runs, and beyond the two
+    // are even at the root of T.  With one id per token only the diagonal is summed, with two on more than 128 experts few cells.
+    // Measured (groups: us), uint8: T = 48000, E = 128, k = 8 8: 22.5, 24: 18.1, 48: 18.1, 94: 18.7; 100000 49: 20.3, 98: 18.9, 196: 23.7;
+    // 450000 48: 27.5, 96: 22.9, 128: 23.1, 256: 26.3; 2^21 128: 36.9, 192: 34.3, 256: 36.4; E = 64, k = 8, 450000 48: 18.1, 96: 15.5, 256: 15.6;
+    // 2^20 128: 18.5, 256: 18.2, on another box 147: 20.8, 256: 23.4; E = 200, k = 4, 150000 48: 31.8, 96: 27.8, 256: 31.6; 2^20 96: 59.9, 192: 49.7, 256:
+    // 51.7; two ids, 100000 48: 29.0, 98: 25.4, 196: 21.8; one id, 450000 64: 44.6, 128: 31.3, 256: 25.9.
+    constexpr int64_t kMaxGroups = 256;
+    // tokens that a workgroup takes in one turn: two slabs per wave, or two passes (more than 8 ids make a turn long, and few tokens on many
+    // experts are worth a workgroup per pass)
+    const int64_t unit = E <= 128 && k <= 8 ? 1024 : T <= 1024 ? 256 : 512;
+    int64_t groups = (int64_t)std::sqrt((double)T / (E <= 128 ? 48.0 : 28.0));
+    groups = std::min(kMaxGroups, std::max(groups, (int64_t)(k == 1 ? 256 : k == 2 && E > 128 ? 192 : 96)));
+    groups = std::max(groups, (T + kCoactMaxRun - 1) / kCoactMaxRun);
+    const int64_t per = ((T + groups - 1) / groups + unit - 1) / unit * unit;
     const dim3 grid((unsigned)((T + per - 1) / per)), block(kCoactThreads);
 #define GROUTER_COACT(EP_)                                                                                         \
     do {                                                                                                           \

@@ -75,6 +75,8 @@ def test_votes_of_the_longest_samples(L, n_nodes):
     (513, 2, 64), (1537, 1, 32), (2049, 3, 128), (1025, 7, 256),    # a last run of one token, whose fetch begins before it
     (511, 4, 65), (1024, 5, 97), (4097, 8, 129),    # one block, several, an odd number; 4 and 8 slots kept
     (5000, 8, 200), (30000, 6, 63), (700, 9, 60), (900, 64, 250),
+    (1025, 2, 200), (1025, 9, 40),                  # runs of 512 tokens; of 256 up to 1024 on many experts or with many ids
+    (98305, 2, 100), (49153, 4, 130), (98305, 2, 129), (131073, 1, 200), (262145, 1, 90),   # one token more than the shortest runs take
 ])
 def test_coactivation_at_the_edges_of_its_kernels(T, k, E, dtype):
     """Exact counts.  Ids repeat inside tokens, and some lie outside [0, E)."""
