@@ -77,15 +77,15 @@ struct CoactShape {
 };
 
 // Where the word of rows (2 rp, 2 rp + 1) and column c of block (bi, bj) is summed.  The storage used is that of block (bj, bi):
-// `cols` rows of `width` cells, taken in order; 16 row pairs (or half of an odd last block) x cols words always fit.  Every
-// second row of blocks uses the lower half of its rows instead of the upper: at E = 128 the 256-byte segments of the upper
-// halves alone fall on half of the memory channels, up to four on one, and the atomics of all workgroups queue there (2048 x
-// 4096 tokens: 71 us, so 63).
+// `cols` rows of 32 cells (of `cols` on the diagonal), taken in order; 16 row pairs (or half of an odd last block) x cols words
+// always fit.  Every second row of blocks uses the lower half of its rows instead of the upper: at E = 128 the 256-byte segments
+// of the upper halves alone fall on half of the memory channels, up to four on one, and the atomics of all workgroups queue
+// there (2048 x 4096 tokens: 71 us, so 63).
 __device__ __forceinline__ size_t coact_word(int E, int bi, int bj, int rp, int c) {
-    const int cols = min(32, E - 32 * bj), width = bi == bj ? cols : 32;
+    const int cols = min(32, E - 32 * bj), half = cols == 32 ? 16 * (bj & 1) : 0;
     const int at = rp * cols + c;
-    const int half = cols == 32 ? 16 * (bj & 1) : 0;
-    return (size_t)(32 * bj + half + at / width) * E + 32 * bi + at % width;
+    const int row = bi == bj ? rp : at >> 5, col = bi == bj ? c : at & 31;   // (dividing `at` by the width took 3 us of a call at E = 256)
+    return (size_t)(32 * bj + half + row) * E + 32 * bi + col;
 }
 
 __device__ __forceinline__ i32x8_t coact_frag(const unsigned char* at) {
