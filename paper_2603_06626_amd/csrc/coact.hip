@@ -57,9 +57,11 @@ struct CoactShape {
     // theirs is ever written out.)
     static constexpr int PITCH = 48, SLAB = (EP + 1) * PITCH, BUFFER = SLABS * SLAB;
     static constexpr int WAVE_BUFFERS = 3, BUFFERS = GROUPS == 1 ? WAVE_BUFFERS * kCoactWaves : 3;
-    // at the end the LDS takes blocks of 4 KB from every wave, ROUND at a time
-    static constexpr int ROUND = NSLOT < 4 ? NSLOT : 4;
-    static constexpr int LDS = BUFFERS * BUFFER > kCoactWaves * ROUND * 4096 ? BUFFERS * BUFFER : kCoactWaves * ROUND * 4096;
+    // at the end the LDS takes blocks of 2 KB from every wave, ROUND at a time
+    static constexpr int ROUND = NSLOT < 10 ? NSLOT : 5;
+    static constexpr int LDS = BUFFERS * BUFFER > kCoactWaves * ROUND * 2048 ? BUFFERS * BUFFER : kCoactWaves * ROUND * 2048;
+    // tokens of a workgroup up to which no wave has more than 2^16 - 1: it has 64 of every 64 * SPLIT, at the end 64 for any rest
+    static constexpr int SHORT = (1 << 16) * SPLIT - 64 * SPLIT;
     static_assert(SLAB % 16 == 0, "cleared in 16-byte pieces");
     // block (row, col) of slot s in wave group g
     static constexpr __device__ __host__ int row_of(int g, int s) {
@@ -249,48 +251,68 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
         else walk(std::integral_constant<int, 3>{});
         static_assert(S::GROUPS == 4, "one walk per group");
     }
-    // ---- the waves' parts meet in LDS, four quads of rows per slot; thread -> quad (slot, v / 4, lane)
+    // ---- the waves' parts meet in LDS, 16 bits of a count at a time and two rows to a word, which halves what is written and read (all of a
+    // wave's blocks are 40 KB of counts at E = 128); thread -> quad of rows (slot, v / 4, lane)
     // accumulator element v of a lane is row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32 of the block
-    constexpr int ROUND = S::ROUND;
-    i32x4_t* const xchg = reinterpret_cast<i32x4_t*>(s_ind);
+    uint2* const xchg = reinterpret_cast<uint2*>(s_ind);
+    auto add_up = [&](auto bits_below) {
+        constexpr int kBelow = decltype(bits_below)::value, ROUND = S::ROUND, kQuads = ROUND * 256;   // quads per wave
 #pragma unroll
-    for (int s0 = 0; s0 < NSLOT; s0 += ROUND) {
-        constexpr int kQuads = ROUND * 256;   // per wave
-        const int n_here = min(ROUND, NSLOT - s0);
-        __syncthreads();
+        for (int s0 = 0; s0 < NSLOT; s0 += ROUND) {
+            const int n_here = min(ROUND, NSLOT - s0);
+            __syncthreads();
 #pragma unroll
-        for (int i = 0; i < ROUND; ++i)
-            if (s0 + i < NSLOT)
+            for (int i = 0; i < ROUND; ++i)
+                if (s0 + i < NSLOT)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    xchg[wave * kQuads + (i * 4 + q) * 64 + lane] =
-                        i32x4_t{(int)acc[s0 + i][4 * q], (int)acc[s0 + i][4 * q + 1], (int)acc[s0 + i][4 * q + 2], (int)acc[s0 + i][4 * q + 3]};
-        __syncthreads();
-        const int n_work = S::GROUPS * n_here * 256;
-        for (int w0 = tid; w0 < n_work; w0 += kCoactThreads) {
-            // every workgroup begins at another place, so that they do not queue for the same cells
-            int w = w0 + (int)(blockIdx.x % (unsigned)(n_work / 64)) * 64;
-            if (w >= n_work) w -= n_work;
-            const int g = w / (n_here * 256), at = w % (n_here * 256);
-            i32x4_t sum = {0, 0, 0, 0};
+                    for (int q = 0; q < 4; ++q) {
+                        auto pair = [&](int v) { return (uint32_t)acc[s0 + i][v] >> kBelow | (uint32_t)acc[s0 + i][v + 1] >> kBelow << 16; };
+                        xchg[wave * kQuads + (i * 4 + q) * 64 + lane] = uint2{pair(4 * q), pair(4 * q + 2)};
+                    }
+            __syncthreads();
+            const int n_work = S::GROUPS * n_here * 256;
+#pragma unroll 3
+            for (int w0 = tid; w0 < n_work; w0 += kCoactThreads) {
+                // every workgroup begins at another place, so that they do not queue for the same cells
+                int w = w0 + (int)(blockIdx.x % (unsigned)(n_work / 64)) * 64;
+                if (w >= n_work) w -= n_work;
+                const int g = w / (n_here * 256), at = w % (n_here * 256);
+                uint32_t sum[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int p = 0; p < S::SPLIT; ++p) sum += xchg[(p * S::GROUPS + g) * kQuads + at];
-            const int slot = s0 + at / 256, q = (at / 64) & 3, l = at & 63;
-            const int bi = S::row_of(g, slot), bj = S::col_of(g, slot), row = 8 * q + 4 * (l >> 5), column = l & 31;
-            if (32 * bj + column >= E) continue;
+                for (int p = 0; p < S::SPLIT; ++p) {
+                    const uint2 part = xchg[(p * S::GROUPS + g) * kQuads + at];
+                    sum[0] += part.x & 0xffffu;
+                    sum[1] += part.x >> 16;
+                    sum[2] += part.y & 0xffffu;
+                    sum[3] += part.y >> 16;
+                }
+                const int slot = s0 + at / 256, q = (at / 64) & 3, l = at & 63;
+                const int bi = S::row_of(g, slot), bj = S::col_of(g, slot), row = 8 * q + 4 * (l >> 5), column = l & 31;
+                if (32 * bj + column >= E) continue;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                if (32 * bi + row + v >= E) break;
-                if (!packed) {
-                    if (sum[v]) atomicAdd(&P[(size_t)(32 * bi + row + v) * E + 32 * bj + column], (unsigned long long)sum[v]);
-                } else if (v % 2 == 0) {   // (rows past E count 0: no id counts there that is not cut off here)
-                    const unsigned long long high = 32 * bi + row + v + 1 < E ? (unsigned long long)sum[v + 1] << 32 : 0ull;
-                    const unsigned long long both = high + (unsigned long long)sum[v];
-                    if (both) atomicAdd(&P[coact_word(E, bi, bj, (row + v) / 2, column)], both);
+                for (int v = 0; v < 4; v += 2) {
+                    const int at_row = 32 * bi + row + v, at_col = 32 * bj + column;
+                    if (at_row >= E) break;
+                    const unsigned long long low = (unsigned long long)sum[v] << kBelow;
+                    const unsigned long long high = at_row + 1 < E ? (unsigned long long)sum[v + 1] << kBelow : 0ull;   // (a row past E is not written)
+                    if (packed) {
+                        if (low | high) atomicAdd(&P[coact_word(E, bi, bj, (row + v) / 2, column)], high << 32 | low);
+                    } else {
+                        if (low) atomicAdd(&P[(size_t)at_row * E + at_col], low);
+                        if (high) atomicAdd(&P[(size_t)(at_row + 1) * E + at_col], high);
+                    }
                 }
             }
         }
+    };
+    if (n > S::SHORT) {   // the upper halves first
+        add_up(std::integral_constant<int, 16>{});
+#pragma unroll
+        for (int s = 0; s < NSLOT; ++s)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[s][v] = (float)((uint32_t)acc[s][v] & 0xffffu);
     }
+    add_up(std::integral_constant<int, 0>{});
 }
 
 // One workgroup per block (bi, bj) on or above the diagonal: spreads out its words if they are packed, and writes block (bj, bi).

@@ -91,8 +91,28 @@ def test_coactivation_at_the_edges_of_its_kernels(T, k, E, dtype):
     assert (P.cpu().numpy() == rs.coactivation(wide, E + 1)[:E, :E]).all()
 
 
+@pytest.mark.parametrize("T,E,pair", [
+    (256 * 1023 * 512, 40, (38, 39)), (256 * 1024 * 512 - 8, 40, (6, 33)),      # 65472 tokens in every wave; 65536, and a shorter last run with as many
+    (256 * 1023 * 512, 64, (32, 33)), (256 * 1024 * 512 - 511, 64, (0, 63)),
+    (256 * 510 * 256, 200, (198, 199)), (256 * 1024 * 128 - 100, 200, (10, 163)),   # the same with 128 of 256 tokens in a wave
+    (256 * 1024 * 128 - 127, 256, (254, 255)),
+    ((1 << 32) - 1, 200, (198, 199)), ((1 << 32) - 1, 200, (96, 97)),           # the most that two counts to a word hold, in both halves
+])
+def test_coactivation_of_one_pair_only(T, E, pair):
+    """Every token picks the same two experts: the largest counts at the limits of 16 bits a wave and 32 bits a word."""
+    idx = torch.tensor(pair, dtype=torch.uint8, device=DEV).repeat(T, 1)
+    P = torch.full((E, E), -1, dtype=torch.int64, device=DEV)
+    b.grouter_coactivation(idx, E, P)
+    del idx
+    ref = torch.zeros((E, E), dtype=torch.int64)
+    for i in pair:
+        for j in pair:
+            ref[i, j] = T
+    assert torch.equal(P.cpu(), ref)
+
+
 def test_coactivation_of_more_tokens_than_half_a_word_counts():
-    """2^32 tokens of one expert and three of another: counts that two to a word could not hold, and 2^21 in every wave's fp32."""
+    """2^32 tokens of one expert and three of another: counts that two to a word could not hold, and up to 2^21 in a wave's fp32."""
     E, T = 200, (1 << 32) + 3
     idx = torch.zeros((T, 1), dtype=torch.uint8, device=DEV)
     idx[T // 2] = idx[5] = idx[T - 1] = 199
