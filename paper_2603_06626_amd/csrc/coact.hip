@@ -167,10 +167,11 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
             ids[0].fetch(base, mine * k, last);
             ids[1].fetch(base, (mine + kCoactThreads) * k, last);
         }
-        for (int i = 0; i < S::WAVE_BUFFERS; ++i) clear(own + i * S::BUFFER, lane, Wave{});
+        clear(own, lane, Wave{});
+        clear(own + S::BUFFER, lane, Wave{});
         in_order();
         set(own, ids[0], mine + 2 * kCoactThreads, nothing);
-        set(own + S::BUFFER, ids[1], mine + 2 * kCoactThreads, nothing);
+        if (wave * 64 + kCoactThreads < n) set(own + S::BUFFER, ids[1], mine + 2 * kCoactThreads, nothing);
         i32x8_t f[2][S::NBLK];
         auto read = [&](i32x8_t (&to)[S::NBLK], int from) {
             in_order();
@@ -179,21 +180,24 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
             in_order();
         };
         read(f[0], 0);
-        int here = 0, next = S::BUFFER, after = 2 * S::BUFFER;
+        int here = 0, next = S::BUFFER, after = 2 * S::BUFFER, t0 = wave * 64;
+        if (t0 + 2 * kCoactThreads < n) clear(own + after, lane, Wave{});
+        // slot s is block (r, r + s - start of row r)
+        auto multiply = [&](const i32x8_t (&x)[S::NBLK], int from, int to) {
+#pragma unroll
+            for (int s = from; s < to; ++s)
+#pragma unroll
+                for (int r = 0; r < S::NBLK; ++r) {
+                    const int start = r * S::NBLK - r * (r - 1) / 2;
+                    if (s >= start && s < start + S::NBLK - r) coact_mfma(x[r], x[r + s - start], acc[s]);
+                }
+        };
         // slab i is multiplied, the fragments of i + 1 are read, i + 2 is set between the MFMAs, and i's buffer is cleared
         auto turn = [&](auto which) {
             constexpr int b = decltype(which)::value;
             read(f[b ^ 1], next);
             constexpr int M = FEW ? N : 1;
-            set(own + after, ids[b], mine + 2 * kCoactThreads, [&](int j) {
-#pragma unroll
-                for (int s = j * S::NSLOT / M; s < (j + 1) * S::NSLOT / M; ++s)
-#pragma unroll
-                    for (int r = 0; r < S::NBLK; ++r) {   // slot s is block (r, r + s - start of row r)
-                        const int start = r * S::NBLK - r * (r - 1) / 2;
-                        if (s >= start && s < start + S::NBLK - r) coact_mfma(f[b][r], f[b][r + s - start], acc[s]);
-                    }
-            });
+            set(own + after, ids[b], mine + 2 * kCoactThreads, [&](int j) { multiply(f[b], j * S::NSLOT / M, (j + 1) * S::NSLOT / M); });
             in_order();
             clear(own + here, lane, Wave{});
             const int free = here;
@@ -201,10 +205,14 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
             next = after;
             after = free;
         };
-        for (int t0 = wave * 64; t0 < n; t0 += 2 * kCoactThreads) {
+        for (; t0 + 2 * kCoactThreads < n; t0 += 2 * kCoactThreads) {
             turn(std::integral_constant<int, 0>{});
-            turn(std::integral_constant<int, 1>{});   // past the end: an empty slab (a way out between the two made the accumulators spill)
+            turn(std::integral_constant<int, 1>{});   // it may set an empty slab (a way out between the two made the accumulators spill)
         }
+        // the last two slabs are set already; nothing is set, fetched or cleared for turns that do not come
+        read(f[1], next);
+        if (t0 < n) multiply(f[0], 0, S::NSLOT);
+        if (t0 + kCoactThreads < n) multiply(f[1], 0, S::NSLOT);
     } else {
         clear(s_ind, tid, Group{});
         clear(s_ind + S::BUFFER, tid, Group{});
