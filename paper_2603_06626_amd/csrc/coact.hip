@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
         clear(own + S::BUFFER, lane, Wave{});
         in_order();
         set(own, ids[0], mine + 2 * kCoactThreads, nothing);
-        if (wave * 64 + kCoactThreads < n) set(own + S::BUFFER, ids[1], mine + 2 * kCoactThreads, nothing);
+        set(own + S::BUFFER, ids[1], mine + 2 * kCoactThreads, nothing);   // (under a condition, the loop's first wait would be for both fetches)
         i32x8_t f[2][S::NBLK];
         auto read = [&](i32x8_t (&to)[S::NBLK], int from) {
             in_order();
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
         if (t0 + kCoactThreads < n) multiply(f[1], 0, S::NSLOT);
     } else {
         clear(s_ind, tid, Group{});
-        clear(s_ind + S::BUFFER, tid, Group{});
+        if (n > TOK) clear(s_ind + S::BUFFER, tid, Group{});
         __syncthreads();
         const bool upper = wave >= kCoactWaves / 2;
         Ids ids{};
@@ -225,9 +225,8 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
         auto walk = [&](auto group) {   // (the branch on the group is outside of the loop: inside, accumulators spilled)
             int here = 0, next = S::BUFFER, after = 2 * S::BUFFER;
             bool odd = false;
-            for (int t0 = 0; t0 < n; t0 += TOK) {
+            auto multiply = [&]() {
                 // (cells past the last token of a short pass are zero, so the slabs need no bound of their own)
-                if (upper != odd) set(s_ind + next, ids, mine + kCoactThreads, nothing);
 #pragma unroll
                 for (int i = 0; i < S::SLABS / S::SPLIT; ++i) {
                     // the two row fragments and two column fragments at a time: all of them do not fit beside the accumulators
@@ -244,6 +243,10 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
+            };
+            for (int t0 = 0; t0 + TOK < n; t0 += TOK) {
+                if (upper != odd) set(s_ind + next, ids, mine + kCoactThreads, nothing);
+                multiply();
                 clear(s_ind + after, tid, Group{});
                 __syncthreads();
                 const int free = here;
@@ -252,6 +255,7 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
                 after = free;
                 odd = !odd;
             }
+            multiply();   // the last pass: nothing is left to set
         };
         if (grp == 0) walk(std::integral_constant<int, 0>{});
         else if (grp == 1) walk(std::integral_constant<int, 1>{});
