@@ -17,18 +17,23 @@
 //   * 256 experts are 36 blocks, which four wave groups share: group g owns block rows g and NBLK-1-g, NBLK+1 blocks whatever
 //     g is.  The workgroup then sets 256 tokens at a time for all waves, in three buffers with one barrier per pass: while
 //     pass p is multiplied, pass p + 1 is set and the buffer of pass p - 1 is cleared for p + 2.
-// fp32 accumulators count exactly to 2^24; kCoactMaxRun keeps a wave's counts at 2^21.
+// fp32 accumulators count exactly to 2^24; kCoactMaxRun keeps a wave's counts at 2^21 and below.
 //
 // At the end the waves' parts are summed as integers through LDS and added into P with 64-bit integer atomics, every
 // workgroup beginning elsewhere.  These atomics cost about 0.03 us per workgroup at E = 128, all workgroups queueing for the
-// same cells (0.06 with one cell per atomic), so two cells, (r, c) and (r + 1, c), travel in one word while they are summed (T below 2^32, so that the lower
-// one never carries).  The words of block (i, j) lie in the storage of block (j, i) below the diagonal, or of the diagonal
-// block itself, and k_coact_finish spreads them out and fills the blocks below the diagonal.
+// same cells (0.06 with one cell per atomic), so two cells, (r, c) and (r + 1, c), travel in one word while they are summed (T
+// below 2^32, so that the lower one never carries).  The words of block (i, j) lie in the storage of block (j, i) below the
+// diagonal, or of the diagonal block itself, and k_coact_finish spreads them out and fills the blocks below the diagonal.
 //
-// Measured (three launches; byte cells, two barriers per pass and one cell per atomic before): 2048 x 4096 tokens, E = 128, k = 8,
-// uint8 117 -> 63 us, of which the ORs, reads and clearing take about 41 and the sums 8; 512 x 2048 tokens, E = 128, k = 8, int32
-// 49 -> 27; 700 x 3000, E = 200, k = 5, uint8 113 -> 73 (one cell per atomic 92); 300 x 1500, E = 60, k = 3, int32 21 -> 14.  Cells of one bit
-// (32 tokens a word) or two need fewer reads, but more lanes then OR the same word: 113 -> 89 and 80 instead of 73.
+// Few tokens are bound by what a workgroup does once: clearing its buffers, and writing and adding up the waves' blocks, which is
+// why those meet in 16-bit halves, why nothing is set or cleared past a run's end and why places are found without a division.
+//
+// Measured (three launches; kernel on byte cells, with two barriers per pass and one cell per atomic / this one): 2048 x 4096 tokens, E = 128,
+// k = 8, uint8 113 / 56 us; 512 x 2048, E = 128, k = 8, int32 48 / 24; 700 x 3000, E = 200, k = 5, uint8 107 / 67 (one cell per atomic 92);
+// 300 x 1500, E = 60, k = 3, int32 22.3 / 13.5; 4000 tokens, k = 8, uint8, E = 128 15.0 / 12.5, E = 256 21.0 / 19.3; 500, E = 256 17.8 / 17.6.
+// More than 8 ids, which are loaded one by one when they are set: 2^20 tokens, k = 16, uint8, E = 128 56 / 28, E = 200, int32 144 / 57; k = 64,
+// uint8, E = 200 152 / 76; 48000, k = 16, E = 128 19.1 / 13.2; 2^23, k = 12, E = 64 125 / 81.
+// Cells of one bit (32 tokens a word) or two need fewer reads, but more lanes then OR the same word: 113 -> 89 and 80 instead of 73 at E = 200.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -222,7 +227,15 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
         if constexpr (FEW) ids.fetch(base, mine * k, last);
         if (!upper) set(s_ind, ids, mine + kCoactThreads, nothing);
         __syncthreads();
-        auto walk = [&](auto group) {   // (the branch on the group is outside of the loop: inside, accumulators spilled)
+        // The four groups walk through loops of their own (with the branch on the group inside of one loop, accumulators spilled) and so meet at
+        // four places of the code, where __syncthreads() is not meant for.  The barrier instruction counts arrivals, wherever they come
+        // from: what must hold is that every walk makes the same number of rounds, which depends on n alone, and leaves none early.
+        auto meet = []() {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        };
+        auto walk = [&](auto group) {
             int here = 0, next = S::BUFFER, after = 2 * S::BUFFER;
             bool odd = false;
             auto multiply = [&]() {
@@ -248,7 +261,7 @@ __global__ __launch_bounds__(kCoactThreads, 2) void k_coactivation(const IdxT* _
                 if (upper != odd) set(s_ind + next, ids, mine + kCoactThreads, nothing);
                 multiply();
                 clear(s_ind + after, tid, Group{});
-                __syncthreads();
+                meet();
                 const int free = here;
                 here = next;
                 next = after;
