@@ -453,34 +453,30 @@ __global__ __launch_bounds__(kStatThreads) void k_maxvio(const unsigned long lon
 // chain of E_S rounds, so what counts is the length of one round.
 //
 // Up to 256 experts one wave runs it, lane l holding the experts l, l + 64, ...: a round is a maximum over the wave in six
-// DPP steps, and one row of the matrix from LDS, staged by the whole workgroup first, or L2.  No barrier is involved.  Scores
-// below 2^24 make one 32-bit key with the expert (fold_keys); otherwise they are doubles, exact below 2^53, and ballots find who
-// holds the maximum; a matrix with larger entries is grouped in 64-bit integers by the same loop.  Measured, a workgroup with
-// three barriers per round / doubles / keys: 128 -> 32 groups 131 / 28 / 21 us; 64 -> 10 - / 12.6 / 9.9; 200 -> 50, which as doubles
-// does not fit the LDS, - / 80 / 47.
-template <int ctrl, class V>
-__device__ __forceinline__ V dpp_max(V v) {
-    union { V v; int w[2]; } a, b;
-    a.v = v;
-    b.w[0] = __builtin_amdgcn_update_dpp(a.w[0], a.w[0], ctrl, 0xf, 0xf, false);
-    b.w[1] = __builtin_amdgcn_update_dpp(a.w[1], a.w[1], ctrl, 0xf, 0xf, false);
-    if constexpr (sizeof(V) == 8 && V(0.5) != V(0)) return __builtin_fmax(a.v, b.v);
-    else return b.v > a.v ? b.v : a.v;
+// DPP steps, and one row of the matrix from LDS, staged by the whole workgroup first, or L2.  No barrier is involved.  Score and
+// expert make one key, of 32 bits where scores stay below 2^24, of 64 below 2^54; larger ones are compared as they are, and
+// ballots find who holds the maximum.
+// Measured, a workgroup with three barriers per round / doubles and ballots, staged where they fit, or int64 from L2 / now.  Scores below
+// 2^24: 128 -> 32 groups 131 / 28.7 / 22.1 us, 64 -> 10 - / 12.8 / 10.4, 200 -> 50 - / 80.8 / 44.2; below 2^54: 128 -> 32 28.7 / 27.1, 64 ->
+// 10 12.8 / 12.5, 200 -> 50 81 / 64, 256 -> 32 114 / 90; beyond: 128 -> 32 37.1 / 31.6, 64 -> 10 16.4 / 14.6, 200 -> 50 77.0 / 77.7.  (A maximum of
+// 64-bit keys as such, five instructions a step, took 31.2 and 71 where two of 32 bits, six instructions each, take 27.1 and 64.)
+template <int ctrl>
+__device__ __forceinline__ long long dpp_max(long long v) {
+    const int low = __builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, 0xf, 0xf, false);
+    const int high = __builtin_amdgcn_update_dpp((int)(v >> 32), (int)(v >> 32), ctrl, 0xf, 0xf, false);
+    const long long other = (long long)((uint64_t)(uint32_t)high << 32 | (uint32_t)low);
+    return other > v ? other : v;
 }
 // the maximum over the wave, in every lane
-template <class V>
-__device__ __forceinline__ V wave_max(V v) {
+__device__ __forceinline__ long long wave_max(long long v) {
     v = dpp_max<0x111>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row of 16
     v = dpp_max<0x112>(v);
     v = dpp_max<0x114>(v);
     v = dpp_max<0x118>(v);
     v = dpp_max<0x142>(v);   // row_bcast:15, row_bcast:31: lane 63 of the wave
     v = dpp_max<0x143>(v);
-    union { V v; int w[2]; } a;
-    a.v = v;
-    a.w[0] = __builtin_amdgcn_readlane(a.w[0], 63);
-    a.w[1] = __builtin_amdgcn_readlane(a.w[1], 63);
-    return a.v;
+    const uint32_t low = (uint32_t)__builtin_amdgcn_readlane((int)v, 63), high = (uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 63);
+    return (long long)((uint64_t)high << 32 | low);
 }
 
 // unsigned: a lane without a source takes 0, and every step is one instruction
@@ -497,8 +493,9 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 }
 
 // row(e, i): entry (e, lane + 64 i) of the matrix
-template <class V, int PER, class Row>
-__device__ __forceinline__ void fold_loop(int E_S, int E_T, int lane, int32_t* __restrict__ group_of, V lowest, Row row) {
+template <int PER, class Row>
+__device__ __forceinline__ void fold_loop(int E_S, int E_T, int lane, int32_t* __restrict__ group_of, Row row) {
+    constexpr long long lowest = -0x7fffffffffffffffLL - 1;
     uint64_t open[PER];   // unassigned experts, by lane
 #pragma unroll
     for (int i = 0; i < PER; ++i) open[i] = __ballot(lane + 64 * i < E_S);
@@ -506,14 +503,14 @@ __device__ __forceinline__ void fold_loop(int E_S, int E_T, int lane, int32_t* _
     int group[PER] = {};
     for (int g = 0; g < E_T; ++g) {
         const int size = g_avg + (g < n_extra ? 1 : 0);
-        V score[PER];
+        long long score[PER];
         for (int m = 0; m < size; ++m) {
             uint64_t best[PER];
             if (m == 0) {   // every unassigned expert ties
 #pragma unroll
                 for (int i = 0; i < PER; ++i) best[i] = open[i];
             } else {
-                V cand[PER], mx = lowest;
+                long long cand[PER], mx = lowest;
 #pragma unroll
                 for (int i = 0; i < PER; ++i) {
                     cand[i] = ((open[i] >> lane) & 1) ? score[i] : lowest;
@@ -535,7 +532,7 @@ __device__ __forceinline__ void fold_loop(int E_S, int E_T, int lane, int32_t* _
             if (m + 1 < size) {
 #pragma unroll
                 for (int i = 0; i < PER; ++i) {
-                    const V p = row(pick, i);
+                    const long long p = row(pick, i);
                     score[i] = m == 0 ? p : score[i] + p;
                 }
             }
@@ -546,10 +543,12 @@ __device__ __forceinline__ void fold_loop(int E_S, int E_T, int lane, int32_t* _
         if (lane + 64 * i < E_S) group_of[lane + 64 * i] = group[i];
 }
 
-// The same loop on keys of 32 bits, score * 256 + 255 - expert: their maximum over the wave is one instruction a step and names the
-// expert, the lowest of those that tie.  For scores below 2^24 and up to 255 experts; the matrix in LDS holds scores * 256.
-template <int PER>
-__device__ __forceinline__ void fold_keys(int E_S, int E_T, int lane, int32_t* __restrict__ group_of, const uint32_t* s_P) {
+// The same loop on keys, score * 256 + 255 - expert: their maximum over the wave names the expert, the lowest of those that tie.
+// Key: uint32_t for scores below 2^24 and up to 255 experts, where a step of the maximum is one instruction; long long for scores
+// below 2^54 in size.  row(at): entry at + mine of the matrix, mine the lane's first expert or the last one there is.
+template <class Key, int PER, class Row>
+__device__ __forceinline__ void fold_keys(int E_S, int E_T, int lane, int mine, int32_t* __restrict__ group_of, Row row) {
+    using U = std::make_unsigned_t<Key>;   // (the keys of experts that are taken may wrap)
     uint64_t open[PER];   // unassigned experts, by lane
     uint32_t alive[PER];  // the same, as a mask of each lane's own
     int group[PER] = {};
@@ -559,20 +558,20 @@ __device__ __forceinline__ void fold_keys(int E_S, int E_T, int lane, int32_t* _
         alive[i] = lane + 64 * i < E_S ? ~0u : 0u;
     }
     const int g_avg = E_S / E_T, n_extra = E_S % E_T;
-    const uint32_t* const mine = s_P + min(lane, E_S - 1);
+    const int last = E_S * E_S - 1 - mine;
     for (int g = 0; g < E_T; ++g) {
         const int size = g_avg + (g < n_extra ? 1 : 0);
-        uint32_t key[PER];
+        U key[PER];
         int pick = 0;   // the group's first member: the lowest unassigned expert
 #pragma unroll
         for (int i = PER - 1; i >= 0; --i)
             if (open[i]) pick = 64 * i + (int)__builtin_ctzll(open[i]);
         for (int m = 0;; ++m) {
             const bool done = m + 1 >= size;
-            uint32_t p[PER];
+            U p[PER];
             if (!done) {   // requested first: the rest of the bookkeeping runs meanwhile (what a lane without an expert reads is masked)
 #pragma unroll
-                for (int i = 0; i < PER; ++i) p[i] = mine[min(pick * E_S + 64 * i, E_S * E_S - min(lane, E_S - 1) - 1)];
+                for (int i = 0; i < PER; ++i) p[i] = (U)row(min(pick * E_S + 64 * i, last));
             }
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
@@ -583,13 +582,28 @@ __device__ __forceinline__ void fold_keys(int E_S, int E_T, int lane, int32_t* _
                 }
             }
             if (done) break;
-            uint32_t mx = 0;
+            if constexpr (sizeof(Key) == 4) {
+                uint32_t mx = 0;
 #pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                key[i] = m == 0 ? p[i] + 255u - (uint32_t)(lane + 64 * i) : key[i] + p[i];
-                mx = max(mx, key[i] & alive[i]);
+                for (int i = 0; i < PER; ++i) {
+                    key[i] = (p[i] << 8) + (m == 0 ? 255u - (uint32_t)(lane + 64 * i) : key[i]);
+                    mx = max(mx, key[i] & alive[i]);
+                }
+                pick = 255 - (int)(wave_max_u32(mx) & 255u);
+            } else {
+                // the upper words first, offset so that none is 0, then the lower ones of those that hold the maximum
+                uint32_t high[PER], mx = 0, mn = 0;
+#pragma unroll
+                for (int i = 0; i < PER; ++i) {
+                    key[i] = (p[i] << 8) + (m == 0 ? (U)(255 - (lane + 64 * i)) : key[i]);
+                    high[i] = ((uint32_t)(key[i] >> 32) ^ 0x80000000u) & alive[i];
+                    mx = max(mx, high[i]);
+                }
+                mx = wave_max_u32(mx);
+#pragma unroll
+                for (int i = 0; i < PER; ++i) mn = max(mn, high[i] == mx ? (uint32_t)key[i] : 0u);
+                pick = 255 - (int)(wave_max_u32(mn) & 255u);
             }
-            pick = 255 - (int)(wave_max_u32(mx) & 255u);
         }
     }
 #pragma unroll
@@ -597,51 +611,81 @@ __device__ __forceinline__ void fold_keys(int E_S, int E_T, int lane, int32_t* _
         if (lane + 64 * i < E_S) group_of[lane + 64 * i] = group[i];
 }
 
-// The matrix is staged in LDS as keys (E_S <= 200) if no score of a group can reach 2^24, otherwise as doubles (E_S <= 128) if all
-// scores are exact in them; what does not fit is read from L2.
+// Up to 128 experts the matrix is staged in LDS as it is, and keys of either width are made of its entries.  Up to 200 experts its low
+// words are staged, for the narrow keys; what does not fit is read from L2.  Scores of 2^54 and more, in size, are compared as they
+// are.  The checks are a few instructions per entry in short loops: one workgroup runs this code once, and what it waits for then
+// is the code itself (entries kept in registers, the same instructions 16 times: 128 -> 32 22 -> 25 us).  A division per entry, to leave
+// out the diagonal, which decides nothing, took 1 us at 64 experts and 3 at 150.
 constexpr int kFoldStaged = 200;
 template <int PER>   // E_S <= 64 PER
 __global__ __launch_bounds__(1024) void k_fold_groups_wave(const long long* __restrict__ P, int E_S, int E_T, int32_t* __restrict__ group_of) {
-    constexpr bool DOUBLES = PER <= 2;
-    constexpr int kWords = DOUBLES ? 2 * 64 * PER * 64 * PER : kFoldStaged * kFoldStaged;
-    constexpr long long kExact = 1ll << 43;   // entries below this: sums of up to 1024 of them are exact in double
+    constexpr bool WHOLE = PER <= 2;
+    constexpr int kWords = WHOLE ? 2 * 64 * PER * 64 * PER : kFoldStaged * kFoldStaged;
+    constexpr int kLarge = 1 << 14;   // upper words of entries below 2^46 in size: sums of up to 256 of them are below 2^54
     __shared__ __attribute__((aligned(16))) uint32_t s_words[kWords];
     __shared__ int s_large, s_wide;
-    double* const s_P = reinterpret_cast<double*>(s_words);
-    const int tid = threadIdx.x;
+    long long* const s_P = reinterpret_cast<long long*>(s_words);
+    const int tid = threadIdx.x, n = E_S * E_S;
+    if (E_S == E_T) {
+        if (tid < E_S) group_of[tid] = tid;
+        return;
+    }
     if (tid == 0) s_large = s_wide = 0;
     __syncthreads();
-    const bool fits = DOUBLES || E_S <= kFoldStaged;
-    const unsigned long long limit = 0xffffffull / (unsigned)((E_S + E_T - 1) / E_T);
-    bool large = false, wide = !fits;
+    const uint32_t limit = 0xffffffu / (unsigned)((E_S + E_T - 1) / E_T);
+    int high = 0, low = 0;       // largest and smallest upper word
+    uint32_t most = 0;           // largest lower word
+    bool wide = !WHOLE && E_S > kFoldStaged;
+    int i = tid;
+    if (!wide) {
+        uint32_t at = (uint32_t)tid % (uint32_t)(E_S + 1);   // 0 on the diagonal
+        const uint32_t step = 1024u % (uint32_t)(E_S + 1);
+        auto look = [&](int i, long long v) {
+            if constexpr (WHOLE) s_P[i] = v;
+            else s_words[i] = (uint32_t)v;
+            v = at == 0 ? 0 : v;
+            high = max(high, (int)(v >> 32));
+            low = min(low, (int)(v >> 32));
+            most = max(most, (uint32_t)v);
+            at += step;
+            at = min(at, at - (uint32_t)(E_S + 1));
+        };
+        if constexpr (WHOLE) {
 #pragma unroll 8
-    for (int i = tid; i < E_S * E_S; i += 1024) {
-        const long long v = P[i];
-        if (i % (E_S + 1) != 0) {   // (the diagonal decides nothing)
-            large |= v >= kExact || v <= -kExact;
-            wide |= (unsigned long long)v > limit;
+            for (; i < n; i += 1024) look(i, P[i]);
+        } else {   // (large entries are seen early, and no more is staged then)
+            for (; i + 7 * 1024 < n && !wide; i += 8 * 1024) {
+                long long v[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v[q] = P[i + 1024 * q];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) look(i + 1024 * q, v[q]);
+                wide = __any(high | low | (int)(most > limit)) != 0;
+            }
+            if (!wide)
+                for (; i < n; i += 1024) look(i, P[i]);
         }
-        if (fits) s_words[i] = (uint32_t)v << 8;
+        wide = (high | low) != 0 || most > limit;
     }
-    if (large) s_large = 1;
+    if constexpr (!WHOLE) {
+#pragma unroll 8
+        for (; i < n; i += 1024) {
+            const int v = (int)(P[i] >> 32);
+            high = max(high, v);
+            low = min(low, v);
+        }
+    }
+    if (high >= kLarge || low < -kLarge) s_large = 1;
     if (wide) s_wide = 1;
     __syncthreads();
-    if (DOUBLES && s_wide && !s_large) {
-        for (int i = tid; i < E_S * E_S; i += 1024) s_P[i] = (double)P[i];
-        __syncthreads();
-    }
     if (tid >= 64) return;
-    auto entry = [&](int e, int i) { return e * E_S + min(tid + 64 * i, E_S - 1); };
-    if (!s_wide) {
-        fold_keys<PER>(E_S, E_T, tid, group_of, s_words);
-    } else if (!s_large) {
-        fold_loop<double, PER>(E_S, E_T, tid, group_of, -1e300, [&](int e, int i) -> double {
-            if constexpr (DOUBLES) return s_P[entry(e, i)];
-            else return (double)P[entry(e, i)];
-        });
-    } else {
-        fold_loop<long long, PER>(E_S, E_T, tid, group_of, -0x7fffffffffffffffLL - 1, [&](int e, int i) { return P[entry(e, i)]; });
-    }
+    const int mine = min(tid, E_S - 1);
+    const uint32_t* const words = s_words + (WHOLE ? 2 * mine : mine);
+    const long long* whole = P + mine;
+    if constexpr (WHOLE) whole = s_P + mine;
+    if (!s_wide) fold_keys<uint32_t, PER>(E_S, E_T, tid, mine, group_of, [&](int at) { return words[WHOLE ? 2 * at : at]; });
+    else if (!s_large) fold_keys<long long, PER>(E_S, E_T, tid, mine, group_of, [&](int at) { return whole[at]; });
+    else fold_loop<PER>(E_S, E_T, tid, group_of, [&](int e, int i) { return whole[e * E_S + min(64 * i, E_S - 1 - mine)]; });
 }
 
 // More than 256 experts: one workgroup, thread j <-> source expert j.

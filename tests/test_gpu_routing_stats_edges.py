@@ -129,14 +129,34 @@ def test_coactivation_of_more_tokens_than_half_a_word_counts():
                                            (64, 8, 349524), (64, 8, 349525), (128, 16, 349524), (128, 16, 349525),
                                            (200, 25, 349524), (200, 25, 349525)])
 def test_fold_groups_sizes_ties_and_large_entries(E_S, E_T, scale):
-    """Few distinct values make many ties; entries of 2^44 and more go through the integer loop (their sums would still be
-    exact in doubles), sums of 2^24 and more through the one in doubles."""
+    """Few distinct values make many ties; sums of 2^24 and more are grouped by 64-bit keys, entries of 2^46 and more, up to 6 *
+    2^44 here, by the loop that compares scores."""
     rng = np.random.default_rng(E_S)
     P = rng.integers(0, 4, size=(E_S, E_S)).astype(np.int64) * scale + (rng.integers(0, 2, size=(E_S, E_S)) if scale > 1 else 0)
     P = P + P.T
     grp = torch.full((E_S,), -1, dtype=torch.int32, device=DEV)
     b.grouter_fold_groups(torch.from_numpy(P).to(DEV), E_T, grp)
     assert (grp.cpu().numpy() == rs.fold_groups(P, E_T)).all()
+
+
+@pytest.mark.parametrize("E_S,E_T", [(5, 2), (60, 1), (64, 9), (128, 1), (128, 30), (180, 50), (200, 7), (201, 30), (256, 1), (256, 60)])
+@pytest.mark.parametrize("lowest,highest", [(-3, 3), (-1, 0), (-(1 << 46), (1 << 46) - 1), (-(1 << 46) - 1, 0), (0, 1 << 46), ((1 << 32) - 2, (1 << 32) + 1)])
+@pytest.mark.parametrize("where", ["all", "last"])
+def test_fold_groups_at_the_limits_of_64_bit_keys(E_S, E_T, lowest, highest, where):
+    """Entries of either sign up to the sizes that 64-bit keys take, and one more; in every place, or only in the last ones looked at."""
+    rng = np.random.default_rng(E_S + E_T)
+    extreme = rng.choice([lowest, highest, lowest + 1, highest - 1], size=(E_S, E_S))
+    P = extreme if where == "all" else rng.integers(0, 4, size=(E_S, E_S))
+    P[-1] = extreme[-1]
+    P = np.triu(P) + np.triu(P, 1).T
+    P[:, -1] = P[-1] = extreme[-1]
+    P[np.arange(E_S), np.arange(E_S)] = rng.choice([1 << 62, 0, -(1 << 62)], size=E_S)     # the diagonal decides nothing
+    P = P.astype(np.int64)
+    grp = torch.full((E_S,), -1, dtype=torch.int32, device=DEV)
+    b.grouter_fold_groups(torch.from_numpy(P).to(DEV), E_T, grp)
+    zero = P.copy()
+    zero[np.arange(E_S), np.arange(E_S)] = 0
+    assert (grp.cpu().numpy() == rs.fold_groups(zero, E_T)).all()
 
 
 def _groups_in_doubles(P, E_T):
