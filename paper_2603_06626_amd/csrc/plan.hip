@@ -16,8 +16,8 @@
 // count / and with the load ranks shared by all threads: N = 6, E = 64 6.5 / 5.9 / 4.6 us; 1600, E = 64 7.8 / 6.2 / 5.5; 2400, E = 128
 // 10.5 / 8.1 / 5.8; 4096, E = 64 9.8 / 6.6 / 6.4; 4995, E = 60, skewed 8.3 / 6.6 / 6.5; two launches, 20000, E = 128 10.8 / - / 8.9; 49152,
 // E = 64 9.2 / - / 8.5.
-// One launch against two where the line is drawn: N = 4995, E = 60, skewed 6.6 against 8.3 us; 8192, E = 64 7.1 / 8.4; 9003, E = 48,
-// skewed 8.4 / 8.3; 16384, skewed 9.5 / 8.6.  The most counts to add up in two launches, 256 x 1024 in each of 257 workgroups: N = 131072, E = 1024 70 us.
+// One launch against two where the line is drawn: 8192 slots, E = 64, uniform 7.0 against 8.2 us, all on one expert 7.8 / 10.0.
+// The most counts to add up in two launches, 256 x 1024 in each of 257 workgroups: N = 131072, E = 1024 70 us.
 // Nothing is accumulated into memory that an earlier launch must have cleared, so a plan can be rebuilt in
 // place and the build can be captured into a HIP graph as it is.
 #include "common.hpp"
@@ -91,6 +91,12 @@ struct PlanOut {
 
 // Workgroup c < n_chunks places chunk c, workgroup n_chunks writes what concerns the plan as a whole.  COUNTING: every workgroup
 // counts all slots itself; otherwise the counts of the chunks come from k_plan_hist.
+// It does so in eight columns per expert, which lanes take in turn: where many slots pick the same expert, adds to one word wait for
+// each other, a wave's 64 in a row (one word each for the slots of an expert and for those in earlier chunks / eight columns, one
+// word for both, E = 64: N = 8192 on one expert 18.4 / 7.8 us, Zipf 10.3 / 7.0, uniform 7.4 / 7.0; N = 4096 11.5 / 7.2, 7.6 / 6.4, 6.5 / 6.4;
+// N = 2000 8.0 / 6.8, 6.2 / 6.0, 6.1 / 6.1; four columns 8.5 at N = 8192 on one expert, sixteen as eight).
+constexpr int kPlanColumns = 8;
+static_assert(kPlanCounting < 1 << 16 && kPlanColumns % 4 == 0, "a column's word holds two counts");
 template <typename IdxT, bool COUNTING>
 __global__ __launch_bounds__(kPlanThreads) void k_plan_place(const IdxT* __restrict__ idx, int N, int E, int k, int bits, int chunk,
                                                              int n_chunks, const int32_t* __restrict__ chunk_hist,
@@ -102,6 +108,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_place(const IdxT* __restr
     __shared__ int32_t s_first[kMaxExperts + 1];  // first tile of each load rank
     __shared__ int32_t s_w[kPlanWaves + 1];
     __shared__ int32_t s_bad;
+    __shared__ uint4 s_col[COUNTING ? kMaxExperts * kPlanColumns / 4 : 1];   // [expert][column]: slots, and above them those in earlier chunks
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool place = (int)blockIdx.x < n_chunks;
     const int64_t begin = (int64_t)blockIdx.x * chunk;
@@ -116,6 +123,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_place(const IdxT* __restr
     s_first[tid] = 0;
     if (place)
         for (int e = lane; e < E; e += 64) my_hist[e] = 0;
+    if (COUNTING)
+        for (int i = tid; i < E * (kPlanColumns / 4); i += kPlanThreads) s_col[i] = uint4{0u, 0u, 0u, 0u};
     __syncthreads();
     bool bad = false;
     if (place)
@@ -132,16 +141,27 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_place(const IdxT* __restr
         if (!place)
             for (int c = tid; c < n_chunks; c += kPlanThreads) bad |= chunk_bad[c] != 0;
     } else {
+        uint32_t* const column = reinterpret_cast<uint32_t*>(s_col) + tid % kPlanColumns;
 #pragma unroll 8
-        for (int i = tid; i < N; i += kPlanThreads) {
-            const int e = load_expert(idx, i, E, &bad);
-            atomicAdd(&s_cnt[e], 1);
-            if (place && i < begin) atomicAdd(&s_before[e], 1);
-        }
+        for (int i = tid; i < N; i += kPlanThreads)
+            atomicAdd(&column[load_expert(idx, i, E, &bad) * kPlanColumns], place && i < begin ? 0x10001u : 1u);
     }
     if (bad) atomicOr(&s_bad, 1);
     __syncthreads();
-    const int cnt = tid < E ? s_cnt[tid] : 0;
+    int cnt = 0;
+    if (tid < E) {
+        if constexpr (COUNTING) {
+            uint32_t both = 0;
+#pragma unroll
+            for (int q = 0; q < kPlanColumns / 4; ++q) {
+                const uint4 c = s_col[tid * (kPlanColumns / 4) + q];
+                both += c.x + c.y + c.z + c.w;
+            }
+            s_cnt[tid] = (int)(both & 0xffffu);
+            s_before[tid] = (int)(both >> 16);
+        }
+        cnt = s_cnt[tid];
+    }
     int total;
     const int off = block_exclusive_scan(cnt, s_w, tid, &total);
     if (tid < E) {

@@ -59,6 +59,25 @@ def test_plan_and_load_order_at_the_edges_of_one_launch(T, k, E, dtype):
         assert rel_max_err(gpu.to_f64(g), r) <= 1e-2, name
 
 
+@pytest.mark.parametrize("T,E,dtype", [
+    (2048, 1, np.uint8), (2049, 2, np.int32), (4097, 7, np.uint8), (8192, 1, np.int32), (8192, 64, np.uint8), (8192, 1024, np.int32), (8193, 300, np.int32),
+])
+@pytest.mark.parametrize("where", ["first", "last", "two"])
+def test_plan_of_slots_that_pick_one_expert(T, E, dtype, where):
+    """All slots on one expert, or all but every 64th, so that the lanes of a wave count the same word."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_util as gpu
+
+    idx = np.full((T, 1), 0 if where == "first" else E - 1, dtype=dtype)
+    if where == "two":
+        idx[5::64] = E // 2
+    layer = gpu.Layer(T, 1, E, 8, 8)
+    layer.build_plan(torch.from_numpy(idx).to(gpu.DEV))
+    for name, got, ref in zip(("counts", "offsets", "row_to_src", "src_to_row"), layer.plan_views(), oracle.plan(idx.astype(np.int32), E)):
+        assert np.array_equal(got, ref), name
+
+
 @pytest.mark.parametrize("E,dtype", [(33, np.uint8), (1024, np.int32)])
 @pytest.mark.parametrize("where", ["first", "middle", "last"])
 def test_a_bad_id_in_any_chunk_is_reported_and_counts_as_expert_0(E, dtype, where):
