@@ -868,21 +868,22 @@ __global__ __launch_bounds__(kStatThreads) void k_fold_weights(const float* __re
 // Whether k_sample_stats8 pays for its table, which it fills and adds up once per sample.  With a workgroup per CU that is
 // one table in a row, and a second round of tokens (L > 256) pays for it; up to 1024 samples the CUs hold all tables at once and a
 // fourth round does; beyond, tables follow each other.  A placement alone only reads its table, so it pays earlier, unless k is small.
-// Measured, general kernel / k_sample_stats8, E = 128, 4 nodes, uint8 unless stated:
-//   256 samples, both statistics: k = 8 256 tokens 8.4 / 8.7 us, 257 10.3 / 9.7, 600 11.5 / 10.4; k = 1 257 9.8 / 9.7, 600 10.5 / 10.3;
-//   placement alone: k = 8 257 4.6 / 3.9, k = 1 257 4.2 / 3.9
-//   600 and 1024 samples, both: k = 8 600 tokens 14.2 / 14.6 (1024 samples), 900 15.7 / 14.8; k = 1 900 14.3 / 14.3, int32 14.3 / 14.7;
-//   affinity alone, k = 4: 600 12.0 / 12.4, 900 13.0 / 12.6; placement alone: k = 4 300 4.8 / 4.6 (600), 400 5.2 / 5.0, k = 1 600
-//   5.9 / 6.1, 900 7.0 / 6.3
-//   2048 samples, both: k = 8 1100 24.9 / 25.3, 1300 26.9 / 25.6 (int32 27.9 / 28.7), 2048 32.7 / 28.9; k = 4 1300 24.8 / 24.2, 2048
-//   29.4 / 26.7; k = 1 2048 27.9 / 26.9 (int32, 8192 samples 83 / 86), 4096 41.7 / 35.7; placement alone: k = 4 1024 10.7 / 9.6, k = 1
-//   1100 11.4 / 11.3 (8192 samples 32.9 / 34.8), 2048 17.0 / 13.7; 1500 samples, k = 8: 700 7.9 / 8.2
-static bool packed_pays(int64_t S, int L, int k, bool affinity) {
+// The general kernel's adds wait for each other where tokens agree, the packed one's do not, so the lines lie where the two are about
+// even on evenly spread ids: there the one loses up to 1.07 on these, the other up to 5 on ids that all tokens share.
+// Measured, general kernel / k_sample_stats8, uint8, 4 nodes; E = 128 evenly spread, E = 8, E = 128 with all tokens alike:
+//   256 samples of 257 tokens, both statistics: k = 8 11.0 / 10.4 us, 11.3 / 10.4, 12.4 / 10.4; k = 1 9.8 / 9.7; placement alone: k = 1 4.2 / 3.9
+//   1024 samples, affinity alone: k = 8 512 tokens 12.3 / 12.6, 13.1 / 11.0, 24.3 / 12.6; 600 13.0 / 13.7, 14.1 / 11.8, 26.8 / 13.4
+//   both: 769 tokens, k = 8 16.7 / 16.1, 16.7 / 13.8, 34.0 / 15.8; k = 1 15.0 / 15.2, 13.9 / 13.4, 15.1 / 15.2
+//   placement alone, E = 128: k = 4 300 tokens (600 samples) 4.8 / 4.6, 400 5.2 / 5.0; k = 1 600 5.9 / 6.1, 900 7.0 / 6.3
+//   2048 samples, affinity alone: k = 8 1024 tokens 20.1 / 20.6, 24.3 / 16.7, 67.9 / 20.6; both: k = 8 700 tokens 21.1 / 23.7, 22.6 / 19.9,
+//   52.7 / 24.4; 1100 25.5 / 26.2, 28.9 / 22.2, 75.0 / 26.0; k = 4, E = 128 2048 tokens 29.4 / 26.7; k = 1 27.9 / 26.9 (int32, 8192 samples 83 / 86)
+//   placement alone: 1024 tokens, k = 3 11.3 / 10.6, 11.3 / 10.2, 11.3 / 10.5; k = 1, E = 128 11.4 / 11.3 at 1100 (8192 samples 32.9 / 34.8)
+static bool packed_pays(int64_t S, int L, int k, bool affinity, bool placement) {
     const int64_t ids = (int64_t)L * k;
     if (S <= 256) return L > 256;
     if (!affinity) return S <= 1024 ? L > 768 || (L > 256 && k >= 4) : L >= 2048 || (L >= 1024 && k >= 4);
-    if (S <= 1024) return L > 768 && ids >= 1024;
-    return (L > 1280 && ids >= 8192) || (L >= 2048 && ids >= 4096);
+    if (S <= 1024) return L >= (placement ? 1024 : 512) || (L > 768 && ids >= 1024);
+    return ids >= 8192 || (L >= 2048 && ids >= 4096);
 }
 
 // counts == nullptr skips the affinity half, comm == nullptr the placement half.
@@ -901,7 +902,7 @@ hipError_t launch_sample_stats(const void* idx, int idx_dtype, int64_t S, int L,
 #define GROUTER_STATS8(T_, A_, P_, R_)                                                                             \
     hipLaunchKernelGGL((k_sample_stats8<T_, A_, P_, R_>), grid, block, 0, s, (const T_*)idx, S, L, k, E, counts, entropy, \
                        expert_nodes, n_nodes, comm, best_node)
-    const bool fast = k <= 8 && E <= kFastStatE && n_nodes <= kFastStatNodes && L <= kFastStatL && packed_pays(S, L, k, counts != nullptr);
+    const bool fast = k <= 8 && E <= kFastStatE && n_nodes <= kFastStatNodes && L <= kFastStatL && packed_pays(S, L, k, counts != nullptr, comm != nullptr);
     // a column per lane where the table then fits 33 KB
 #define GROUTER_STATS_T(A_, P_)                                                      \
     do {                                                                             \

@@ -36,13 +36,16 @@ from tests.test_gpu_routing_stats import DEV, check_all     # noqa: E402
     (1, 65281, 4, 9, 3, np.int32),      # by the length
     (257, 256, 8, 128, 4, np.int32),    # more samples than CUs: general kernel
     (257, 257, 4, 128, 4, np.uint8),    # packed for placement alone
-    (300, 768, 3, 60, 4, np.uint8),     # the last size of the general kernel
+    (300, 768, 3, 60, 4, np.uint8),     # both statistics in one call: the last size of the general kernel
     (300, 769, 3, 60, 4, np.int32),     # packed
-    (257, 1023, 1, 8, 4, np.uint8),     # one id per token: general with the affinity, packed for placement alone
+    (257, 1023, 1, 8, 4, np.uint8),     # one id per token: both statistics general, either alone packed
     (257, 1023, 2, 8, 4, np.uint8),
     (257, 1024, 2, 8, 4, np.uint8),
-    (1025, 1024, 8, 64, 3, np.uint8),   # more samples than fit at once: packed for placement alone, general with the affinity
-    (1025, 1281, 7, 64, 3, np.int32),   # packed
+    (257, 511, 2, 8, 4, np.uint8),      # general for the affinity alone
+    (257, 512, 2, 8, 4, np.uint8),      # packed
+    (1025, 1023, 8, 64, 3, np.uint8),   # more samples than fit at once: general
+    (1025, 1024, 8, 64, 3, np.uint8),   # packed
+    (1025, 1281, 7, 64, 3, np.int32),   # the same with fewer ids per token
     (1025, 2047, 2, 200, 4, np.uint8),  # general
     (1025, 2048, 2, 200, 4, np.uint8),  # packed
     (512, 3, 2, 64, 4, np.uint8),       # loads in one workgroup
