@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_stats8(const IdxT* __re
     };
     for (int t0 = 0; t0 < L; t0 += 2 * kStatThreads) {
         turn(ids[0], t0 + tid);
-        turn(ids[1], t0 + kStatThreads + tid);   // past the end: spare rows only
+        if (t0 + kStatThreads < L) turn(ids[1], t0 + kStatThreads + tid);
     }
     if (PLACE) {
         // four byte counts become two words of two 16-bit sums (at most 64 * 255 each), which are added over the wave: chains that
