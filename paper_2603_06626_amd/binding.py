@@ -102,24 +102,27 @@ def _p(t):
     return None if t is None else t.data_ptr()     # (the argument types make a pointer of it)
 
 
-def _first_raw_stream() -> int:
-    """The current stream's handle; from the second call on without building a torch.cuda.Stream, which costs about as much as
-    a kernel launch."""
-    global _raw_stream
+def _find_raw_stream():
+    """How to get the current stream's handle: from torch itself, since building a torch.cuda.Stream for it on every call costs
+    about as much as a kernel launch."""
     import torch
 
-    handle = torch.cuda.current_stream().cuda_stream     # initialises the device on the first call
-    get, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
-    if get is not None and get(device()) == handle:
-        _raw_stream = lambda: get(device())              # noqa: E731
-    return handle
+    get, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device   # (the latter initialises torch.cuda)
+    if get is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: get(device())
 
 
-_raw_stream = _first_raw_stream
+_raw_stream = None
 
 
 def _stream(stream=None):
-    return _raw_stream() if stream is None else stream.cuda_stream
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        _raw_stream = _find_raw_stream()
+    return _raw_stream()
 
 
 def _dev(t, name, dtype=None):

@@ -400,6 +400,24 @@ def test_step_replays_from_a_hip_graph(gpu):
         b.grouter_plan_status(layer.plan)
 
 
+def test_calls_go_to_the_stream_that_is_current():
+    """Without a stream of its own a call goes to the current one, whichever was current at the first call."""
+    from paper_2603_06626_amd import binding as b
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    sides = [torch.cuda.Stream(), torch.cuda.Stream()]
+    assert len({s.cuda_stream for s in sides} | {torch.cuda.current_stream().cuda_stream}) == 3
+    for forget in (True, False):
+        for s in (torch.cuda.current_stream(), sides[0], torch.cuda.current_stream(), sides[1]):
+            if forget:
+                b._raw_stream = None
+            with torch.cuda.stream(s):
+                assert b._stream() == s.cuda_stream == torch.cuda.current_stream().cuda_stream
+                assert b._stream(sides[1]) == sides[1].cuda_stream
+            assert b._stream() == torch.cuda.current_stream().cuda_stream
+
+
 def test_next_plan_built_on_a_side_stream_while_a_layer_runs(gpu):
     """Plan streaming: every call takes a stream and a plan is a caller-owned buffer, so the plan of the next
     micro-batch can be built on a side stream while the current one computes.  Results must not change."""
