@@ -33,6 +33,8 @@
 // 300 x 1500, E = 60, k = 3, int32 22.3 / 13.5; 4000 tokens, k = 8, uint8, E = 128 15.0 / 12.5, E = 256 21.0 / 19.3; 500, E = 256 17.8 / 17.6.
 // More than 8 ids, which are loaded one by one when they are set: 2^20 tokens, k = 16, uint8, E = 128 56 / 28, E = 200, int32 144 / 57; k = 64,
 // uint8, E = 200 152 / 76; 48000, k = 16, E = 128 19.1 / 13.2; 2^23, k = 12, E = 64 125 / 81.
+// Slower than on byte cells where all tokens pick the same experts, since then eight lanes OR each word and few cells queue, which would
+// allow more workgroups: k = 8, uint8, E = 64, 2^23 tokens 60 / 71, 450000 16 / 19, E = 128 18 / 24; with a dozen experts in use 18 / 19.
 // Cells of one bit (32 tokens a word) or two need fewer reads, but more lanes then OR the same word: 113 -> 89 and 80 instead of 73 at E = 200.
 #include <algorithm>
 #include <cmath>
