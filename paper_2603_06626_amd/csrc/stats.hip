@@ -881,6 +881,9 @@ __global__ __launch_bounds__(kStatThreads) void k_fold_weights(const float* __re
 //   2048 samples, affinity alone: k = 8 1024 tokens 20.1 / 20.6, 24.3 / 16.7, 67.9 / 20.6; both: k = 8 700 tokens 21.1 / 23.7, 22.6 / 19.9,
 //   52.7 / 24.4; 1100 25.5 / 26.2, 28.9 / 22.2, 75.0 / 26.0; k = 4, E = 128 2048 tokens 29.4 / 26.7; k = 1 27.9 / 26.9 (int32, 8192 samples 83 / 86)
 //   placement alone: 1024 tokens, k = 3 11.3 / 10.6, 11.3 / 10.2, 11.3 / 10.5; k = 1, E = 128 11.4 / 11.3 at 1100 (8192 samples 32.9 / 34.8)
+// The lines take no account of id type, E and nodes: over uint8 and int32, E = 8, 64, 128, 200 and 247, 4 and 16 nodes, the packed kernel is at
+// most 1.04 times the general one's time where it is chosen for fewer than 1024 tokens or at its lines (int32, k = 3, 8192 samples of 2048
+// tokens 71.9 / 74.2, 16 nodes, 1024 samples of 300, placement 7.5 / 7.8), but for the 1.07 above.
 static bool packed_pays(int64_t S, int L, int k, bool affinity, bool placement) {
     const int64_t ids = (int64_t)L * k;
     if (S <= 256) return L > 256;
