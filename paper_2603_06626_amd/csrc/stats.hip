@@ -872,7 +872,7 @@ __global__ __launch_bounds__(kStatThreads) void k_fold_weights(const float* __re
 // one table in a row, and a second round of tokens (L > 256) pays for it; up to 1024 samples the CUs hold all tables at once and a
 // fourth round does; beyond, tables follow each other.  A placement alone only reads its table, so it pays earlier, unless k is small.
 // The general kernel's adds wait for each other where tokens agree, the packed one's do not, so the lines lie where the two are about
-// even on evenly spread ids: there the one loses up to 1.07 on these, the other up to 5 on ids that all tokens share.
+// even on evenly spread ids: there the one loses up to 1.08 on these, the other up to 5 on ids that all tokens share (not with one id).
 // Measured, general kernel / k_sample_stats8, uint8, 4 nodes; E = 128 evenly spread, E = 8, E = 128 with all tokens alike:
 //   256 samples of 257 tokens, both statistics: k = 8 11.0 / 10.4 us, 11.3 / 10.4, 12.4 / 10.4; k = 1 9.8 / 9.7; placement alone: k = 1 4.2 / 3.9
 //   1024 samples, affinity alone: k = 8 512 tokens 12.3 / 12.6, 13.1 / 11.0, 24.3 / 12.6; 600 13.0 / 13.7, 14.1 / 11.8, 26.8 / 13.4
@@ -881,14 +881,14 @@ __global__ __launch_bounds__(kStatThreads) void k_fold_weights(const float* __re
 //   2048 samples, affinity alone: k = 8 1024 tokens 20.1 / 20.6, 24.3 / 16.7, 67.9 / 20.6; both: k = 8 700 tokens 21.1 / 23.7, 22.6 / 19.9,
 //   52.7 / 24.4; 1100 25.5 / 26.2, 28.9 / 22.2, 75.0 / 26.0; k = 4, E = 128 2048 tokens 29.4 / 26.7; k = 1 27.9 / 26.9 (int32, 8192 samples 83 / 86)
 //   placement alone: 1024 tokens, k = 3 11.3 / 10.6, 11.3 / 10.2, 11.3 / 10.5; k = 1, E = 128 11.4 / 11.3 at 1100 (8192 samples 32.9 / 34.8)
-// The lines take no account of id type, E and nodes: over uint8 and int32, E = 8, 64, 128, 200 and 247, 4 and 16 nodes, the packed kernel is at
-// most 1.04 times the general one's time where it is chosen for fewer than 1024 tokens or at its lines (int32, k = 3, 8192 samples of 2048
-// tokens 71.9 / 74.2, 16 nodes, 1024 samples of 300, placement 7.5 / 7.8), but for the 1.07 above.
+// The lines take no account of id type, E and nodes.  Over uint8 and int32, E = 8, 64, 128, 200 and 247, 4 and 16 nodes, the packed kernel's
+// largest losses on evenly spread ids are: int32, k = 8, both, 2048 samples of 1100 tokens 27.5 / 29.7; 8192 of 1024, 16 nodes 84.5 / 90.5 (E = 8,
+// 4 nodes 79.7 / 63.9); affinity alone, k = 3, 1024 of 600 12.8 / 13.6; one id, which stays with the general kernel there, 12.4 / 13.3.
 static bool packed_pays(int64_t S, int L, int k, bool affinity, bool placement) {
     const int64_t ids = (int64_t)L * k;
     if (S <= 256) return L > 256;
     if (!affinity) return S <= 1024 ? L > 768 || (L > 256 && k >= 4) : L >= 2048 || (L >= 1024 && k >= 4);
-    if (S <= 1024) return L >= (placement ? 1024 : 512) || (L > 768 && ids >= 1024);
+    if (S <= 1024) return (k > 1 && L >= (placement ? 1024 : 512)) || (L > 768 && ids >= 1024);
     return ids >= 8192 || (L >= 2048 && ids >= 4096);
 }
 

@@ -43,6 +43,7 @@ from tests.test_gpu_routing_stats import DEV, check_all     # noqa: E402
     (257, 1024, 2, 8, 4, np.uint8),
     (257, 511, 2, 8, 4, np.uint8),      # general for the affinity alone
     (257, 512, 2, 8, 4, np.uint8),      # packed
+    (257, 768, 1, 8, 4, np.uint8),      # general with one id
     (1025, 1023, 8, 64, 3, np.uint8),   # more samples than fit at once: general
     (1025, 1024, 8, 64, 3, np.uint8),   # packed
     (1025, 1281, 7, 64, 3, np.int32),   # the same with fewer ids per token
